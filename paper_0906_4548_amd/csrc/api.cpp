@@ -1027,7 +1027,7 @@ extern "C" int dgp_interp_backward(dgp_plan* pl, const double* mesh, int ncomp, 
   if (grad_pos && !mesh) return fail(DGP_E_INVALID, "grad_pos needs the mesh");
   TRY(require_batch1(pl));
   launch_interp_backward(pl->n, pl->box, mesh, ncomp, pos, pos_is_fp32, np, grad_out, grad_pos, grad_mesh, pl->grid,
-                         pl->fx_state, pl->flag, static_cast<hipStream_t>(stream));
+                         pl->fx_state, pl->red, pl->flag, static_cast<hipStream_t>(stream));
   LAUNCHCHK();
   return DGP_OK;
 }

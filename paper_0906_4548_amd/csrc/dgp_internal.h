@@ -254,10 +254,11 @@ void launch_interp_kick_drift(int n, double box, const void* mesh3, int mesh_fp3
 void launch_deposit_backward(int n, double box, const void* pos, int pos_fp32, long long np,
                              const double* grad_delta, double* grad_pos, hipStream_t s);
 // adjoint of launch_interp for dL/dout = g [nc][np]: grad_pos [3][np] (optional) and grad_mesh [nc][n3]
-// (optional, deterministic fixed-point sums); grid: n3 int64 scratch, st: 3 words of scratch
+// (optional, deterministic fixed-point sums); grid: n3 int64 scratch, st: 3 words of scratch, red:
+// absmean_scratch_doubles(n3, 1) doubles of scratch, 16-byte aligned
 void launch_interp_backward(int n, double box, const double* mesh, int nc, const void* pos, int pos_fp32, long long np,
                             const double* g, double* grad_pos, double* grad_mesh, long long* grid,
-                            unsigned long long* st, int* bad, hipStream_t s);
+                            unsigned long long* st, double* red, int* bad, hipStream_t s);
 template <typename T>
 void launch_convert(size_t count, const void* in, int in_fp32, T* out, hipStream_t s);
 

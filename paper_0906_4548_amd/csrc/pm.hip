@@ -463,16 +463,13 @@ k_interp_grad_pos(const double* __restrict__ mesh, const P* __restrict__ pos, lo
   grad[2 * np + p] = gz;
 }
 
-__global__ void k_zero_scale_state(unsigned long long* __restrict__ st, int* __restrict__ bad) {
-  if (threadIdx.x < 3) st[threadIdx.x] = 0ull;
-  if (threadIdx.x == 0) *bad = 0;
-}
-
-// st[0]: bit pattern of max |g| (non-negative doubles order like their bit patterns), st[1]: the
-// largest fixed-point mass of the grid; *bad raised for a non-finite g
+// part[block] = {bit pattern of the block's max |g| (non-negative doubles order like their bit
+// patterns), its largest fixed-point mass of the grid}; *bad raised for a non-finite g.  Bound by
+// reading g and the grid once (3 x 2.1M values on 128^3, 67 MB: 16 us); one atomicMax per wavefront
+// on two shared words instead of the partials took 747 us, serialised on those words.
 __global__ void __launch_bounds__(256)
 k_max_abs_and_mass(const double* __restrict__ g, size_t count, const long long* __restrict__ grid, size_t n3,
-                   unsigned long long* __restrict__ st, int* __restrict__ bad) {
+                   ulonglong2* __restrict__ part, int* __restrict__ bad) {
   double m = 0.0;
   long long mm = 0;
   bool ok = true;
@@ -488,17 +485,37 @@ k_max_abs_and_mass(const double* __restrict__ g, size_t count, const long long* 
     mm = max(mm, __shfl_xor(mm, o, 64));
   }
   if (!ok) atomicOr(bad, 1);
+  __shared__ double wm[4];
+  __shared__ long long wmm[4];
   if ((threadIdx.x & 63) == 0) {
-    atomicMax(&st[0], (unsigned long long)__double_as_longlong(m));
-    atomicMax(&st[1], (unsigned long long)mm);
+    wm[threadIdx.x >> 6] = m;
+    wmm[threadIdx.x >> 6] = mm;
+  }
+  lds_barrier();
+  if (threadIdx.x == 0) {
+    m = fmax(fmax(wm[0], wm[1]), fmax(wm[2], wm[3]));
+    mm = max(max(wmm[0], wmm[1]), max(wmm[2], wmm[3]));
+    part[blockIdx.x] = make_ulonglong2((unsigned long long)__double_as_longlong(m), (unsigned long long)mm);
   }
 }
 
-// st[2] = e with (max|g|) (mass bound) 2^e < 2^62
-__global__ void k_interp_scale(unsigned long long* __restrict__ st) {
+// st[2] = e with (max|g|) (mass bound) 2^e < 2^62, from the partial maxima (one wavefront)
+__global__ void __launch_bounds__(64)
+k_interp_scale(const ulonglong2* __restrict__ part, int blocks, unsigned long long* __restrict__ st) {
+  double gmax = 0.0;
+  long long mm = 0;
+  for (int i = threadIdx.x; i < blocks; i += 64) {
+    const ulonglong2 v = part[i];
+    gmax = fmax(gmax, __longlong_as_double((long long)v.x));
+    mm = max(mm, (long long)v.y);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    gmax = fmax(gmax, __shfl_xor(gmax, o, 64));
+    mm = max(mm, __shfl_xor(mm, o, 64));
+  }
   if (threadIdx.x != 0) return;
-  const double gmax = __longlong_as_double((long long)st[0]);
-  const double mass = double((long long)st[1]) * 0x1p-40 * (1.0 + 0x1p-20) + 0x1p-20;
+  const double mass = double(mm) * 0x1p-40 * (1.0 + 0x1p-20) + 0x1p-20;
   const double bound = gmax * mass;
   int e = 0;
   if (bound > 0.0 && isfinite(bound)) {
@@ -700,8 +717,8 @@ void launch_zero_flag(int* bad, hipStream_t s) { hipLaunchKernelGGL(k_zero_flag,
 
 template <typename P, int NC>
 static void interp_bwd_t(int n, double box, const double* mesh, const P* pos, long long np, const double* g,
-                         double* grad_pos, double* grad_mesh, long long* grid, unsigned long long* st, int* bad,
-                         hipStream_t s) {
+                         double* grad_pos, double* grad_mesh, long long* grid, unsigned long long* st, double* red,
+                         int* bad, hipStream_t s) {
   const double scale = double(n) / box;
   const size_t n3 = (size_t)n * n * n;
   if (grad_pos)
@@ -711,11 +728,12 @@ static void interp_bwd_t(int n, double box, const double* mesh, const P* pos, lo
   auto* acc = reinterpret_cast<unsigned long long*>(grad_mesh);
   launch_fill_zero(acc, NC * n3, s);
   launch_fill_zero(grid, n3, s);
-  hipLaunchKernelGGL(k_zero_scale_state, dim3(1), dim3(64), 0, s, st, bad);
+  launch_zero_flag(bad, s);
   launch_deposit(n, box, pos, sizeof(P) == 4, np, grid, bad, s);
-  hipLaunchKernelGGL(k_max_abs_and_mass, dim3(grid_strided(n3)), dim3(256), 0, s, g, (size_t)NC * np, grid, n3, st,
-                     bad);
-  hipLaunchKernelGGL(k_interp_scale, dim3(1), dim3(64), 0, s, st);
+  const int blocks = int(absmean_scratch_doubles(n3, 1) / 2);   // one pair of words per block
+  hipLaunchKernelGGL(k_max_abs_and_mass, dim3(blocks), dim3(256), 0, s, g, (size_t)NC * np, grid, n3,
+                     reinterpret_cast<ulonglong2*>(red), bad);
+  hipLaunchKernelGGL(k_interp_scale, dim3(1), dim3(64), 0, s, reinterpret_cast<const ulonglong2*>(red), blocks, st);
   const unsigned gch = unsigned((np + kIgChunk - 1) / kIgChunk);
   hipLaunchKernelGGL((k_interp_grad_mesh_bin<P, NC>), dim3(gch), dim3(256), 0, s, pos, np, n, scale, g, st, acc);
   hipLaunchKernelGGL(k_fixed_to_double, dim3(grid_strided(NC * n3)), dim3(256), 0, s, acc, NC * n3, st, bad);
@@ -723,9 +741,9 @@ static void interp_bwd_t(int n, double box, const double* mesh, const P* pos, lo
 
 void launch_interp_backward(int n, double box, const double* mesh, int nc, const void* pos, int pos_fp32, long long np,
                             const double* g, double* grad_pos, double* grad_mesh, long long* grid,
-                            unsigned long long* st, int* bad, hipStream_t s) {
+                            unsigned long long* st, double* red, int* bad, hipStream_t s) {
 #define DGP_IB(P, NC) \
-  interp_bwd_t<P, NC>(n, box, mesh, static_cast<const P*>(pos), np, g, grad_pos, grad_mesh, grid, st, bad, s)
+  interp_bwd_t<P, NC>(n, box, mesh, static_cast<const P*>(pos), np, g, grad_pos, grad_mesh, grid, st, red, bad, s)
   if (pos_fp32) {
     if (nc == 1) DGP_IB(float, 1);
     else if (nc == 2) DGP_IB(float, 2);
