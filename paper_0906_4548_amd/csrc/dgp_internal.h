@@ -121,8 +121,8 @@ struct RowTile {
 // 1D form for particle chunks: consecutive chunks (neighbouring Lagrangian blocks, whose
 // mesh boxes overlap) run on the same XCD and share its L2.
 __device__ __forceinline__ long long xcd_chunk() {
-  const long long g = gridDim.x, i = blockIdx.x;
-  return ((g & 7) == 0) ? (i & 7) * (g >> 3) + (i >> 3) : i;
+  const long long q = gridDim.x >> 3, r = gridDim.x & 7, x = blockIdx.x & 7;   // XCD x: q (+ 1 for x < r) chunks
+  return x * q + (x < r ? x : r) + (blockIdx.x >> 3);
 }
 
 __device__ __forceinline__ void xcd_tile(int& bx, int& by) {

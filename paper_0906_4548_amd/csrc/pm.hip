@@ -280,32 +280,12 @@ __device__ __forceinline__ size_t corner_index(const Cic& c, int a, int b, int c
   return (ix * n + iy) * n + iz;
 }
 
-// interpolate an NC-component mesh [NC][N^3] to particles
-template <int NC, typename M>
-__device__ __forceinline__ void gather_mesh(const M* __restrict__ mesh, size_t n3, int n, const Cic& c,
-                                            double (&f)[NC]) {
-  gather_corners<NC>(
-      c, [&](int a, int b, int cc, int k) { return double(mesh[(size_t)k * n3 + corner_index(c, a, b, cc, n)]); }, f);
-}
-
-// out[k][p] = sum_c W_c(x_p) mesh[k][c]
-template <typename P, typename M, int NC>
-__global__ void __launch_bounds__(256)
-k_interp(const M* __restrict__ mesh, const P* __restrict__ pos, long long np, int n, double scale,
-         double* __restrict__ out) {
-  const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (p >= np) return;
-  const Cic c = cic_of(pos, np, p, n, scale);
-  double f[NC];
-  gather_mesh<NC, M>(mesh, (size_t)n * n * n, n, c, f);
-#pragma unroll
-  for (int k = 0; k < NC; ++k) out[(size_t)k * np + p] = f[k];
-}
-
-// Leapfrog with momenta at half steps: p += kick * g(x_n); x += drift * p; wrap into [0, L).
-// The force mesh of the chunk's box is staged in LDS (coalesced rows), with the chunking of the
-// binned deposit (smaller chunks: three components per cell in LDS); chunks with larger boxes
-// gather from the mesh.
+// LDS staging of the particle gathers.  A workgroup takes a chunk of consecutive particles; when
+// the periodic box of their cells fits, the box's mesh values are staged in LDS (coalesced rows,
+// each cell read once) and the corners gathered from there, otherwise each corner is read from the
+// mesh.  What bounds the direct gather is the L2-to-L1 traffic of its rows (a wavefront of an 8^3
+// block touches ~24 lines of 128 bytes per component), which staging replaces by ~3.3 cells per
+// particle.
 #ifndef DGP_GATHER_CHUNK
 #define DGP_GATHER_CHUNK 256
 #endif
@@ -317,18 +297,15 @@ constexpr int kGatherPPT = kGatherChunk / 256;
 constexpr int kGatherCap = DGP_GATHER_BIN_CAP;
 static_assert(kGatherChunk % 256 == 0, "chunk must be a multiple of the workgroup size");
 
-template <typename P, typename M>
-__global__ void __launch_bounds__(256)
-k_interp_kick_drift_bin(const M* __restrict__ mesh3, P* __restrict__ pos, P* __restrict__ vel, long long np,
-                        int n, double scale, double box, double kick, double drift) {
+// A chunk's box staged from the NC-component mesh [NC][N^3] into fl[NC][kGatherCap]; every thread of
+// the workgroup calls it, and `apply(p, k, cell, at)` then runs for each of the thread's particles
+// with at(a, b, c, component), the mesh value of a corner.
+template <int NC, typename P, typename M, class Apply>
+__device__ __forceinline__ void gather_chunk(const M* __restrict__ mesh, const P* __restrict__ pos,
+                                             const P (&xs)[kGatherPPT][3], long long np, long long p0, int n,
+                                             double scale, M* fl, const Apply& apply) {
 #pragma clang fp contract(off)
-  __shared__ M fl[3 * kGatherCap];
   const size_t n3 = (size_t)n * n * n;
-  const long long p0 = xcd_chunk() * kGatherChunk;
-  // positions and velocities are loaded together up front and kept in registers
-  P xs[kGatherPPT][3], vs[kGatherPPT][3];
-  load_chunk<kGatherPPT>(pos, np, p0, xs);
-  load_chunk<kGatherPPT>(vel, np, p0, vs);
   Cic cr, cs[kGatherPPT];
   int off[kGatherPPT][3], bx[6];
   const bool binned = chunk_box<kGatherPPT>(pos, xs, np, n, scale, p0, kGatherCap, cr, cs, off, bx);
@@ -336,9 +313,8 @@ k_interp_kick_drift_bin(const M* __restrict__ mesh3, P* __restrict__ pos, P* __r
     const int vol = bx[3] * bx[4] * bx[5];
     for (int i = threadIdx.x; i < vol; i += 256) {
       const size_t g = box_cell(i, cr, bx, n);
-      fl[i] = mesh3[g];
-      fl[kGatherCap + i] = mesh3[n3 + g];
-      fl[2 * kGatherCap + i] = mesh3[2 * n3 + g];
+#pragma unroll
+      for (int q = 0; q < NC; ++q) fl[q * kGatherCap + i] = mesh[(size_t)q * n3 + g];
     }
   }
   lds_barrier();
@@ -346,23 +322,57 @@ k_interp_kick_drift_bin(const M* __restrict__ mesh3, P* __restrict__ pos, P* __r
   for (int k = 0; k < kGatherPPT; ++k) {
     const long long p = p0 + threadIdx.x + k * 256;
     if (p >= np) continue;
-    double f[3];
     // the cell and weights again from the position (the chunk box's arithmetic): not holding
-    // them across the staging loop and its barrier leaves 65 instead of 75 VGPRs (occupancy
-    // 6 -> 7-8; 512^3 float32 particles 2.71 -> 2.30 ms, 256^3 unchanged)
+    // them across the staging loop and its barrier leaves the kick-drift 65 instead of 75 VGPRs
+    // (occupancy 6 -> 7-8; 512^3 float32 particles 2.71 -> 2.30 ms, 256^3 unchanged)
     const double s3[3] = {double(xs[k][0]) * scale, double(xs[k][1]) * scale, double(xs[k][2]) * scale};
-    const Cic ck = cic_at(s3, n);
+    const Cic c = cic_at(s3, n);
     if (binned) {
-      gather_corners<3>(
-          ck,
-          [&](int a, int b, int cc, int q) {
-            const int li = ((off[k][0] + a - bx[0]) * bx[4] + (off[k][1] + b - bx[1])) * bx[5] + (off[k][2] + cc - bx[2]);
-            return double(fl[q * kGatherCap + li]);
-          },
-          f);
+      apply(p, k, c, [&](int a, int b, int cc, int q) {
+        const int li = ((off[k][0] + a - bx[0]) * bx[4] + (off[k][1] + b - bx[1])) * bx[5] + (off[k][2] + cc - bx[2]);
+        return double(fl[q * kGatherCap + li]);
+      });
     } else {
-      gather_mesh<3, M>(mesh3, n3, n, ck, f);
+      apply(p, k, c, [&](int a, int b, int cc, int q) {
+        return double(mesh[(size_t)q * n3 + corner_index(c, a, b, cc, n)]);
+      });
     }
+  }
+}
+
+// out[k][p] = sum_c W_c(x_p) mesh[k][c]
+template <typename P, typename M, int NC>
+__global__ void __launch_bounds__(256)
+k_interp(const M* __restrict__ mesh, const P* __restrict__ pos, long long np, int n, double scale,
+         double* __restrict__ out) {
+  __shared__ M fl[NC * kGatherCap];
+  const long long p0 = xcd_chunk() * kGatherChunk;
+  P xs[kGatherPPT][3];
+  load_chunk<kGatherPPT>(pos, np, p0, xs);
+  gather_chunk<NC>(mesh, pos, xs, np, p0, n, scale, fl, [&](long long p, int, const Cic& c, const auto& at) {
+    double f[NC];
+    gather_corners<NC>(c, at, f);
+#pragma unroll
+    for (int q = 0; q < NC; ++q) __builtin_nontemporal_store(f[q], &out[(size_t)q * np + p]);
+  });
+}
+
+// Leapfrog with momenta at half steps: p += kick * g(x_n); x += drift * p; wrap into [0, L), the force
+// gathered through the staged box.
+template <typename P, typename M>
+__global__ void __launch_bounds__(256)
+k_interp_kick_drift_bin(const M* __restrict__ mesh3, P* __restrict__ pos, P* __restrict__ vel, long long np,
+                        int n, double scale, double box, double kick, double drift) {
+#pragma clang fp contract(off)
+  __shared__ M fl[3 * kGatherCap];
+  const long long p0 = xcd_chunk() * kGatherChunk;
+  // positions and velocities are loaded together up front and kept in registers
+  P xs[kGatherPPT][3], vs[kGatherPPT][3];
+  load_chunk<kGatherPPT>(pos, np, p0, xs);
+  load_chunk<kGatherPPT>(vel, np, p0, vs);
+  gather_chunk<3>(mesh3, pos, xs, np, p0, n, scale, fl, [&](long long p, int k, const Cic& c, const auto& at) {
+    double f[3];
+    gather_corners<3>(c, at, f);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const size_t i = (size_t)d * np + p;
@@ -374,6 +384,32 @@ k_interp_kick_drift_bin(const M* __restrict__ mesh3, P* __restrict__ pos, P* __r
       __builtin_nontemporal_store(P(v), &vel[i]);   // streaming: read again only by the next step
       __builtin_nontemporal_store(xo, &pos[i]);
     }
+  });
+}
+
+// dL/dx_p of a loss whose derivative with respect to the weight of corner (a, b, cc) is
+// val(a, b, cc): sum over the corners of val dW/dx (derivative of the unquantised weights)
+template <class Val>
+__device__ __forceinline__ void gather_weight_grad(const Cic& c, double scale, const Val& val, double (&g)[3]) {
+  g[0] = g[1] = g[2] = 0.0;
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const double wx = a ? c.w1[0] : c.w0[0];
+    const double dx = a ? scale : -scale;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const double wy = b ? c.w1[1] : c.w0[1];
+      const double dy = b ? scale : -scale;
+#pragma unroll
+      for (int cc = 0; cc < 2; ++cc) {
+        const double wz = cc ? c.w1[2] : c.w0[2];
+        const double dz = cc ? scale : -scale;
+        const double v = val(a, b, cc);
+        g[0] += v * dx * wy * wz;
+        g[1] += v * wx * dy * wz;
+        g[2] += v * wx * wy * dz;
+      }
+    }
   }
 }
 
@@ -382,34 +418,16 @@ template <typename P>
 __global__ void __launch_bounds__(256)
 k_deposit_backward(const P* __restrict__ pos, long long np, int n, double scale, const double* __restrict__ g,
                    double mass, double* __restrict__ grad) {
-  const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (p >= np) return;
-  const Cic c = cic_of(pos, np, p, n, scale);
-  double gx = 0.0, gy = 0.0, gz = 0.0;
+  __shared__ double fl[kGatherCap];
+  const long long p0 = xcd_chunk() * kGatherChunk;
+  P xs[kGatherPPT][3];
+  load_chunk<kGatherPPT>(pos, np, p0, xs);
+  gather_chunk<1>(g, pos, xs, np, p0, n, scale, fl, [&](long long p, int, const Cic& c, const auto& at) {
+    double gx[3];
+    gather_weight_grad(c, scale, [&](int a, int b, int cc) { return at(a, b, cc, 0); }, gx);
 #pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    const double wx = a ? c.w1[0] : c.w0[0];
-    const double dx = a ? scale : -scale;
-    const size_t ix = (size_t)(a ? c.i1[0] : c.i0[0]);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const double wy = b ? c.w1[1] : c.w0[1];
-      const double dy = b ? scale : -scale;
-      const size_t iy = (size_t)(b ? c.i1[1] : c.i0[1]);
-#pragma unroll
-      for (int cc = 0; cc < 2; ++cc) {
-        const double wz = cc ? c.w1[2] : c.w0[2];
-        const double dz = cc ? scale : -scale;
-        const double gc = g[(ix * n + iy) * n + (size_t)(cc ? c.i1[2] : c.i0[2])];
-        gx += gc * dx * wy * wz;
-        gy += gc * wx * dy * wz;
-        gz += gc * wx * wy * dz;
-      }
-    }
-  }
-  grad[p] = gx * mass;
-  grad[np + p] = gy * mass;
-  grad[2 * np + p] = gz * mass;
+    for (int d = 0; d < 3; ++d) __builtin_nontemporal_store(gx[d] * mass, &grad[(size_t)d * np + p]);
+  });
 }
 
 // ------------------------------------------------------------------ CIC interpolation adjoint
@@ -428,39 +446,26 @@ template <typename P, int NC>
 __global__ void __launch_bounds__(256)
 k_interp_grad_pos(const double* __restrict__ mesh, const P* __restrict__ pos, long long np, int n, double scale,
                   const double* __restrict__ g, double* __restrict__ grad) {
-  const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (p >= np) return;
-  const Cic c = cic_of(pos, np, p, n, scale);
-  const size_t n3 = (size_t)n * n * n;
-  double gm[NC];
+  __shared__ double fl[NC * kGatherCap];
+  const long long p0 = xcd_chunk() * kGatherChunk;
+  P xs[kGatherPPT][3];
+  load_chunk<kGatherPPT>(pos, np, p0, xs);
+  gather_chunk<NC>(mesh, pos, xs, np, p0, n, scale, fl, [&](long long p, int, const Cic& c, const auto& at) {
+    double gm[NC], gx[3];
 #pragma unroll
-  for (int m = 0; m < NC; ++m) gm[m] = g[(size_t)m * np + p];
-  double gx = 0.0, gy = 0.0, gz = 0.0;
+    for (int m = 0; m < NC; ++m) gm[m] = g[(size_t)m * np + p];
+    gather_weight_grad(
+        c, scale,
+        [&](int a, int b, int cc) {
+          double proj = 0.0;
 #pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    const double wx = a ? c.w1[0] : c.w0[0];
-    const double dx = a ? scale : -scale;
+          for (int m = 0; m < NC; ++m) proj += gm[m] * at(a, b, cc, m);
+          return proj;
+        },
+        gx);
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const double wy = b ? c.w1[1] : c.w0[1];
-      const double dy = b ? scale : -scale;
-#pragma unroll
-      for (int cc = 0; cc < 2; ++cc) {
-        const double wz = cc ? c.w1[2] : c.w0[2];
-        const double dz = cc ? scale : -scale;
-        const size_t idx = corner_index(c, a, b, cc, n);
-        double proj = 0.0;
-#pragma unroll
-        for (int m = 0; m < NC; ++m) proj += gm[m] * mesh[(size_t)m * n3 + idx];
-        gx += proj * dx * wy * wz;
-        gy += proj * wx * dy * wz;
-        gz += proj * wx * wy * dz;
-      }
-    }
-  }
-  grad[p] = gx;
-  grad[np + p] = gy;
-  grad[2 * np + p] = gz;
+    for (int d = 0; d < 3; ++d) __builtin_nontemporal_store(gx[d], &grad[(size_t)d * np + p]);
+  });
 }
 
 // part[block] = {bit pattern of the block's max |g| (non-negative doubles order like their bit
@@ -614,10 +619,7 @@ __global__ void __launch_bounds__(256) k_convert(size_t count, const void* __res
     out[i] = in_fp32 ? T(static_cast<const float*>(in)[i]) : T(static_cast<const double*>(in)[i]);
 }
 
-static unsigned grid_for(long long count) {
-  long long g = (count + 255) / 256;
-  return unsigned(g < 1 ? 1 : g);
-}
+static unsigned gather_chunks(long long np) { return unsigned((np + kGatherChunk - 1) / kGatherChunk); }
 static unsigned grid_strided(size_t count) {
   size_t g = (count + 255) / 256;
   return unsigned(g > 8192 ? 8192 : (g < 1 ? 1 : g));
@@ -660,10 +662,10 @@ static void interp_m(int n, double box, const M* mesh, const void* pos, int pos_
                      hipStream_t s) {
   const double scale = double(n) / box;
   if (pos_fp32)
-    hipLaunchKernelGGL((k_interp<float, M, NC>), dim3(grid_for(np)), dim3(256), 0, s, mesh,
+    hipLaunchKernelGGL((k_interp<float, M, NC>), dim3(gather_chunks(np)), dim3(256), 0, s, mesh,
                        static_cast<const float*>(pos), np, n, scale, out);
   else
-    hipLaunchKernelGGL((k_interp<double, M, NC>), dim3(grid_for(np)), dim3(256), 0, s, mesh,
+    hipLaunchKernelGGL((k_interp<double, M, NC>), dim3(gather_chunks(np)), dim3(256), 0, s, mesh,
                        static_cast<const double*>(pos), np, n, scale, out);
 }
 
@@ -684,7 +686,7 @@ template <typename M>
 static void kick_m(int n, double box, const M* mesh3, void* pos, void* vel, int fp32, long long np, double kick,
                    double drift, hipStream_t s) {
   const double scale = double(n) / box;
-  const unsigned g = unsigned((np + kGatherChunk - 1) / kGatherChunk);
+  const unsigned g = gather_chunks(np);
   if (fp32)
     hipLaunchKernelGGL((k_interp_kick_drift_bin<float, M>), dim3(g), dim3(256), 0, s, mesh3, static_cast<float*>(pos),
                        static_cast<float*>(vel), np, n, scale, box, kick, drift);
@@ -706,10 +708,10 @@ void launch_deposit_backward(int n, double box, const void* pos, int pos_fp32, l
   const double scale = double(n) / box;
   const double mass = double(n) * n * n / double(np);
   if (pos_fp32)
-    hipLaunchKernelGGL((k_deposit_backward<float>), dim3(grid_for(np)), dim3(256), 0, s,
+    hipLaunchKernelGGL((k_deposit_backward<float>), dim3(gather_chunks(np)), dim3(256), 0, s,
                        static_cast<const float*>(pos), np, n, scale, grad_delta, mass, grad_pos);
   else
-    hipLaunchKernelGGL((k_deposit_backward<double>), dim3(grid_for(np)), dim3(256), 0, s,
+    hipLaunchKernelGGL((k_deposit_backward<double>), dim3(gather_chunks(np)), dim3(256), 0, s,
                        static_cast<const double*>(pos), np, n, scale, grad_delta, mass, grad_pos);
 }
 
@@ -722,7 +724,7 @@ static void interp_bwd_t(int n, double box, const double* mesh, const P* pos, lo
   const double scale = double(n) / box;
   const size_t n3 = (size_t)n * n * n;
   if (grad_pos)
-    hipLaunchKernelGGL((k_interp_grad_pos<P, NC>), dim3(grid_for(np)), dim3(256), 0, s, mesh, pos, np, n, scale, g,
+    hipLaunchKernelGGL((k_interp_grad_pos<P, NC>), dim3(gather_chunks(np)), dim3(256), 0, s, mesh, pos, np, n, scale, g,
                        grad_pos);
   if (!grad_mesh) return;
   auto* acc = reinterpret_cast<unsigned long long*>(grad_mesh);
