@@ -413,7 +413,7 @@ static int plan_alloc(dgp_plan* pl) {
   TRY(dalloc(pl, &pl->fx_state, 4));
   TRY(dalloc(pl, &pl->bin_tab, 129 + 128 * B));
   TRY(dalloc(pl, &pl->bin_partial, (size_t)p3_row_groups(pl->n) * B * 2 * 128));
-  TRY(halloc(pl, &pl->bin_host, (size_t)p3_row_groups(pl->n) * B * 2 * 128));
+  TRY(halloc(pl, &pl->bin_host, 129 + 128 * B));
   return DGP_OK;
 }
 
@@ -568,7 +568,7 @@ static int setup_source(dgp_plan* pl, const dgp_params* p, const double* delta, 
   Timed tm(pl, s, DGP_T_SETUP);
   cx<double>* dspec = w.spec6 + 6 * fs;
   TRY(fwd3<double>(pl, delta, dspec, B, nullptr, s));
-  launch_p3<double>(n, SPEC_SOURCE, dspec, fs, 1, w.spec6, fs, 2, B, cf, nullptr, nullptr, nullptr, nullptr, s);
+  launch_p3<double>(n, SPEC_SOURCE, dspec, fs, 1, w.spec6, fs, 2, B, cf, nullptr, nullptr, nullptr, s);
   launch_p2<double>(n, w.spec6, 2, B, +1, nullptr, s);
   launch_p1_inv<double>(n, w.spec6, w.S, B, nullptr, s, S32);
   if (want_linear) launch_p1_inv<double>(n, w.spec6 + fs, w.U, B, nullptr, s, U32);
@@ -588,7 +588,7 @@ static int enqueue_pass(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const Solve
   }
   {
     Timed t(pl, s, tcls<T>(DGP_T_FANOUT));
-    launch_p3<T>(n, SPEC_HSPLIT, w.spec_u, fs, 1, w.spec6, fs, 3, B, cf, nullptr, nullptr, pl->mean_u, pl->ctl, s);
+    launch_p3<T>(n, SPEC_HSPLIT, w.spec_u, fs, 1, w.spec6, fs, 3, B, cf, nullptr, pl->mean_u, pl->ctl, s);
   }
   {
     Timed t(pl, s, tcls<T>(DGP_T_AXIS1_INV));
@@ -704,7 +704,7 @@ static int c_field(dgp_plan* pl, const dgp_params* p, const double* u, double* c
   const size_t fs = (size_t)B * pl->hs;
   const SpecCoef cf = spec_coef(pl, p);
   TRY(fwd3<double>(pl, u, pl->spec_u, B, nullptr, s));
-  launch_p3<double>(n, SPEC_CFIELD, pl->spec_u, fs, 1, pl->spec6, fs, 1, B, cf, nullptr, nullptr, nullptr, nullptr, s);
+  launch_p3<double>(n, SPEC_CFIELD, pl->spec_u, fs, 1, pl->spec6, fs, 1, B, cf, nullptr, nullptr, nullptr, s);
   launch_p2<double>(n, pl->spec6, 1, B, +1, nullptr, s);
   launch_p1_inv<double>(n, pl->spec6, c_out, B, nullptr, s);
   LAUNCHCHK();
@@ -892,8 +892,7 @@ static int force_mesh(dgp_plan* pl, const dgp_params* p, const double* delta, co
       launch_p2<float>(n, fin, use_u ? 2 : 1, 1, -1, nullptr, s);
     else if (use_u)
       launch_p2<float>(n, fin + fs, 1, 1, -1, nullptr, s);
-    launch_p3<float>(n, SPEC_FORCES, fin, fs, use_u ? 2 : 1, pl->spec6_32, fs, 2, 1, cf, nullptr, nullptr, nullptr,
-                     nullptr, s);
+    launch_p3<float>(n, SPEC_FORCES, fin, fs, use_u ? 2 : 1, pl->spec6_32, fs, 2, 1, cf, nullptr, nullptr, nullptr, s);
     launch_p2_force_split<float>(n, pl->spec6_32, fs, 1, phi_n ? 1 : 0, cf.force_scale * cf.kf, s);
     launch_p1_inv<float>(n, pl->spec6_32, pl->mesh3_32, 3, nullptr, s);
     if (phi_n) {
@@ -910,8 +909,7 @@ static int force_mesh(dgp_plan* pl, const dgp_params* p, const double* delta, co
     launch_p2<double>(n, fin, use_u ? 2 : 1, 1, -1, nullptr, s);
   else if (use_u)
     launch_p2<double>(n, fin + fs, 1, 1, -1, nullptr, s);
-  launch_p3<double>(n, SPEC_FORCES, fin, fs, use_u ? 2 : 1, pl->spec6, fs, 2, 1, cf, nullptr, nullptr, nullptr,
-                    nullptr, s);
+  launch_p3<double>(n, SPEC_FORCES, fin, fs, use_u ? 2 : 1, pl->spec6, fs, 2, 1, cf, nullptr, nullptr, nullptr, s);
   launch_p2_force_split<double>(n, pl->spec6, fs, 1, phi_n ? 1 : 0, cf.force_scale * cf.kf, s);
   launch_p1_inv<double>(n, pl->spec6, pl->mesh3, 3, nullptr, s);
   if (phi_n) launch_p1_inv<double>(n, pl->spec6 + 3 * fs, phi_n, 1, nullptr, s);
@@ -1049,34 +1047,54 @@ static void bin_thresholds(int n, int nbins, std::vector<double>& t) {
   t[nbins] = half * half + 1.0;
 }
 
+// Modes per bin of the half spectrum, counted with their multiplicity (exact integers): the pairs
+// (n0, n1) by n0^2 + n1^2, cumulated, then the third axis.  The bins lie inside |n| <= N/2.
+static void bin_counts(int n, int nbins, const std::vector<double>& thr, std::vector<double>& cnt) {
+  const int half = n / 2;
+  std::vector<long long> cum(half * half + 2, 0);   // cum[x]: pairs with n0^2 + n1^2 < x
+  for (int n0 = 0; n0 <= half; ++n0)
+    for (int n1 = -half; n1 < half; ++n1) {
+      const int q = n0 * n0 + n1 * n1;
+      if (q <= half * half) cum[q + 1] += (n0 == 0 || n0 == half) ? 1 : 2;
+    }
+  for (size_t i = 1; i < cum.size(); ++i) cum[i] += cum[i - 1];
+  std::vector<long long> below(nbins + 1, 0);       // modes with |n|^2 < thr[b]
+  for (int b = 0; b <= nbins; ++b)
+    for (int n2 = -half; n2 < half; ++n2) {
+      const int x = int(thr[b]) - n2 * n2;
+      if (x > 0) below[b] += cum[x];
+    }
+  cnt.resize(nbins);
+  for (int b = 0; b < nbins; ++b) cnt[b] = double(below[b + 1] - below[b]);
+}
+
+// thresholds (and, appended, `extra`) into the device table through pinned memory
+static int bin_table(dgp_plan* pl, const std::vector<double>& tab, hipStream_t s) {
+  std::memcpy(pl->bin_host, tab.data(), sizeof(double) * tab.size());
+  HIPCHK(hipMemcpyAsync(pl->bin_tab, pl->bin_host, sizeof(double) * tab.size(), hipMemcpyHostToDevice, s));
+  return DGP_OK;
+}
+
+// per element and bin, the sum of |f|^2; per bin, the count of its modes (counted here while the
+// device works)
 static int power_impl(dgp_plan* pl, const dgp_params* p, const double* field, int of_c, int nbins,
                       std::vector<double>& sums, std::vector<double>& cnts, hipStream_t s) {
   const int n = pl->n, B = pl->batch;
-  const size_t fs = (size_t)B * pl->hs;
   std::vector<double> thr;
   bin_thresholds(n, nbins, thr);
-  HIPCHK(hipMemcpyAsync(pl->bin_tab, thr.data(), sizeof(double) * thr.size(), hipMemcpyHostToDevice, s));
+  TRY(bin_table(pl, thr, s));
   SpecCoef cf = spec_coef(pl, p);
   cf.nbins = nbins;
   cf.power_c = of_c ? 1 : 0;
   TRY(fwd3<double>(pl, field, pl->spec_u, B, nullptr, s));
-  launch_p3<double>(n, SPEC_POWER, pl->spec_u, fs, 1, nullptr, 0, 0, B, cf, pl->bin_tab, pl->bin_partial, nullptr,
-                    nullptr, s);
+  double* const dev = pl->bin_tab + nbins + 1;   // the sums, after the thresholds
+  launch_power(n, pl->spec_u, B, cf, pl->bin_tab, pl->bin_partial, dev, s);
   LAUNCHCHK();
-  const int g = p3_row_groups(n);
-  const size_t cnt = (size_t)B * g * 2 * nbins;
-  HIPCHK(hipMemcpyAsync(pl->bin_host, pl->bin_partial, sizeof(double) * cnt, hipMemcpyDeviceToHost, s));
+  const size_t cnt = (size_t)B * nbins;
+  HIPCHK(hipMemcpyAsync(pl->bin_host, dev, sizeof(double) * cnt, hipMemcpyDeviceToHost, s));
+  bin_counts(n, nbins, thr, cnts);
   HIPCHK(hipStreamSynchronize(s));
-  sums.assign((size_t)B * nbins, 0.0);
-  cnts.assign((size_t)B * nbins, 0.0);
-  for (int b = 0; b < B; ++b)
-    for (int k = 0; k < g; ++k) {
-      const double* row = pl->bin_host + ((size_t)b * g + k) * 2 * nbins;
-      for (int i = 0; i < nbins; ++i) {
-        sums[(size_t)b * nbins + i] += row[i];
-        cnts[(size_t)b * nbins + i] += row[nbins + i];
-      }
-    }
+  sums.assign(pl->bin_host, pl->bin_host + cnt);
   return DGP_OK;
 }
 
@@ -1090,7 +1108,7 @@ extern "C" int dgp_power_spectrum(dgp_plan* pl, const dgp_params* p, const doubl
   const double norm = std::pow(pl->box, 3) / (double(pl->n3) * double(pl->n3));
   for (int b = 0; b < pl->batch; ++b)
     for (int i = 0; i < nbins; ++i) {
-      const double c = cnts[(size_t)b * nbins + i];
+      const double c = cnts[i];
       pk[(size_t)b * nbins + i] = c > 0 ? sums[(size_t)b * nbins + i] / c * norm : 0.0;
     }
   if (counts)
@@ -1104,25 +1122,23 @@ extern "C" int dgp_power_spectrum_backward(dgp_plan* pl, const dgp_params* p, co
   TRY(check_params(p));
   if (nbins < 1 || nbins > 128) return fail(DGP_E_INVALID, "nbins must be in [1, 128]");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  std::vector<double> sums, cnts;
-  TRY(power_impl(pl, p, field, of_c, nbins, sums, cnts, s));
   const int n = pl->n, B = pl->batch;
-  std::vector<double> tab;
+  std::vector<double> tab, cnts;
   bin_thresholds(n, nbins, tab);
+  bin_counts(n, nbins, tab, cnts);
   const double norm = std::pow(pl->box, 3) / (double(pl->n3) * double(pl->n3));
   for (int b = 0; b < B; ++b)
     for (int i = 0; i < nbins; ++i) {
-      const double c = cnts[(size_t)b * nbins + i];
+      const double c = cnts[i];
       tab.push_back(c > 0 ? grad_pk[(size_t)b * nbins + i] * norm / c * 2.0 * double(pl->n3) : 0.0);
     }
-  HIPCHK(hipMemcpyAsync(pl->bin_tab, tab.data(), sizeof(double) * tab.size(), hipMemcpyHostToDevice, s));
+  TRY(bin_table(pl, tab, s));
   SpecCoef cf = spec_coef(pl, p);
   cf.nbins = nbins;
   cf.power_c = of_c ? 1 : 0;
   const size_t fs = (size_t)B * pl->hs;
   TRY(fwd3<double>(pl, field, pl->spec_u, B, nullptr, s));
-  launch_p3<double>(n, SPEC_POWER_GRAD, pl->spec_u, fs, 1, pl->spec6, fs, 1, B, cf, pl->bin_tab, nullptr, nullptr,
-                    nullptr, s);
+  launch_p3<double>(n, SPEC_POWER_GRAD, pl->spec_u, fs, 1, pl->spec6, fs, 1, B, cf, pl->bin_tab, nullptr, nullptr, s);
   launch_p2<double>(n, pl->spec6, 1, B, +1, nullptr, s);
   launch_p1_inv<double>(n, pl->spec6, grad_field, B, nullptr, s);
   LAUNCHCHK();
@@ -1142,12 +1158,11 @@ extern "C" int dgp_fft_forward(dgp_plan* pl, const double* field, double* spectr
   if (pl->precision == DGP_FP64) {
     TRY(fwd3<double>(pl, field, pl->spec_u, B, nullptr, s));
     launch_p3<double>(n, SPEC_FWD_ONLY, pl->spec_u, fs, 1, reinterpret_cast<cx<double>*>(spectrum), fs, 1, B, cf,
-                      nullptr, nullptr, nullptr, nullptr, s);
+                      nullptr, nullptr, nullptr, s);
   } else {
     launch_convert<float>(B * pl->n3, field, 0, pl->U32, s);
     TRY(fwd3<float>(pl, pl->U32, pl->spec_u32, B, nullptr, s));
-    launch_p3<float>(n, SPEC_FWD_ONLY, pl->spec_u32, fs, 1, pl->spec6_32, fs, 1, B, cf, nullptr, nullptr, nullptr,
-                     nullptr, s);
+    launch_p3<float>(n, SPEC_FWD_ONLY, pl->spec_u32, fs, 1, pl->spec6_32, fs, 1, B, cf, nullptr, nullptr, nullptr, s);
     launch_convert<double>(2 * fs, pl->spec6_32, 1, spectrum, s);
   }
   LAUNCHCHK();
@@ -1164,13 +1179,12 @@ extern "C" int dgp_fft_inverse(dgp_plan* pl, const double* spectrum, double* fie
   const SpecCoef cf = spec_coef(pl, &p);
   if (pl->precision == DGP_FP64) {
     launch_p3<double>(n, SPEC_INV_ONLY, reinterpret_cast<const cx<double>*>(spectrum), fs, 1, pl->spec_u, fs, 1, B, cf,
-                      nullptr, nullptr, nullptr, nullptr, s);
+                      nullptr, nullptr, nullptr, s);
     launch_p2<double>(n, pl->spec_u, 1, B, +1, nullptr, s);
     launch_p1_inv<double>(n, pl->spec_u, field, B, nullptr, s);
   } else {
     launch_convert<float>(2 * fs, spectrum, 0, reinterpret_cast<float*>(pl->spec6_32), s);
-    launch_p3<float>(n, SPEC_INV_ONLY, pl->spec6_32, fs, 1, pl->spec_u32, fs, 1, B, cf, nullptr, nullptr, nullptr,
-                     nullptr, s);
+    launch_p3<float>(n, SPEC_INV_ONLY, pl->spec6_32, fs, 1, pl->spec_u32, fs, 1, B, cf, nullptr, nullptr, nullptr, s);
     launch_p2<float>(n, pl->spec_u32, 1, B, +1, nullptr, s);
     launch_p1_inv<float>(n, pl->spec_u32, pl->U32, B, nullptr, s);
     launch_convert<double>(B * pl->n3, pl->U32, 1, field, s);
@@ -1209,8 +1223,7 @@ static int hessians(dgp_plan* pl, const dgp_params* p, const double* u, double* 
   const size_t fs = (size_t)B * pl->hs, bn = (size_t)B * pl->n3;
   const SpecCoef cf = spec_coef(pl, p);
   TRY(fwd3<double>(pl, u, pl->spec_u, B, nullptr, s));
-  launch_p3<double>(n, SPEC_HSPLIT, pl->spec_u, fs, 1, pl->spec6, fs, 3, B, cf, nullptr, nullptr, pl->mean_u, nullptr,
-                    s);
+  launch_p3<double>(n, SPEC_HSPLIT, pl->spec_u, fs, 1, pl->spec6, fs, 3, B, cf, nullptr, pl->mean_u, nullptr, s);
   launch_p2_split<double>(n, pl->spec6, fs, B, nullptr, s);
   for (int f = 0; f < 5; ++f) launch_p1_inv<double>(n, pl->spec6 + f * fs, H5 + f * bn, B, nullptr, s);
   LAUNCHCHK();
@@ -1279,8 +1292,7 @@ int adjoint_solve(dgp_plan* pl, const dgp_params* p, const double* delta, const 
     const int m = std::min(chunk, limit - enqueued);
     for (int j = 0; j < m; ++j) {
       launch_p2_adj_split(n, pl->spec6, fs, B, cf.lam2, pl->adj_ctl, s);
-      launch_p3<double>(n, SPEC_ADJ_COMBINE3, pl->spec6, fs, 3, pl->spec_u, fs, 1, B, cf, nullptr, nullptr, nullptr,
-                        pl->adj_ctl, s);
+      launch_p3<double>(n, SPEC_ADJ_COMBINE3, pl->spec6, fs, 3, pl->spec_u, fs, 1, B, cf, nullptr, nullptr, pl->adj_ctl, s);
       launch_p2<double>(n, pl->spec_u, 1, B, +1, pl->adj_ctl, s);
       launch_adj_step(n, true, pl->spec_u, MU, bn, u_star, H5, grad_u, pl->mean_u, pl->adj_vec, pl->spec6, fs,
                       pl->adj_red, ak, pl->adj_ctl, B, s);
@@ -1303,7 +1315,7 @@ int adjoint_solve(dgp_plan* pl, const dgp_params* p, const double* delta, const 
                           hipMemcpyDeviceToDevice, s));
   }
   TRY(fwd3<double>(pl, RES, pl->spec_u, B, nullptr, s));
-  launch_p3<double>(n, SPEC_SOURCE, pl->spec_u, fs, 1, pl->spec6, fs, 2, B, cf, nullptr, nullptr, nullptr, nullptr, s);
+  launch_p3<double>(n, SPEC_SOURCE, pl->spec_u, fs, 1, pl->spec6, fs, 2, B, cf, nullptr, nullptr, nullptr, s);
   launch_p2<double>(n, pl->spec6, 1, B, +1, nullptr, s);
   launch_p1_inv<double>(n, pl->spec6, grad_delta, B, nullptr, s);
   LAUNCHCHK();
@@ -1350,7 +1362,7 @@ extern "C" int dgp_diagnostics(dgp_plan* pl, const dgp_params* p, const double* 
     TRY(power_impl(pl, p, delta, 0, nbins, sd, cd, s));
     const double coef = p->alpha * p->eta / (3.0 * (p->eta - 1.0));
     for (size_t i = 0; i < (size_t)B * nbins; ++i) {
-      const double pu = cu[i] > 0 ? su[i] / cu[i] : 0.0, pd = cd[i] > 0 ? sd[i] / cd[i] : 0.0;
+      const double pu = cu[i % nbins] > 0 ? su[i] / cu[i % nbins] : 0.0, pd = cd[i % nbins] > 0 ? sd[i] / cd[i % nbins] : 0.0;
       pc_over_pm[i] = pd > 0 ? coef * coef * pu / pd : 0.0;
     }
   }
@@ -1363,7 +1375,7 @@ extern "C" int dgp_diagnostics(dgp_plan* pl, const dgp_params* p, const double* 
       for (int i = 0; i < nbins; ++i) {
         const size_t j = (size_t)b * nbins + i;
         const double kc = kf * std::pow(pl->n / 2.0, (i + 0.5) / nbins);
-        const double pk = cc[j] > 0 ? sc[j] / cc[j] * norm : 0.0;
+        const double pk = cc[i] > 0 ? sc[j] / cc[i] * norm : 0.0;
         delta_gradc[j] = 4.0 * M_PI * std::pow(kc, 5) * pk;
       }
   }

@@ -14,7 +14,6 @@ enum SpecMode : int {
   SPEC_SOURCE = 1,    // delta(k) -> S(k) = A(1 - beta/kbar) delta, u_lin(k) = S/(alpha - gamma/kbar)
   SPEC_CFIELD = 2,    // u(k) -> C(k) = -u/kbar^2
   SPEC_FORCES = 3,    // delta(k)[, u(k)] -> phi(k) (slot 0) and g_2 = -(c/H0)^2 i k_2 phi(k) (slot 2)
-  SPEC_POWER = 4,     // f(k) -> per-bin sums of |f|^2 (no outputs); optional 1/kbar^2 weight
   SPEC_POWER_GRAD = 5,// f(k) -> per-bin coefficient * f(k) [* 1/kbar^4]
   SPEC_ADJ_COMBINE3 = 6,// the three group sums of launch_p2_adj_split -> one combined spectrum
   SPEC_COPY = 7,      // identity (plain forward+inverse round trip, for tests)
@@ -40,8 +39,8 @@ struct SpecCoef {
   double inv_n3;    // 1/N^3 (inverse-transform normalisation, folded into the multiplier)
   double lam2;      // 2 lam (adjoint combine)
   int force_mode;   // ForceMode
-  int power_c;      // POWER/POWER_GRAD: weight |f|^2 by 1/kbar^4 (spectrum of C from u)
-  int nbins;        // POWER: number of bins
+  int power_c;      // power spectrum and its gradient: weight |f|^2 by 1/kbar^4 (spectrum of C from u)
+  int nbins;        // power spectrum: number of bins
 };
 
 // Per-batch-element control block of the relaxation (device memory).
@@ -165,8 +164,13 @@ void launch_p2_force_split(int n, cx<T>* data, size_t fstride, int batch, int wi
 template <typename T>
 void launch_p3(int n, SpecMode mode, const cx<T>* in, size_t in_stride, int nin, cx<T>* out,
                size_t out_stride, int nout, int batch, const SpecCoef& coef, const double* bin_coef,
-               double* bin_partial, double* mean_out, const SolveCtl* ctl, hipStream_t s);
-int p3_row_groups(int n);   // workgroups per batch element of the axis-2 pass (for POWER partials)
+               double* mean_out, const SolveCtl* ctl, hipStream_t s);
+int p3_row_groups(int n);   // workgroups per batch element of the float64 axis-2 pass
+// binned power spectrum of [batch] axis-0/1 spectra: sums[b][nbins] of |f|^2 (times 1/kbar^4 with
+// coef.power_c) over the modes with thr[bin] <= |n|^2 < thr[bin + 1]; partial: p3_row_groups(n) x batch x
+// nbins doubles of scratch
+void launch_power(int n, const cx<double>* in, int batch, const SpecCoef& coef, const double* thr, double* partial,
+                  double* sums, hipStream_t s);
 
 // fused relaxation pass (inverse axis-0 of 6 spectra + pointwise update + forward axis-0);
 // ev0/ev1 (may be null): timing events recorded by the kernel's dispatch at its start and end

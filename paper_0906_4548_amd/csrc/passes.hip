@@ -431,7 +431,7 @@ template <typename T, int N, SpecMode MODE>
 __global__ void __launch_bounds__((Geo<T, N>::kP3))
 k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, size_t out_stride,
      const cx<T>* __restrict__ tw, SpecCoef cf, const double* __restrict__ bin_coef,
-     double* __restrict__ bin_partial, double* __restrict__ mean_out, const SolveCtl* __restrict__ ctl) {
+     double* __restrict__ mean_out, const SolveCtl* __restrict__ ctl) {
   using P = typename Geo<T, N>::P3;
   constexpr int R = P::R;
   using G = RowTile<N, R>;
@@ -472,56 +472,6 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
       for (int q = 0; q < R; ++q) v[q] = scale(v[q], T(cf.inv_n3));
     }
     store_row(out, v);
-    return;
-  } else if constexpr (MODE == SPEC_POWER) {
-    // deterministic binning: every mode's (bin, weighted |f|^2) goes to LDS, then thread b sums
-    // bin b over the workgroup's modes in a fixed order
-    constexpr int NE = G::kThreads * R;
-    __shared__ double pval[NE];
-    __shared__ short pbin[NE];
-    load_row(in);
-    fft<T, N, P, -1>(v, tw, L, t);
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const int slot = (c * R + q) * TT + t;
-      short bin = -1;
-      double val = 0.0;
-      if (valid) {
-        const Mode3 m = mode_of(N, k0, k1, t + q * TT);
-        const double ms = double(m.msq);
-        if (ms >= bin_coef[0] && ms < bin_coef[cf.nbins]) {
-          int lo = 0, hi = cf.nbins;   // largest lo with thr[lo] <= ms
-          while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (bin_coef[mid] <= ms) lo = mid; else hi = mid;
-          }
-          const double mult = (m.n0 == 0 || m.q0) ? 1.0 : 2.0;
-          double p2 = double(v[q].x) * double(v[q].x) + double(v[q].y) * double(v[q].y);
-          if (cf.power_c) {
-            const double kb2 = cf.kappa * cf.kappa * kf * kf * ms;
-            p2 /= kb2 * kb2;
-          }
-          bin = short(lo);
-          val = mult * p2;
-        }
-      }
-      pval[slot] = val;
-      pbin[slot] = bin;
-    }
-    __syncthreads();
-    double* dstp = bin_partial + ((size_t)b * gridDim.x + blockIdx.x) * 2 * cf.nbins;
-    for (int bb = threadIdx.x; bb < cf.nbins; bb += blockDim.x) {
-      double sum = 0.0, cnt = 0.0;
-      for (int i = 0; i < NE; ++i) {
-        if (pbin[i] == bb) {
-          sum += pval[i];
-          const int kk0 = (blockIdx.x * RW + i / (TT * R)) / N;   // plane of the mode's row
-          cnt += (kk0 == 0 || kk0 == N / 2) ? 1.0 : 2.0;
-        }
-      }
-      dstp[bb] = sum;
-      dstp[cf.nbins + bb] = cnt;
-    }
     return;
   } else if constexpr (MODE == SPEC_ADJ_COMBINE3) {
     // the three group sums of k_p2_adj_split (slots 0, 3, 5: the axis-1 and axis-0 factors and
@@ -738,6 +688,123 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
   }
 }
 
+// ------------------------------------------------------------------ binned power spectrum
+// Axis-2 forward transform of every row and the sums of |f|^2 (times 1/kbar^4 with power_c) per bin,
+// float64.  A workgroup walks the row tiles blockIdx.x, blockIdx.x + gridDim.x, ...; along a row
+// (fixed n0, n1) the modes of a bin are the |n2| of one interval, so thread `bin` adds that
+// interval's values from LDS and keeps its sums in registers over the rows (wavefront w takes rows
+// w, w + 4, ... of a tile): every sum has a fixed order.  Bound by the row loads and transforms
+// (8 x 128^3: 61 us a launch); with every thread walking all modes of the workgroup's rows and the
+// partial sums of each row group added on the host it took 1300 us and 2 ms of host time.
+constexpr int kPowerGroupsMax = 1024;
+template <int N>
+struct PowerGeo {
+  using P = Plan8<N>;
+  using G = RowTile<N, P::R>;
+  static constexpr int kTiles = ((N / 2 + 1) * N + G::kRW - 1) / G::kRW;
+  static constexpr int kGroups = kTiles < kPowerGroupsMax ? kTiles : kPowerGroupsMax;
+  static_assert(G::kThreads == 256, "four wavefronts per workgroup");
+};
+
+// smallest r >= 0 with r^2 >= x (x below 2^24)
+__device__ __forceinline__ int ceil_sqrt(int x) {
+  if (x <= 0) return 0;
+  int r = int(sqrtf(float(x)));
+  while (r * r < x) ++r;
+  while ((r - 1) * (r - 1) >= x) --r;
+  return r;
+}
+
+template <int N>
+__global__ void __launch_bounds__(256)
+k_power(const cx<double>* __restrict__ in, const cx<double>* __restrict__ tw, SpecCoef cf,
+        const double* __restrict__ thr, double* __restrict__ partial) {
+  using T = double;
+  using PG = PowerGeo<N>;
+  using P = typename PG::P;
+  using G = typename PG::G;
+  constexpr int R = P::R, RW = G::kRW, TT = G::kT, ROWS = (N / 2 + 1) * N;
+  const int b = blockIdx.y, t = threadIdx.x % TT, c = threadIdx.x / TT;
+  const int bin = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  __shared__ cx<T> lds[RW * LdsRow<T, N>::kStride];
+  double* const p2 = reinterpret_cast<double*>(lds);   // |f|^2 of the tile, row c at c * N
+  LdsRow<T, N, (TT <= 64 && 64 % TT == 0 && DGP_P3_WAVE_SYNC)> L{lds, c};
+  int lo[2], hi[2];   // the bins' integer intervals of |n|^2 (empty for an unused slot)
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int k = bin + 64 * j;
+    lo[j] = k < cf.nbins ? int(thr[k]) : 0;
+    hi[j] = k < cf.nbins ? int(thr[k + 1]) : 0;
+  }
+  double sum[2] = {0.0, 0.0};
+  const double kk = cf.kappa * cf.kappa * cf.kf * cf.kf;
+  for (int tile = blockIdx.x; tile < PG::kTiles; tile += gridDim.x) {
+    const int row = tile * RW + c;
+    const bool valid = row < ROWS;
+    const cx<T>* src = in + ((size_t)b * ROWS + (valid ? row : 0)) * N + t;
+    cx<T> v[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) v[q] = src[q * TT];
+    fft<T, N, P, -1>(v, tw, L, t);
+    const int k0 = row / N, k1 = row % N, n1 = k1 < N / 2 ? k1 : k1 - N;
+    const int s2 = k0 * k0 + n1 * n1;
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int e = t + q * TT, n2 = e < N / 2 ? e : e - N;
+      double x = v[q].x * v[q].x + v[q].y * v[q].y;
+      if (cf.power_c) {
+        const double kb2 = kk * double(s2 + n2 * n2);
+        x /= kb2 * kb2;   // (no bin holds the mode 0, whose value is not finite)
+      }
+      p2[c * N + e] = x;
+    }
+    lds_barrier();
+    for (int r = wv; r < RW; r += 4) {
+      const int rw = tile * RW + r;
+      if (rw >= ROWS) break;
+      const int r0 = rw / N, r1 = rw % N, m1 = r1 < N / 2 ? r1 : r1 - N;
+      const int s = r0 * r0 + m1 * m1;
+      const double mult = (r0 == 0 || r0 == N / 2) ? 1.0 : 2.0;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (hi[j] <= s) continue;
+        const int m0 = ceil_sqrt(lo[j] - s), me = min(ceil_sqrt(hi[j] - s), N / 2 + 1);
+        double a = 0.0;
+        for (int m = m0; m < me; ++m) {
+          a += p2[r * N + m];
+          if (m > 0 && m < N / 2) a += p2[r * N + N - m];
+        }
+        sum[j] += mult * a;
+      }
+    }
+    lds_barrier();
+  }
+  __shared__ double ws[4][128];
+  ws[wv][bin] = sum[0];
+  ws[wv][bin + 64] = sum[1];
+  lds_barrier();
+  if ((int)threadIdx.x < cf.nbins)
+    partial[((size_t)b * gridDim.x + blockIdx.x) * cf.nbins + threadIdx.x] =
+        ((ws[0][threadIdx.x] + ws[1][threadIdx.x]) + ws[2][threadIdx.x]) + ws[3][threadIdx.x];
+}
+
+// sums[b][bin] over the workgroups' partial sums, in a fixed order (16 slices per bin)
+__global__ void __launch_bounds__(1024)
+k_power_final(const double* __restrict__ partial, int groups, int nbins, double* __restrict__ sums) {
+  const int b = blockIdx.x, bin = blockIdx.y * 64 + (threadIdx.x & 63), sl = threadIdx.x >> 6;
+  __shared__ double w[16][64];
+  double a = 0.0;
+  if (bin < nbins)
+#pragma unroll 4
+    for (int g = sl; g < groups; g += 16) a += partial[((size_t)b * groups + g) * nbins + bin];
+  w[sl][threadIdx.x & 63] = a;
+  __syncthreads();
+  if (sl != 0 || bin >= nbins) return;
+  for (int i = 1; i < 16; ++i) a += w[i][threadIdx.x];
+  sums[(size_t)b * nbins + bin] = a;
+}
+
 // ------------------------------------------------------------------ launchers
 template <typename T, int N, typename I = T>
 static void p1_fwd_n(const I* in, cx<T>* out, int batch, const SolveCtl* ctl, const cx<T>* tw, hipStream_t s) {
@@ -781,17 +848,16 @@ static void p2_force_split_n(cx<T>* data, size_t fstride, int batch, int with_ph
 }
 template <typename T, int N>
 static void p3_n(SpecMode mode, const cx<T>* in, size_t is, cx<T>* out, size_t os, int batch, const SpecCoef& cf,
-                 const double* bc, double* bp, double* mean, const SolveCtl* ctl, const cx<T>* tw, hipStream_t s) {
+                 const double* bc, double* mean, const SolveCtl* ctl, const cx<T>* tw, hipStream_t s) {
   using G = RowTile<N, Geo<T, N>::P3::R>;
   constexpr int ROWS = (N / 2 + 1) * N;
   dim3 grid((ROWS + G::kRW - 1) / G::kRW, batch);
   dim3 blk(G::kThreads);
-#define DGP_P3(M) hipLaunchKernelGGL((k_p3<T, N, M>), grid, blk, 0, s, in, is, out, os, tw, cf, bc, bp, mean, ctl)
+#define DGP_P3(M) hipLaunchKernelGGL((k_p3<T, N, M>), grid, blk, 0, s, in, is, out, os, tw, cf, bc, mean, ctl)
   switch (mode) {
     case SPEC_SOURCE: DGP_P3(SPEC_SOURCE); break;
     case SPEC_CFIELD: DGP_P3(SPEC_CFIELD); break;
     case SPEC_FORCES: DGP_P3(SPEC_FORCES); break;
-    case SPEC_POWER: DGP_P3(SPEC_POWER); break;
     case SPEC_POWER_GRAD: DGP_P3(SPEC_POWER_GRAD); break;
     case SPEC_ADJ_COMBINE3: DGP_P3(SPEC_ADJ_COMBINE3); break;
     case SPEC_COPY: DGP_P3(SPEC_COPY); break;
@@ -867,17 +933,31 @@ void launch_p2_force_split(int n, cx<T>* data, size_t fstride, int batch, int wi
 }
 template <typename T>
 void launch_p3(int n, SpecMode mode, const cx<T>* in, size_t in_stride, int nin, cx<T>* out, size_t out_stride,
-               int nout, int batch, const SpecCoef& coef, const double* bin_coef, double* bin_partial,
-               double* mean_out, const SolveCtl* ctl, hipStream_t s) {
+               int nout, int batch, const SpecCoef& coef, const double* bin_coef, double* mean_out,
+               const SolveCtl* ctl, hipStream_t s) {
   (void)nin;
   (void)nout;
   const cx<T>* tw = twiddles<T>(n);
-#define C(NN) p3_n<T, NN>(mode, in, in_stride, out, out_stride, batch, coef, bin_coef, bin_partial, mean_out, ctl, tw, s)
+#define C(NN) p3_n<T, NN>(mode, in, in_stride, out, out_stride, batch, coef, bin_coef, mean_out, ctl, tw, s)
   DGP_DISPATCH_N(n, C)
 #undef C
 }
 
-int p3_row_groups(int n) {   // row groups of the float64 axis-2 pass (the P(k) binning uses it)
+void launch_power(int n, const cx<double>* in, int batch, const SpecCoef& coef, const double* thr, double* partial,
+                  double* sums, hipStream_t s) {
+  const cx<double>* tw = twiddles<double>(n);
+  int g = 0;
+#define C(NN)                                                                                               \
+  {                                                                                                         \
+    g = PowerGeo<NN>::kGroups;                                                                              \
+    hipLaunchKernelGGL((k_power<NN>), dim3(g, batch), dim3(256), 0, s, in, tw, coef, thr, partial);         \
+  }
+  DGP_DISPATCH_N(n, C)
+#undef C
+  hipLaunchKernelGGL(k_power_final, dim3(batch, (coef.nbins + 63) / 64), dim3(1024), 0, s, partial, g, coef.nbins, sums);
+}
+
+int p3_row_groups(int n) {   // row groups of the float64 axis-2 pass (bounds the P(k) partials)
   int r = 0;
 #define C(NN)                                                          \
   {                                                                    \
@@ -900,8 +980,8 @@ template void launch_p2_split<float>(int, cx<float>*, size_t, int, const SolveCt
 template void launch_p2_force_split<double>(int, cx<double>*, size_t, int, int, double, hipStream_t);
 template void launch_p2_force_split<float>(int, cx<float>*, size_t, int, int, double, hipStream_t);
 template void launch_p3<double>(int, SpecMode, const cx<double>*, size_t, int, cx<double>*, size_t, int, int,
-                                const SpecCoef&, const double*, double*, double*, const SolveCtl*, hipStream_t);
+                                const SpecCoef&, const double*, double*, const SolveCtl*, hipStream_t);
 template void launch_p3<float>(int, SpecMode, const cx<float>*, size_t, int, cx<float>*, size_t, int, int,
-                               const SpecCoef&, const double*, double*, double*, const SolveCtl*, hipStream_t);
+                               const SpecCoef&, const double*, double*, const SolveCtl*, hipStream_t);
 
 }  // namespace dgp
