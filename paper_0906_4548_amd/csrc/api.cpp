@@ -198,8 +198,6 @@ struct dgp_plan {
   // control
   SolveCtl* ctl = nullptr;           // device [B]
   SolveCtl* ctl_host = nullptr;      // pinned [B]
-  int* n_active = nullptr;
-  int* n_active_host = nullptr;
   double* mean_u = nullptr;          // [B]
   double* means_host = nullptr;      // pinned [B]: <u> of the returned iterates
   int hint32 = 0, hint64 = 0;        // passes of the last solve (float32 phase, float64 solve or phase)
@@ -394,8 +392,6 @@ static int plan_alloc(dgp_plan* pl) {
   }
   TRY(dalloc(pl, &pl->ctl, B));
   TRY(halloc(pl, &pl->ctl_host, B));
-  TRY(dalloc(pl, &pl->n_active, 1));
-  TRY(halloc(pl, &pl->n_active_host, 1));
   TRY(dalloc(pl, &pl->mean_u, B));
   TRY(halloc(pl, &pl->means_host, B));
   TRY(dalloc(pl, &pl->vec, 4 * B));
@@ -600,7 +596,7 @@ static int enqueue_pass(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const Solve
   }
   {
     Timed t(pl, s, tcls<T>(DGP_T_FINALIZE));
-    launch_finalize(w.partial, w.groups, pl->ctl, cfg, pl->n_active, s);
+    launch_finalize(w.partial, w.groups, pl->ctl, cfg, s);
   }
   LAUNCHCHK();
   return DGP_OK;

@@ -180,8 +180,7 @@ void launch_relax(int n, const cx<T>* spec6, T* ubuf, const T* s_field, cx<T>* s
                   hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 int relax_groups(int n, int elem_bytes);   // workgroups per batch element of the fused pass
 
-void launch_finalize(const double* partial, int groups, SolveCtl* ctl, const SolveCfg& cfg,
-                     int* n_active, hipStream_t s);
+void launch_finalize(const double* partial, int groups, SolveCtl* ctl, const SolveCfg& cfg, hipStream_t s);
 
 // reductions: per-batch mean of |x| and mean of x (double results)
 template <typename T>
