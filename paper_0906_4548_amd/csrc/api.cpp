@@ -829,14 +829,15 @@ static int require_batch1(const dgp_plan* pl) {
   return DGP_OK;
 }
 
+// the spectral workspace, free outside a solve and its force mesh, serves as the deposit's scratch
+static size_t spec6_bytes(const dgp_plan* pl) { return 8 * (size_t)pl->batch * pl->hs * sizeof(cx<double>); }
+
 // (a non-finite position raises the plan's flag and turns delta into NaN, which the solve's
 // source then reports as invalid input)
 static int deposit_impl(dgp_plan* pl, const void* pos, int fp32, long long np, long long* grid, double* delta,
                         bool remove_mean, hipStream_t s) {
   Timed tm(pl, s, DGP_T_DEPOSIT);
-  launch_fill_zero(grid, pl->n3, s);
-  launch_zero_flag(pl->flag, s);
-  launch_deposit(pl->n, pl->box, pos, fp32, np, grid, pl->flag, s);
+  launch_deposit(pl->n, pl->box, pos, fp32, np, grid, pl->flag, pl->spec6, spec6_bytes(pl), s);
   if (delta) {
     if (remove_mean) {   // the mean of the counts (deterministic reduction), removed in the same pass
       launch_absmean<long long>(pl->n3, grid, 1, pl->red, nullptr, pl->vec, s);
@@ -993,9 +994,7 @@ extern "C" int dgp_deposit_noalloc(int n, double box, const void* pos, int pos_i
   double* mean = sc + parts;
   int* flag = reinterpret_cast<int*>(sc + parts + 2);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  launch_fill_zero(grid_fixed, n3, s);
-  launch_zero_flag(flag, s);
-  launch_deposit(n, box, pos, pos_is_fp32, np, grid_fixed, flag, s);
+  launch_deposit(n, box, pos, pos_is_fp32, np, grid_fixed, flag, nullptr, 0, s);
   launch_absmean<long long>(n3, grid_fixed, 1, sc, nullptr, mean, s);
   launch_counts_to_delta(n, grid_fixed, np, delta, flag, s, mean);
   LAUNCHCHK();
@@ -1021,7 +1020,7 @@ extern "C" int dgp_interp_backward(dgp_plan* pl, const double* mesh, int ncomp, 
   if (grad_pos && !mesh) return fail(DGP_E_INVALID, "grad_pos needs the mesh");
   TRY(require_batch1(pl));
   launch_interp_backward(pl->n, pl->box, mesh, ncomp, pos, pos_is_fp32, np, grad_out, grad_pos, grad_mesh, pl->grid,
-                         pl->fx_state, pl->red, pl->flag, static_cast<hipStream_t>(stream));
+                         pl->fx_state, pl->red, pl->flag, pl->spec6, spec6_bytes(pl), static_cast<hipStream_t>(stream));
   LAUNCHCHK();
   return DGP_OK;
 }

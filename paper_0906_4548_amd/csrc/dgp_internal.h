@@ -238,8 +238,10 @@ void launch_nonelliptic(size_t n3, int batch, const double* u, const double* h5,
                         double alpha, double* part, hipStream_t s);
 
 // PM kernels.  `bad` (device int) is raised when a particle coordinate is not finite.
+// fixed-point counts of np particles into grid (cleared here, with *bad); scratch (may be null): device
+// bytes, 256-byte aligned, that the tile sort may use; the result is the same without it
 void launch_deposit(int n, double box, const void* pos, int pos_fp32, long long np, long long* grid, int* bad,
-                    hipStream_t s);
+                    void* scratch, size_t scratch_bytes, hipStream_t s);
 // delta = Q 2^-40 N^3/np - 1 (NaN everywhere when *bad is set)
 // delta from the fixed-point counts; mean_q (optional, device): the mean of the counts, whose delta
 // value is subtracted in the same pass (mean removal)
@@ -247,7 +249,6 @@ void launch_counts_to_delta(int n, const long long* grid, long long np, double* 
                             const double* mean_q = nullptr);
 // zero `words` 8-byte words (a fill kernel: no memset node in captured streams)
 void launch_fill_zero(void* p, size_t words, hipStream_t s);
-void launch_zero_flag(int* bad, hipStream_t s);
 // out[k][p] = CIC interpolation of component k of mesh [nc][n3] (nc in 1..3), float64 (mesh_fp32 = 0)
 // or float32 (1) mesh
 void launch_interp(int n, double box, const void* mesh, int mesh_fp32, int nc, const void* pos, int pos_fp32,
@@ -258,10 +259,11 @@ void launch_deposit_backward(int n, double box, const void* pos, int pos_fp32, l
                              const double* grad_delta, double* grad_pos, hipStream_t s);
 // adjoint of launch_interp for dL/dout = g [nc][np]: grad_pos [3][np] (optional) and grad_mesh [nc][n3]
 // (optional, deterministic fixed-point sums); grid: n3 int64 scratch, st: 3 words of scratch, red:
-// absmean_scratch_doubles(n3, 1) doubles of scratch, 16-byte aligned
+// absmean_scratch_doubles(n3, 1) doubles of scratch, 16-byte aligned; scratch: as for launch_deposit
 void launch_interp_backward(int n, double box, const double* mesh, int nc, const void* pos, int pos_fp32, long long np,
                             const double* g, double* grad_pos, double* grad_mesh, long long* grid,
-                            unsigned long long* st, double* red, int* bad, hipStream_t s);
+                            unsigned long long* st, double* red, int* bad, void* scratch, size_t scratch_bytes,
+                            hipStream_t s);
 template <typename T>
 void launch_convert(size_t count, const void* in, int in_fp32, T* out, hipStream_t s);
 

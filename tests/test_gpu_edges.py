@@ -41,3 +41,37 @@ def test_power_spectrum_bins_and_gradient(dgp, n, batch, nbins):
         assert np.array_equal(cnt, cnt_ref)
         assert np.allclose(pk[b], ref, rtol=1e-12, atol=0) and np.allclose(pc[b], refc, rtol=1e-12, atol=0)
         assert rel_l2(gf[b].cpu().numpy(), power.power_spectrum_grad(f[b], g[b], box, nbins)) <= 1e-12
+
+
+def _sort_loads():
+    """(name, mesh, positions) of loads around the tile sort's rules, 2^18 to 2^20 particles."""
+    rng = np.random.default_rng(5)
+    np_ = 2 ** 20 + 37
+    lat = inputs.zeldovich_load(104, 128.0, 8)[0]
+    yield "small mesh", 64, lat[:, :np_].copy()
+    yield "lattice order, ragged", 128, 2.0 * lat[:, :np_]
+    yield "float32", 128, (2.0 * lat[:, :np_]).astype(np.float32)
+    yield "random order", 128, rng.uniform(0.0, 256.0, (3, np_))
+    # compact chunks deposited directly beside sorted ones
+    mixed = 2.0 * lat[:, :np_]
+    mixed[:, :300000] = 3.0 + rng.uniform(0.0, 8.0, (3, 300000))
+    yield "compact and spread chunks", 128, mixed
+    # one tile holding most particles (several work items), over the periodic corner, in random order
+    dense = (rng.normal(0.0, 6.0, (3, np_)) + 1.0) % 256.0
+    yield "dense periodic corner", 128, np.where(dense >= 256.0, 0.0, dense)
+    yield "just below the rule", 128, 2.0 * lat[:, :2 ** 18 - 1]
+    yield "at the rule", 128, 2.0 * lat[:, :2 ** 18]
+
+
+@pytest.mark.timeout(600)
+def test_deposit_tile_sort_bit_exact(dgp):
+    from oracle import pm
+    for name, n, pos in _sort_loads():
+        print(name, flush=True)
+        box = 2.0 * n
+        ref = pm.cic_deposit_fixed(pos.astype(np.float64), n, box)
+        with dgp.Plan(n, box) as plan:
+            g = torch.zeros(n ** 3, dtype=torch.int64, device="cuda")
+            for _ in range(2):   # the second pass over a workspace that the first one used
+                plan.deposit(to_dev(pos, torch.float32 if pos.dtype == np.float32 else torch.float64), g)
+            assert np.array_equal(g.cpu().numpy().reshape(n, n, n), ref), name
