@@ -17,7 +17,7 @@ OUT = os.path.join(HERE, "libdgp.so")
 BUILD = os.path.join(ROOT, "_build")
 ARCH = os.environ.get("DGP_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["passes.hip", "relax.hip", "adjoint.hip", "pm.hip", "api.cpp"]
+SOURCES = ["passes.hip", "plane.hip", "relax.hip", "adjoint.hip", "pm.hip", "api.cpp"]
 # Packed FP32 instructions are kept out of the generated code: the compiler would
 # otherwise form v_pk_* from ordinary float code.
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

@@ -554,8 +554,8 @@ static Ws<double> ws64(dgp_plan* pl) { return {pl->U, pl->S, pl->spec_u, pl->spe
 static Ws<float> ws32(dgp_plan* pl) { return {pl->U32, pl->S32, pl->spec_u32, pl->spec6_32, pl->partial32, pl->groups32}; }
 
 // S and the linear guess from delta (float64; S32 / U32 receive their float32 roundings when
-// given).  The axis-0/1 spectrum of delta stays in spectral field 6, where the PM step's
-// force computation picks it up.
+// given).  The axis-0/1 spectrum of delta (axis-0 where the plane kernels serve the mesh) stays in
+// spectral field 6, where the PM step's force computation picks it up.
 static int setup_source(dgp_plan* pl, const dgp_params* p, const double* delta, Ws<double>& w, bool want_linear,
                         hipStream_t s, float* S32 = nullptr, float* U32 = nullptr) {
   const int n = pl->n, B = pl->batch;
@@ -563,9 +563,14 @@ static int setup_source(dgp_plan* pl, const dgp_params* p, const double* delta, 
   const SpecCoef cf = spec_coef(pl, p);
   Timed tm(pl, s, DGP_T_SETUP);
   cx<double>* dspec = w.spec6 + 6 * fs;
-  TRY(fwd3<double>(pl, delta, dspec, B, nullptr, s));
-  launch_p3<double>(n, SPEC_SOURCE, dspec, fs, 1, w.spec6, fs, 2, B, cf, nullptr, nullptr, nullptr, s);
-  launch_p2<double>(n, w.spec6, 2, B, +1, nullptr, s);
+  if (plane_ok<double>(n)) {
+    launch_p1_fwd<double>(n, delta, dspec, B, nullptr, s);
+    launch_plane<double>(n, SPEC_SOURCE, dspec, fs, w.spec6, fs, want_linear ? 2 : 1, B, cf, nullptr, nullptr, s);
+  } else {
+    TRY(fwd3<double>(pl, delta, dspec, B, nullptr, s));
+    launch_p3<double>(n, SPEC_SOURCE, dspec, fs, 1, w.spec6, fs, 2, B, cf, nullptr, nullptr, nullptr, s);
+    launch_p2<double>(n, w.spec6, 2, B, +1, nullptr, s);
+  }
   launch_p1_inv<double>(n, w.spec6, w.S, B, nullptr, s, S32);
   if (want_linear) launch_p1_inv<double>(n, w.spec6 + fs, w.U, B, nullptr, s, U32);
   LAUNCHCHK();
@@ -578,17 +583,22 @@ static int enqueue_pass(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const Solve
   const int n = pl->n, B = pl->batch;
   const size_t fs = (size_t)B * pl->hs;
   const SpecCoef cf = spec_coef(pl, p);
-  {
-    Timed t(pl, s, tcls<T>(DGP_T_AXIS1_FWD));
-    launch_p2<T>(n, w.spec_u, 1, B, -1, pl->ctl, s);
-  }
-  {
+  if (plane_ok<T>(n)) {
     Timed t(pl, s, tcls<T>(DGP_T_FANOUT));
-    launch_p3<T>(n, SPEC_HSPLIT, w.spec_u, fs, 1, w.spec6, fs, 3, B, cf, nullptr, pl->mean_u, pl->ctl, s);
-  }
-  {
-    Timed t(pl, s, tcls<T>(DGP_T_AXIS1_INV));
-    launch_p2_split<T>(n, w.spec6, fs, B, pl->ctl, s);
+    launch_plane<T>(n, SPEC_HSPLIT, w.spec_u, fs, w.spec6, fs, 6, B, cf, pl->mean_u, pl->ctl, s);
+  } else {
+    {
+      Timed t(pl, s, tcls<T>(DGP_T_AXIS1_FWD));
+      launch_p2<T>(n, w.spec_u, 1, B, -1, pl->ctl, s);
+    }
+    {
+      Timed t(pl, s, tcls<T>(DGP_T_FANOUT));
+      launch_p3<T>(n, SPEC_HSPLIT, w.spec_u, fs, 1, w.spec6, fs, 3, B, cf, nullptr, pl->mean_u, pl->ctl, s);
+    }
+    {
+      Timed t(pl, s, tcls<T>(DGP_T_AXIS1_INV));
+      launch_p2_split<T>(n, w.spec6, fs, B, pl->ctl, s);
+    }
   }
   {
     TimedLaunch t(pl, tcls<T>(DGP_T_RELAX));
@@ -699,9 +709,14 @@ static int c_field(dgp_plan* pl, const dgp_params* p, const double* u, double* c
   const int n = pl->n, B = pl->batch;
   const size_t fs = (size_t)B * pl->hs;
   const SpecCoef cf = spec_coef(pl, p);
-  TRY(fwd3<double>(pl, u, pl->spec_u, B, nullptr, s));
-  launch_p3<double>(n, SPEC_CFIELD, pl->spec_u, fs, 1, pl->spec6, fs, 1, B, cf, nullptr, nullptr, nullptr, s);
-  launch_p2<double>(n, pl->spec6, 1, B, +1, nullptr, s);
+  if (plane_ok<double>(n)) {
+    launch_p1_fwd<double>(n, u, pl->spec_u, B, nullptr, s);
+    launch_plane<double>(n, SPEC_CFIELD, pl->spec_u, fs, pl->spec6, fs, 1, B, cf, nullptr, nullptr, s);
+  } else {
+    TRY(fwd3<double>(pl, u, pl->spec_u, B, nullptr, s));
+    launch_p3<double>(n, SPEC_CFIELD, pl->spec_u, fs, 1, pl->spec6, fs, 1, B, cf, nullptr, nullptr, nullptr, s);
+    launch_p2<double>(n, pl->spec6, 1, B, +1, nullptr, s);
+  }
   launch_p1_inv<double>(n, pl->spec6, c_out, B, nullptr, s);
   LAUNCHCHK();
   return DGP_OK;
@@ -877,6 +892,7 @@ static int force_mesh(dgp_plan* pl, const dgp_params* p, const double* delta, co
     cf.om15 = 1.5 * p->omega_m0 / (p->a * p->a * p->a * e * e);
   }
   const bool use_u = p->force_mode == DGP_FORCE_NLDGP;
+  const bool plane = plane_ok<double>(n);   // (what the solve's setup leaves depends on it, in either precision)
   if (pl->precision == DGP_FP32) {
     cx<float>* fin = pl->spec6_32 + 6 * fs;   // delta, then u
     float* tmp = pl->U32;                     // the solve's float32 iterates are free here
@@ -885,12 +901,16 @@ static int force_mesh(dgp_plan* pl, const dgp_params* p, const double* delta, co
     else
       launch_p1_fwd_from64(n, delta, fin, 1, nullptr, s);
     if (use_u) launch_p1_fwd_from64(n, u, fin + fs, 1, nullptr, s);
-    if (!delta_ready)
-      launch_p2<float>(n, fin, use_u ? 2 : 1, 1, -1, nullptr, s);
-    else if (use_u)
-      launch_p2<float>(n, fin + fs, 1, 1, -1, nullptr, s);
-    launch_p3<float>(n, SPEC_FORCES, fin, fs, use_u ? 2 : 1, pl->spec6_32, fs, 2, 1, cf, nullptr, nullptr, nullptr, s);
-    launch_p2_force_split<float>(n, pl->spec6_32, fs, 1, phi_n ? 1 : 0, cf.force_scale * cf.kf, s);
+    if (plane) {
+      launch_plane<float>(n, SPEC_FORCES, fin, fs, pl->spec6_32, fs, phi_n ? 4 : 3, 1, cf, nullptr, nullptr, s);
+    } else {
+      if (!delta_ready)
+        launch_p2<float>(n, fin, use_u ? 2 : 1, 1, -1, nullptr, s);
+      else if (use_u)
+        launch_p2<float>(n, fin + fs, 1, 1, -1, nullptr, s);
+      launch_p3<float>(n, SPEC_FORCES, fin, fs, use_u ? 2 : 1, pl->spec6_32, fs, 2, 1, cf, nullptr, nullptr, nullptr, s);
+      launch_p2_force_split<float>(n, pl->spec6_32, fs, 1, phi_n ? 1 : 0, cf.force_scale * cf.kf, s);
+    }
     launch_p1_inv<float>(n, pl->spec6_32, pl->mesh3_32, 3, nullptr, s);
     if (phi_n) {
       launch_p1_inv<float>(n, pl->spec6_32 + 3 * fs, tmp, 1, nullptr, s);
@@ -902,12 +922,16 @@ static int force_mesh(dgp_plan* pl, const dgp_params* p, const double* delta, co
   cx<double>* fin = pl->spec6 + 6 * fs;   // delta, then u
   if (!delta_ready) launch_p1_fwd<double>(n, delta, fin, 1, nullptr, s);
   if (use_u) launch_p1_fwd<double>(n, u, fin + fs, 1, nullptr, s);
-  if (!delta_ready)
-    launch_p2<double>(n, fin, use_u ? 2 : 1, 1, -1, nullptr, s);
-  else if (use_u)
-    launch_p2<double>(n, fin + fs, 1, 1, -1, nullptr, s);
-  launch_p3<double>(n, SPEC_FORCES, fin, fs, use_u ? 2 : 1, pl->spec6, fs, 2, 1, cf, nullptr, nullptr, nullptr, s);
-  launch_p2_force_split<double>(n, pl->spec6, fs, 1, phi_n ? 1 : 0, cf.force_scale * cf.kf, s);
+  if (plane) {
+    launch_plane<double>(n, SPEC_FORCES, fin, fs, pl->spec6, fs, phi_n ? 4 : 3, 1, cf, nullptr, nullptr, s);
+  } else {
+    if (!delta_ready)
+      launch_p2<double>(n, fin, use_u ? 2 : 1, 1, -1, nullptr, s);
+    else if (use_u)
+      launch_p2<double>(n, fin + fs, 1, 1, -1, nullptr, s);
+    launch_p3<double>(n, SPEC_FORCES, fin, fs, use_u ? 2 : 1, pl->spec6, fs, 2, 1, cf, nullptr, nullptr, nullptr, s);
+    launch_p2_force_split<double>(n, pl->spec6, fs, 1, phi_n ? 1 : 0, cf.force_scale * cf.kf, s);
+  }
   launch_p1_inv<double>(n, pl->spec6, pl->mesh3, 3, nullptr, s);
   if (phi_n) launch_p1_inv<double>(n, pl->spec6 + 3 * fs, phi_n, 1, nullptr, s);
   LAUNCHCHK();
@@ -1217,9 +1241,14 @@ static int hessians(dgp_plan* pl, const dgp_params* p, const double* u, double* 
   const int n = pl->n, B = pl->batch;
   const size_t fs = (size_t)B * pl->hs, bn = (size_t)B * pl->n3;
   const SpecCoef cf = spec_coef(pl, p);
-  TRY(fwd3<double>(pl, u, pl->spec_u, B, nullptr, s));
-  launch_p3<double>(n, SPEC_HSPLIT, pl->spec_u, fs, 1, pl->spec6, fs, 3, B, cf, nullptr, pl->mean_u, nullptr, s);
-  launch_p2_split<double>(n, pl->spec6, fs, B, nullptr, s);
+  if (plane_ok<double>(n)) {
+    launch_p1_fwd<double>(n, u, pl->spec_u, B, nullptr, s);
+    launch_plane<double>(n, SPEC_HSPLIT, pl->spec_u, fs, pl->spec6, fs, 5, B, cf, pl->mean_u, nullptr, s);
+  } else {
+    TRY(fwd3<double>(pl, u, pl->spec_u, B, nullptr, s));
+    launch_p3<double>(n, SPEC_HSPLIT, pl->spec_u, fs, 1, pl->spec6, fs, 3, B, cf, nullptr, pl->mean_u, nullptr, s);
+    launch_p2_split<double>(n, pl->spec6, fs, B, nullptr, s);
+  }
   for (int f = 0; f < 5; ++f) launch_p1_inv<double>(n, pl->spec6 + f * fs, H5 + f * bn, B, nullptr, s);
   LAUNCHCHK();
   return DGP_OK;

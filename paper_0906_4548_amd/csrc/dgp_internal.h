@@ -165,6 +165,13 @@ template <typename T>
 void launch_p3(int n, SpecMode mode, const cx<T>* in, size_t in_stride, int nin, cx<T>* out,
                size_t out_stride, int nout, int batch, const SpecCoef& coef, const double* bin_coef,
                double* mean_out, const SolveCtl* ctl, hipStream_t s);
+// axis-1 forward, axis-2 and axis-1 inverse passes of whole k0 planes in one launch (plane.hip), for meshes
+// whose plane fits the LDS (plane_ok); `in` as the axis-0 pass left it, output o to out + o * out_stride
+template <typename T>
+bool plane_ok(int n);
+template <typename T>
+void launch_plane(int n, SpecMode mode, const cx<T>* in, size_t in_stride, cx<T>* out, size_t out_stride, int nout,
+                  int batch, const SpecCoef& cf, double* mean_out, const SolveCtl* ctl, hipStream_t s);
 int p3_row_groups(int n);   // workgroups per batch element of the float64 axis-2 pass
 // binned power spectrum of [batch] axis-0/1 spectra: sums[b][nbins] of |f|^2 (times 1/kbar^4 with
 // coef.power_c) over the modes with thr[bin] <= |n|^2 < thr[bin + 1]; partial: p3_row_groups(n) x batch x

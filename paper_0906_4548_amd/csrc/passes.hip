@@ -18,6 +18,7 @@
 //   k = 0 multipliers of 1/kbar, 1/k^2, k_i k_j / k^2 are 0; a multiplier odd in
 //   component d (mixed Hessian terms, the gradient) is 0 at the Nyquist index of d.
 #include "dgp_internal.h"
+#include "spectral.h"
 
 namespace dgp {
 
@@ -409,24 +410,6 @@ k_p2_force_split(cx<T>* __restrict__ data, size_t fstride, int batch, int with_p
 }
 
 // ------------------------------------------------------------------ axis 2 with spectral multipliers
-struct Mode3 {
-  int n0, n1, n2;        // signed mode numbers (n0 >= 0 on the half axis)
-  bool q0, q1, q2;       // Nyquist flags
-  long long msq;         // |n|^2
-};
-
-__device__ __forceinline__ Mode3 mode_of(int N, int k0, int k1, int k2) {
-  Mode3 m;
-  m.n0 = k0;
-  m.n1 = (k1 < N / 2) ? k1 : k1 - N;
-  m.n2 = (k2 < N / 2) ? k2 : k2 - N;
-  m.q0 = (k0 == N / 2);
-  m.q1 = (k1 == N / 2);
-  m.q2 = (k2 == N / 2);
-  m.msq = (long long)m.n0 * m.n0 + (long long)m.n1 * m.n1 + (long long)m.n2 * m.n2;
-  return m;
-}
-
 template <typename T, int N, SpecMode MODE>
 __global__ void __launch_bounds__((Geo<T, N>::kP3))
 k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, size_t out_stride,
@@ -522,26 +505,13 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
     if constexpr (MODE == SPEC_HSPLIT) {
       // The Hessian multipliers n_i n_j / |n|^2 factor as (1/|n|^2) times one factor per axis:
       // this pass applies 1/|n|^2 and the axis-2 factor i n2 (0 at the Nyquist index), the axis-1
-      // pass (k_p2_split) the axis-1 and axis-0 factors.  Per mode: ic = 1/(N^3 |n|^2) and
-      // ib = -1/(N^3 kappa kf |n|), both 0 at n = 0; float32 fields form them in float32
-      // (reciprocal and reciprocal-sqrt estimates, the reciprocal refined by one Newton step).
+      // pass (k_p2_split) the axis-1 and axis-0 factors.
       T ic[R], ib[R], a2[R];
-      const float in3f = float(cf.inv_n3), ikbs = float(cf.inv_n3 / (cf.kappa * kf));
 #pragma unroll
       for (int q = 0; q < R; ++q) {
         const Mode3 m = mode_of(N, k0, k1, t + q * TT);
-        const bool nz = m.msq != 0;
-        if constexpr (sizeof(T) == 4) {
-          const float ms = float(m.msq);
-          float r = __builtin_amdgcn_rcpf(ms);
-          r = r * (2.0f - ms * r);
-          ic[q] = nz ? r * in3f : 0.0f;
-          ib[q] = nz ? -__builtin_amdgcn_rsqf(ms) * ikbs : 0.0f;
-        } else {
-          const double ms = double(m.msq);
-          ic[q] = nz ? cf.inv_n3 / ms : 0.0;
-          ib[q] = nz ? -cf.inv_n3 / (cf.kappa * kf * sqrt(ms)) : 0.0;
-        }
+        ic[q] = inv_square<T>(cf, m);
+        ib[q] = nonlocal_mult<T>(cf, m);
         a2[q] = m.q2 ? T(0) : T(m.n2);
       }
 #pragma unroll 1
@@ -576,31 +546,7 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
 #pragma unroll
       for (int q = 0; q < R; ++q) {
         const Mode3 m = mode_of(N, k0, k1, t + q * TT);
-        ph[q] = mk(T(0), T(0));
-        if (m.msq != 0) {
-          const double ms = double(m.msq);
-          const double kb = cf.kappa * kf * sqrt(ms);
-          const double ikb = 1.0 / kb;
-          // phi(k) from the modified Poisson equation (or its linear / GR forms)
-          const double dr = double(v[q].x), di = double(v[q].y);
-          double nr, ni, den;
-          if (cf.force_mode == FORCE_GRH || cf.force_mode == FORCE_GR) {   // Eq. GRPoisson (kappa, om15 of the run's background)
-            nr = cf.om15 * dr; ni = cf.om15 * di; den = kb * kb;
-          } else {
-            double ur, ui;
-            if (cf.force_mode == FORCE_NLDGP) {
-              ur = double(v2[q].x); ui = double(v2[q].y);
-            } else {   // linear solution from delta
-              const double sl = cf.A * (1.0 - cf.beta * ikb) / (cf.alpha - cf.gamma * ikb);
-              ur = sl * dr; ui = sl * di;
-            }
-            const double cu = -cf.inv2eta + cf.c2 * ikb;
-            nr = cf.om15 * dr + cu * ur;
-            ni = cf.om15 * di + cu * ui;
-            den = kb * kb + kb * cf.inv_eta_nl;
-          }
-          ph[q] = mk(T(-nr / den * cf.inv_n3), T(-ni / den * cf.inv_n3));
-        }
+        ph[q] = phi_of(cf, m, v[q], (cf.force_mode == FORCE_NLDGP) ? v2[q] : v[q]);
       }
       // two outputs: phi (slot 0; the axis-1 pass k_p2_force_split forms g0, g1 and phi from it)
       // and g2 (slot 2), the gradient factor being a product of per-axis factors
@@ -629,14 +575,7 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
 #pragma unroll
       for (int q = 0; q < R; ++q) {
         const Mode3 m = mode_of(N, k0, k1, t + q * TT);
-        m0[q] = T(0);
-        m1[q] = T(0);
-        if (m.msq != 0) {
-          const double ikb = 1.0 / (cf.kappa * kf * sqrt(double(m.msq)));
-          const double sv = cf.A * (1.0 - cf.beta * ikb);
-          m0[q] = T(sv * cf.inv_n3);
-          m1[q] = T(sv / (cf.alpha - cf.gamma * ikb) * cf.inv_n3);
-        }
+        source_mults(cf, m, m0[q], m1[q]);
       }
 #pragma unroll 1
       for (int o = 0; o < 2; ++o) {
