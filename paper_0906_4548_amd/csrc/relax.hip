@@ -645,6 +645,169 @@ k_relax_w(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf,
   }
 }
 
+// ------------------------------------------------------------------ small meshes (N <= 64)
+// The same pass with one group of threads per field: a launch on a mesh this small does not fill the
+// device, and its time is its latency chain, six transforms one after another in k_relax and
+// k_relax_w.  Here the six fields are loaded and inverse-transformed at once by six groups, the
+// transformed values meet in LDS, every thread takes pair-points of the update, and the first group
+// forward-transforms u^(n+1).  A group's transforms (radix 8, one exchange up to N = 64) sit inside
+// one wavefront.  One 32^3 float64 field: 10.8 -> 5.5 us, one 64^3: 13.6 -> 10.2 us; 5 x 64^3 float32
+// 15.1 us either way.
+constexpr int kRelaxSmallMax = 64;
+template <typename T, int N>
+struct RelaxSGeo {
+  using P = Plan8<N>;
+  static constexpr int R = P::R, kT = N / R;
+  static constexpr int kBase = 128 / (4 * int(sizeof(T)));   // column pairs of a 128-byte row segment
+  static constexpr int kTP = kBase < N / 2 ? kBase : N / 2;
+  static constexpr int kGroup = kTP * kT, kThreads = 6 * kGroup, kWaves = (kThreads + 63) / 64;
+  static constexpr int kPts = N * kTP, kPPT = (kPts + kThreads - 1) / kThreads;   // pair-points, per thread
+  // exchange rows padded by one after every 8, as in k_relax
+  static constexpr int kField = (N + N / 8) * kTP;
+  static_assert(64 % kGroup == 0, "a group's lanes sit in one wavefront");
+};
+
+template <typename T, int C>
+struct LdsColWave : LdsCol<T, C, 8> {   // column exchanges inside one wavefront
+  __device__ __forceinline__ void sync() const { wave_sync(); }
+};
+
+template <typename T, int N>
+__global__ void __launch_bounds__((RelaxSGeo<T, N>::kThreads))
+k_relax_small(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf, const T* __restrict__ sfield,
+              cx<T>* __restrict__ spec_u, double* __restrict__ partial, const double* __restrict__ mean_u, SolveCfg cfg,
+              const SolveCtl* __restrict__ ctl, const cx<T>* __restrict__ tw) {
+  using G = RelaxSGeo<T, N>;
+  using P = typename G::P;
+  constexpr int R = G::R, TP = G::kTP, TT = G::kT, NT = G::kThreads, H = N / 2 + 1;
+  constexpr size_t N3 = (size_t)N * N * N, NN = (size_t)N * N;
+  const int b = blockIdx.z;
+  if (ctl[b].done) return;
+  int tile, i1;
+  xcd_tile(tile, i1);
+  const int i2 = tile * 2 * TP;
+  const int f = threadIdx.x / G::kGroup, l = threadIdx.x % G::kGroup, c = l % TP, t = l / TP;
+  __shared__ cx<T> lds[6 * G::kField];
+  __shared__ cx<T> twl[N];
+  __shared__ double red[G::kWaves];
+  __shared__ int redi[G::kWaves];
+  const size_t col0 = (size_t)b * H * NN + (size_t)i1 * N + i2;
+  // the spectral rows of the thread's transform elements (row N - e conjugated), one column pair each
+  const cx<T>* src = spec6 + f * fstride + col0 + 2 * c;
+  cx<T> xa[R], xb[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int e = t + q * TT;
+    const cx<T>* p = src + (size_t)(e <= N / 2 ? e : N - e) * NN;
+    xa[q] = mk(p[0].x, p[0].y);
+    xb[q] = mk(p[1].x, p[1].y);
+  }
+  const size_t pt0 = (size_t)i1 * N + i2;
+  const T* uin = ubuf + ((size_t)ctl[b].cur * cfg.batch + b) * N3 + pt0;
+  const T* sp = sfield + (size_t)b * N3 + pt0;
+  cx<T> up[G::kPPT], spv[G::kPPT];
+#pragma unroll
+  for (int k = 0; k < G::kPPT; ++k) {
+    const int pt = min(int(threadIdx.x) + k * NT, G::kPts - 1);
+    const size_t off = (size_t)(pt / TP) * NN + 2 * (pt % TP);
+    up[k] = *reinterpret_cast<const cx<T>*>(uin + off);
+    spv[k] = *reinterpret_cast<const cx<T>*>(sp + off);
+  }
+  for (int i = threadIdx.x; i < N; i += NT) twl[i] = tw[i];
+  lds_barrier();
+  cx<T> v[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int e = t + q * TT;
+    if (e > N / 2) {
+      xa[q] = conjg(xa[q]);
+      xb[q] = conjg(xb[q]);
+    }
+    if (e == 0 || e == N / 2) { xa[q].y = T(0); xb[q].y = T(0); }
+    v[q] = mk(xa[q].x - xb[q].y, xa[q].y + xb[q].x);   // x_a + i x_b
+  }
+  LdsColWave<T, TP> L;
+  L.base = lds + f * G::kField;
+  L.c = c;
+  fft<T, N, P, +1>(v, twl, L, t);
+  wave_sync();
+#pragma unroll
+  for (int q = 0; q < R; ++q) L.store(t + q * TT, v[q]);
+  lds_barrier();
+  // pointwise residual and update; a pair-point's slots are read, and its first one rewritten, by
+  // its own thread only
+  const PointCoef pc = point_coef(cfg, mean_u[b]);
+  T* uout = ubuf + ((size_t)ctl[b].out * cfg.batch + b) * N3 + pt0;
+  double abs_r = 0.0;
+  int nbad = 0;
+#pragma unroll
+  for (int k = 0; k < G::kPPT; ++k) {
+    const int pt = int(threadIdx.x) + k * NT;
+    if (pt >= G::kPts) break;
+    const int e = pt / TP, pc2 = pt % TP;
+    LdsCol<T, TP, 8> A{lds, pc2};
+    cx<T> h[6];
+#pragma unroll
+    for (int g = 0; g < 6; ++g) {
+      A.base = lds + g * G::kField;
+      h[g] = A.load(e);
+    }
+    // sum of the squared entries other than h22 and -(h00 + h11), in the field's type
+    T sx = h[0].x * h[0].x, sy = h[0].y * h[0].y;
+    sx += h[1].x * h[1].x;
+    sy += h[1].y * h[1].y;
+#pragma unroll
+    for (int g = 2; g < 5; ++g) {
+      sx += T(2) * h[g].x * h[g].x;
+      sy += T(2) * h[g].y * h[g].y;
+    }
+    const double ux = relax_point(pc, double(up[k].x), double(spv[k].x), double(h[5].x), double(sx),
+                                  double(-h[0].x - h[1].x), abs_r, nbad);
+    const double uy = relax_point(pc, double(up[k].y), double(spv[k].y), double(h[5].y), double(sy),
+                                  double(-h[0].y - h[1].y), abs_r, nbad);
+    const cx<T> o = mk(T(ux), T(uy));
+    *reinterpret_cast<cx<T>*>(uout + (size_t)e * NN + 2 * pc2) = o;
+    A.base = lds;
+    A.store(e, o);
+  }
+  abs_r = wave_sum<64>(abs_r);
+  nbad = wave_sum<64>(nbad);
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6] = abs_r;
+    redi[threadIdx.x >> 6] = nbad;
+  }
+  lds_barrier();
+  if (f == 0) {   // forward axis-0 transform of u^(n+1)
+#pragma unroll
+    for (int q = 0; q < R; ++q) v[q] = L.load(t + q * TT);
+    fft<T, N, P, -1>(v, twl, L, t);
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < R; ++q) L.store(t + q * TT, v[q]);
+  }
+  lds_barrier();
+  cx<T>* dst = spec_u + col0;
+  for (int idx = threadIdx.x; idx < H * TP; idx += NT) {
+    const int k = idx / TP, p = idx % TP;
+    const LdsCol<T, TP, 8> Z{lds, p};
+    const cx<T> zk = Z.load(k), zn = Z.load((N - k) & (N - 1));
+    dst[(size_t)k * NN + 2 * p] = mk(T(0.5) * (zk.x + zn.x), T(0.5) * (zk.y - zn.y));
+    dst[(size_t)k * NN + 2 * p + 1] = mk(T(0.5) * (zk.y + zn.y), T(0.5) * (zn.x - zk.x));
+  }
+  if (threadIdx.x == 0) {
+    double sr = 0.0;
+    int sb = 0;
+    for (int i = 0; i < G::kWaves; ++i) {
+      sr += red[i];
+      sb += redi[i];
+    }
+    const size_t g = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const size_t groups = (size_t)gridDim.x * gridDim.y;
+    partial[((size_t)b * groups + g) * 2] = sr;
+    partial[((size_t)b * groups + g) * 2 + 1] = double(sb);
+  }
+}
+
 // Convergence control: one workgroup of NT threads per batch element (strided partial sums,
 // wavefront shuffles, a fixed-order sum over the wavefronts).  Latency bound: an element per
 // workgroup, and 256 threads where those read all partial sums in a few loads (5 x 64^3 float32
@@ -794,7 +957,12 @@ static void relax_n(const cx<T>* spec6, T* ubuf, const T* sfield, cx<T>* spec_u,
                     const double* mean_u, int batch, const SolveCfg& cfg, const SolveCtl* ctl, hipStream_t s,
                     hipEvent_t ev0, hipEvent_t ev1) {
   constexpr size_t fstride = (size_t)(N / 2 + 1) * N * N;
-  if constexpr (sizeof(T) == 8) {
+  if constexpr (N <= kRelaxSmallMax) {
+    using G = RelaxSGeo<T, N>;
+    dim3 grid(N / (2 * G::kTP), N, batch);
+    hipExtLaunchKernelGGL((k_relax_small<T, N>), grid, dim3(G::kThreads), 0, s, ev0, ev1, 0, spec6, fstride * batch,
+                          ubuf, sfield, spec_u, partial, mean_u, cfg, ctl, twiddles<T>(N));
+  } else if constexpr (sizeof(T) == 8) {
     using W = RelaxWGeo<T, N>;
     dim3 grid(N / (2 * W::kTP), N, batch);
     hipExtLaunchKernelGGL((k_relax_w<T, N>), grid, dim3(W::kThreads), 0, s, ev0, ev1, 0, spec6, fstride * batch,
@@ -828,7 +996,8 @@ void launch_relax(int n, const cx<T>* spec6, T* ubuf, const T* sfield, cx<T>* sp
 // column pairs per workgroup of the relaxation kernel that launches for (T, N)
 template <typename T, int N>
 static constexpr int relax_tp() {
-  if constexpr (sizeof(T) == 8) return RelaxWGeo<T, N>::kTP;
+  if constexpr (N <= kRelaxSmallMax) return RelaxSGeo<T, N>::kTP;
+  else if constexpr (sizeof(T) == 8) return RelaxWGeo<T, N>::kTP;
   else return RelaxGeo<T, N>::G::kTP;
 }
 
