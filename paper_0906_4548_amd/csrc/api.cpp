@@ -509,6 +509,7 @@ static SpecCoef spec_coef(const dgp_plan* pl, const dgp_params* p) {
   c.force_scale = kCOverH0 * kCOverH0;
   c.inv_n3 = 1.0 / double(pl->n3);
   c.lam2 = 2.0 * p->lambda;
+  c.nl_scale = c.inv_n3 / (c.kappa * c.kf);
   c.force_mode = p->force_mode;
   c.power_c = 0;
   c.nbins = 64;

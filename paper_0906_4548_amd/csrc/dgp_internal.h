@@ -38,6 +38,7 @@ struct SpecCoef {
   double force_scale;  // (c/H0)^2
   double inv_n3;    // 1/N^3 (inverse-transform normalisation, folded into the multiplier)
   double lam2;      // 2 lam (adjoint combine)
+  double nl_scale;  // 1/(N^3 kappa kf): the nonlocal term's -1/kbar, normalised, is -nl_scale/|n|
   int force_mode;   // ForceMode
   int power_c;      // power spectrum and its gradient: weight |f|^2 by 1/kbar^4 (spectrum of C from u)
   int nbins;        // power spectrum: number of bins

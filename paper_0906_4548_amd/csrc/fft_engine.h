@@ -303,7 +303,8 @@ struct LdsCol {
   int c;
   __device__ __forceinline__ int at(int e) const {
     const unsigned u = unsigned(e);
-    return int(PG > 0 ? u + u / PG : u) * C + c;
+    if constexpr (PG > 0) return int(u + u / PG) * C + c;
+    else return int(u) * C + c;
   }
   __device__ __forceinline__ cx<T> load(int e) const { return base[at(e)]; }
   __device__ __forceinline__ void store(int e, cx<T> v) const { base[at(e)] = v; }

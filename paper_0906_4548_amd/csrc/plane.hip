@@ -24,7 +24,7 @@ struct PlaneGeo {
   // elements apart) and consecutive rows over the banks
   static constexpr int kLD = N + N / R;
   static_assert(kThreads <= 1024 && kT <= 64 && 64 % kT == 0, "a row's threads sit in one wavefront");
-  static_assert(sizeof(cx<T>) * N * kLD <= 160 * 1024, "the plane must fit the LDS");
+  static_assert(sizeof(cx<T>) * N * (kLD + 1) <= 160 * 1024, "the plane and the twiddles must fit the LDS");
   static __device__ __forceinline__ int at(int r, int e) { return r * kLD + e + int(unsigned(e) / R); }
 };
 
@@ -61,6 +61,8 @@ k_plane(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out,
   if (ctl != nullptr && ctl[b].done != 0) return;
   int tid = threadIdx.x;
   __shared__ cx<T> lds[N * G::kLD];
+  __shared__ cx<T> twl[N];   // (the first twiddled stage would wait on a cold global load)
+  for (int i = tid; i < N; i += G::kThreads) twl[i] = tw[i];   // ordered by the first exchange's barrier
   const size_t off = ((size_t)b * H + k0) * N * N;
 
   auto forward = [&](const cx<T>* src, cx<T> (&v)[R]) {
@@ -70,14 +72,14 @@ k_plane(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out,
     const PlaneRow<T, N> LR{lds, r};
 #pragma unroll
     for (int q = 0; q < R; ++q) v[q] = src[off + c + (size_t)(t + q * TT) * N];
-    fft<T, N, P, -1>(v, tw, LC, t);
+    fft<T, N, P, -1>(v, twl, LC, t);
     lds_barrier();
 #pragma unroll
     for (int q = 0; q < R; ++q) lds[G::at(t + q * TT, c)] = v[q];
     lds_barrier();
 #pragma unroll
     for (int q = 0; q < R; ++q) v[q] = lds[G::at(r, tr + q * TT)];
-    fft<T, N, P, -1>(v, tw, LR, tr);
+    fft<T, N, P, -1>(v, twl, LR, tr);
   };
   cx<T> v[R];
   if constexpr (MODE == SPEC_FORCES) {
@@ -99,24 +101,24 @@ k_plane(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out,
   const int o1 = min(nout, int(blockIdx.x) * per + per);
 #pragma unroll 1
   for (int o = blockIdx.x * per; o < o1; ++o) {
-    // opaque per output: twiddles, addresses and multipliers are not held across the loop
-    const cx<T>* twq = tw;
-    asm volatile("" : "+s"(twq), "+v"(tid));
+    // opaque per output: addresses and multipliers are not held across the loop
+    asm volatile("" : "+v"(tid));
     const int c = tid % N, t = tid / N, r = tid / TT, tr = tid % TT;
     const PlaneCol<T, N> LC{lds, c};
     const PlaneRow<T, N> LR{lds, r};
+    // SPEC_HSPLIT: n_i n_j / |n|^2 (0 where an odd factor is at its Nyquist index); the part that is
+    // constant along the row
+    const Mode3 mr = mode_of(N, k0, r, 0);
+    const T o0 = mr.q0 ? T(0) : T(mr.n0), o1f = mr.q1 ? T(0) : T(mr.n1);
+    const T rowf = o == 0 ? T(mr.n0 * mr.n0) : o == 1 ? T(mr.n1 * mr.n1) : o == 2 ? o0 * o1f : o == 3 ? o0 : o1f;
     cx<T> w[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) {
       const Mode3 m = mode_of(N, k0, r, tr + q * TT);
-      if constexpr (MODE == SPEC_HSPLIT) {   // n_i n_j / |n|^2 (0 where an odd factor is at its Nyquist index)
-        if (o == 5) {
-          w[q] = scale(v[q], nonlocal_mult<T>(cf, m));
-        } else {
-          const int i = o == 1 || o == 4 ? m.n1 : m.n0, j = o == 0 ? m.n0 : o < 3 ? m.n1 : m.n2;
-          const bool zero = (o == 2 && (m.q0 || m.q1)) || (o == 3 && (m.q0 || m.q2)) || (o == 4 && (m.q1 || m.q2));
-          w[q] = scale(v[q], zero ? T(0) : T(i * j) * inv_square<T>(cf, m));
-        }
+      if constexpr (MODE == SPEC_HSPLIT) {   // row factor (n_i n_j or n_i) times the axis-2 factor / |n|^2
+        T f = o == 5 ? nonlocal_mult<T>(cf, m) : rowf * inv_square<T>(cf, m);
+        if (o == 3 || o == 4) f *= m.q2 ? T(0) : T(m.n2);
+        w[q] = scale(v[q], f);
       } else if constexpr (MODE == SPEC_SOURCE) {
         T ms, ml;
         source_mults(cf, m, ms, ml);
@@ -130,14 +132,14 @@ k_plane(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out,
         w[q] = scale(v[q], T(-ikb * ikb * cf.inv_n3));
       }
     }
-    fft<T, N, P, +1>(w, twq, LR, tr);
+    fft<T, N, P, +1>(w, twl, LR, tr);
     wave_sync();
 #pragma unroll
     for (int q = 0; q < R; ++q) lds[G::at(r, tr + q * TT)] = w[q];
     lds_barrier();
 #pragma unroll
     for (int q = 0; q < R; ++q) w[q] = lds[G::at(t + q * TT, c)];
-    fft<T, N, P, +1>(w, twq, LC, t);
+    fft<T, N, P, +1>(w, twl, LC, t);
     cx<T>* const dst = out + o * out_stride + off + c;
 #pragma unroll
     for (int q = 0; q < R; ++q) dst[(size_t)(t + q * TT) * N] = w[q];

@@ -8,7 +8,7 @@ namespace dgp {
 struct Mode3 {
   int n0, n1, n2;        // signed mode numbers (n0 >= 0 on the half axis)
   bool q0, q1, q2;       // Nyquist flags
-  long long msq;         // |n|^2
+  int msq;               // |n|^2 (at most 3 x 256^2)
 };
 
 __device__ __forceinline__ Mode3 mode_of(int N, int k0, int k1, int k2) {
@@ -19,7 +19,7 @@ __device__ __forceinline__ Mode3 mode_of(int N, int k0, int k1, int k2) {
   m.q0 = (k0 == N / 2);
   m.q1 = (k1 == N / 2);
   m.q2 = (k2 == N / 2);
-  m.msq = (long long)m.n0 * m.n0 + (long long)m.n1 * m.n1 + (long long)m.n2 * m.n2;
+  m.msq = m.n0 * m.n0 + m.n1 * m.n1 + m.n2 * m.n2;
   return m;
 }
 
@@ -33,15 +33,24 @@ __device__ __forceinline__ T inv_square(const SpecCoef& cf, const Mode3& m) {
     r = r * (2.0f - ms * r);
     return m.msq != 0 ? r * float(cf.inv_n3) : 0.0f;
   } else {
-    return m.msq != 0 ? cf.inv_n3 / double(m.msq) : 0.0;
+    const double ms = double(m.msq);   // reciprocal estimate and two Newton steps
+    double r = __builtin_amdgcn_rcp(ms);
+    r = fma(r, fma(-ms, r, 1.0), r);
+    r = fma(r, fma(-ms, r, 1.0), r);
+    return m.msq != 0 ? r * cf.inv_n3 : 0.0;
   }
 }
 template <typename T>
 __device__ __forceinline__ T nonlocal_mult(const SpecCoef& cf, const Mode3& m) {
-  if constexpr (sizeof(T) == 4)
-    return m.msq != 0 ? -__builtin_amdgcn_rsqf(float(m.msq)) * float(cf.inv_n3 / (cf.kappa * cf.kf)) : 0.0f;
-  else
-    return m.msq != 0 ? -cf.inv_n3 / (cf.kappa * cf.kf * sqrt(double(m.msq))) : 0.0;
+  if constexpr (sizeof(T) == 4) {
+    return m.msq != 0 ? -__builtin_amdgcn_rsqf(float(m.msq)) * float(cf.nl_scale) : 0.0f;
+  } else {
+    const double ms = double(m.msq);   // reciprocal-sqrt estimate and two Newton steps
+    double r = __builtin_amdgcn_rsq(ms);
+    r = fma(0.5 * r, fma(-ms * r, r, 1.0), r);
+    r = fma(0.5 * r, fma(-ms * r, r, 1.0), r);
+    return m.msq != 0 ? -cf.nl_scale * r : 0.0;
+  }
 }
 
 // multipliers, times 1/N^3 (0 at k = 0), of S = A (1 - beta/kbar) delta and of the linear solution
