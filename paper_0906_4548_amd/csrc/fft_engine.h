@@ -211,9 +211,13 @@ template <int N, int SEL> struct PlanPick { using type = Plan8<N>; };
 template <int N> struct PlanPick<N, 1> { using type = Plan<N>; };
 template <int N> struct PlanPick<N, 2> { using type = Plan4<N>; };
 
-// One Stockham stage.  v: the thread's R registers.  lds: accessor with
-// load(e), store(e, value) for element e of this thread's transform.  The
-// caller guarantees a barrier-safe LDS region per transform.
+// One Stockham stage.  v: the thread's R registers.  lds: accessor with load_q<S>(j, q), element
+// j + q S (j < S = N / r) of this thread's transform, and store_q<Ns>(e, q, value), element e + q Ns
+// with e = (j div Ns) Ns r + j mod Ns; q is a constant once unrolled.  In both, for every power of
+// two P, (e + q S) div P = e div P + (q S) div P (the low parts never carry), so a padded or split
+// layout takes one address per call and constant offsets; formed per element, the address
+// arithmetic is as much vector work as the transform.  The caller guarantees a barrier-safe LDS
+// region per transform.
 template <typename T, int N, int R, int r, int Ns, bool FIRST, bool LAST, int DIR, class Lds>
 __device__ __forceinline__ void fft_stage(cx<T> (&v)[R], const cx<T>* __restrict__ tw, Lds& lds, int t) {
   constexpr int TT = N / R;   // threads per transform
@@ -229,7 +233,7 @@ __device__ __forceinline__ void fft_stage(cx<T> (&v)[R], const cx<T>* __restrict
     for (int b = 0; b < B; ++b) {
       const int j = t + b * TT;
 #pragma unroll
-      for (int q = 0; q < r; ++q) x[b * r + q] = lds.load(j + q * (N / r));
+      for (int q = 0; q < r; ++q) x[b * r + q] = lds.template load_q<N / r>(j, q);
     }
   }
 #pragma unroll
@@ -252,7 +256,7 @@ __device__ __forceinline__ void fft_stage(cx<T> (&v)[R], const cx<T>* __restrict
       const int j = t + b * TT;
       const int base = (j / Ns) * Ns * r + (j % Ns);
 #pragma unroll
-      for (int q = 0; q < r; ++q) lds.store(base + q * Ns, x[b * r + q]);
+      for (int q = 0; q < r; ++q) lds.template store_q<Ns>(base, q, x[b * r + q]);
     }
     lds.sync();
   } else {
@@ -308,6 +312,11 @@ struct LdsCol {
   }
   __device__ __forceinline__ cx<T> load(int e) const { return base[at(e)]; }
   __device__ __forceinline__ void store(int e, cx<T> v) const { base[at(e)] = v; }
+  template <int S>
+  __device__ __forceinline__ cx<T> load_q(int j, int q) const { return base[at(j) + off(q * S)]; }
+  template <int Ns>
+  __device__ __forceinline__ void store_q(int e, int q, cx<T> v) const { base[at(e) + off(q * Ns)] = v; }
+  static __device__ __forceinline__ int off(int d) { return (PG > 0 ? d + d / (PG > 0 ? PG : 1) : d) * C; }
   __device__ __forceinline__ void sync() const { lds_barrier(); }
 };
 
@@ -327,6 +336,10 @@ struct LdsRow {
   __device__ __forceinline__ int at(int e) const { return c * kStride + e + unsigned(e) / kPad; }
   __device__ __forceinline__ cx<T> load(int e) const { return base[at(e)]; }
   __device__ __forceinline__ void store(int e, cx<T> v) const { base[at(e)] = v; }
+  template <int S>
+  __device__ __forceinline__ cx<T> load_q(int j, int q) const { return base[at(j) + q * S + q * S / kPad]; }
+  template <int Ns>
+  __device__ __forceinline__ void store_q(int e, int q, cx<T> v) const { base[at(e) + q * Ns + q * Ns / kPad] = v; }
   __device__ __forceinline__ void sync() const {
     if constexpr (WAVE) wave_sync();
     else lds_barrier();

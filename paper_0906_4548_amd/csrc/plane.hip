@@ -1,9 +1,9 @@
 // Plane kernels: axis-1 and axis-2 transforms of whole k0 planes in one launch.
 //
 // For a fixed k0 the axis-1 forward pass, the axis-2 pass with its spectral multipliers and the
-// axis-1 inverse pass touch one N x N plane only.  Where that plane fits the LDS (160 KB: float64 up
-// to 64^3 meshes, float32 up to 128^3) one workgroup does all three on it: the plane is read once
-// and each output written once (7 instead of 15 spectra of memory traffic for the relaxation's six
+// axis-1 inverse pass touch one N x N plane only.  Up to N = 64 that plane takes at most half of the
+// LDS and one workgroup does all three on it (a 128^2 float32 plane fills it: 8 fields 193 us a
+// launch against 183 for the three passes): the plane is read once and each output written once (7 instead of 15 spectra of memory traffic for the relaxation's six
 // outputs), and a pass takes one launch instead of three.  On meshes this small a launch is bound
 // by its latency chain (load, exchanges, store), so the outputs of a plane are spread over several
 // workgroups, each repeating the forward transforms, while the device is not full.
@@ -17,31 +17,36 @@ const cx<T>* twiddles(int n);   // device table exp(-2 pi i m / n), defined with
 
 template <typename T, int N>
 struct PlaneGeo {
-  // 8 elements per thread; 16 at N = 128, where 8 would take 2048 threads
-  using P = typename PlanPick<N, (N >= 128 ? 1 : 0)>::type;
+  using P = Plan8<N>;
   static constexpr int R = P::R, kT = N / R, kThreads = N * kT;
-  // element e of row r at r * kLD + e + e / R: the padding spreads a first stage's stores (R
-  // elements apart) and consecutive rows over the banks
-  static constexpr int kLD = N + N / R;
+  // element e of row r at r * kLD + e + e / kPad: the padding spreads a first stage's stores (R elements
+  // apart) over the banks and leaves the 16 consecutive columns of an access together
+  static constexpr int kPad = 16, kLD = N + (N + kPad - 1) / kPad;
   static_assert(kThreads <= 1024 && kT <= 64 && 64 % kT == 0, "a row's threads sit in one wavefront");
   static_assert(sizeof(cx<T>) * N * (kLD + 1) <= 160 * 1024, "the plane and the twiddles must fit the LDS");
-  static __device__ __forceinline__ int at(int r, int e) { return r * kLD + e + int(unsigned(e) / R); }
+  static __device__ __forceinline__ int at(int r, int e) { return r * kLD + e + int(unsigned(e) / kPad); }
 };
 
 template <typename T, int N>
 struct PlaneCol {   // exchanges of column c (any wavefronts)
+  using G = PlaneGeo<T, N>;
   cx<T>* base;
   int c;
-  __device__ __forceinline__ cx<T> load(int e) const { return base[PlaneGeo<T, N>::at(e, c)]; }
-  __device__ __forceinline__ void store(int e, cx<T> v) const { base[PlaneGeo<T, N>::at(e, c)] = v; }
+  template <int S>
+  __device__ __forceinline__ cx<T> load_q(int j, int q) const { return base[G::at(j, c) + q * S * G::kLD]; }
+  template <int Ns>
+  __device__ __forceinline__ void store_q(int e, int q, cx<T> v) const { base[G::at(e, c) + q * Ns * G::kLD] = v; }
   __device__ __forceinline__ void sync() const { lds_barrier(); }
 };
 template <typename T, int N>
 struct PlaneRow {   // exchanges of row r (inside one wavefront)
+  using G = PlaneGeo<T, N>;
   cx<T>* base;
   int r;
-  __device__ __forceinline__ cx<T> load(int e) const { return base[PlaneGeo<T, N>::at(r, e)]; }
-  __device__ __forceinline__ void store(int e, cx<T> v) const { base[PlaneGeo<T, N>::at(r, e)] = v; }
+  template <int S>
+  __device__ __forceinline__ cx<T> load_q(int j, int q) const { return base[G::at(r, j) + q * S + q * S / G::kPad]; }
+  template <int Ns>
+  __device__ __forceinline__ void store_q(int e, int q, cx<T> v) const { base[G::at(r, e) + q * Ns + q * Ns / G::kPad] = v; }
   __device__ __forceinline__ void sync() const { wave_sync(); }
 };
 
@@ -75,10 +80,10 @@ k_plane(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out,
     fft<T, N, P, -1>(v, twl, LC, t);
     lds_barrier();
 #pragma unroll
-    for (int q = 0; q < R; ++q) lds[G::at(t + q * TT, c)] = v[q];
+    for (int q = 0; q < R; ++q) lds[G::at(t, c) + q * TT * G::kLD] = v[q];
     lds_barrier();
 #pragma unroll
-    for (int q = 0; q < R; ++q) v[q] = lds[G::at(r, tr + q * TT)];
+    for (int q = 0; q < R; ++q) v[q] = lds[G::at(r, tr) + q * TT + q * TT / G::kPad];
     fft<T, N, P, -1>(v, twl, LR, tr);
   };
   cx<T> v[R];
@@ -135,10 +140,10 @@ k_plane(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out,
     fft<T, N, P, +1>(w, twl, LR, tr);
     wave_sync();
 #pragma unroll
-    for (int q = 0; q < R; ++q) lds[G::at(r, tr + q * TT)] = w[q];
+    for (int q = 0; q < R; ++q) lds[G::at(r, tr) + q * TT + q * TT / G::kPad] = w[q];
     lds_barrier();
 #pragma unroll
-    for (int q = 0; q < R; ++q) w[q] = lds[G::at(t + q * TT, c)];
+    for (int q = 0; q < R; ++q) w[q] = lds[G::at(t, c) + q * TT * G::kLD];
     fft<T, N, P, +1>(w, twl, LC, t);
     cx<T>* const dst = out + o * out_stride + off + c;
 #pragma unroll
@@ -160,18 +165,16 @@ static void plane_n(SpecMode mode, const cx<T>* in, size_t is, cx<T>* out, size_
   const cx<T>* tw = twiddles<T>(N);
 #define DGP_PLANE(M) hipLaunchKernelGGL((k_plane<T, N, M>), grid, blk, 0, s, in, is, out, os, nout, per, tw, cf, mean, ctl)
   if (mode == SPEC_HSPLIT) DGP_PLANE(SPEC_HSPLIT);
-  if constexpr (N <= 64) {   // (the source and C are formed in float64, the force mesh with the source's spectra)
-    if (mode == SPEC_FORCES) DGP_PLANE(SPEC_FORCES);
-    if constexpr (sizeof(T) == 8) {
-      if (mode == SPEC_SOURCE) DGP_PLANE(SPEC_SOURCE);
-      if (mode == SPEC_CFIELD) DGP_PLANE(SPEC_CFIELD);
-    }
+  if (mode == SPEC_FORCES) DGP_PLANE(SPEC_FORCES);
+  if constexpr (sizeof(T) == 8) {   // (the source and C are formed in float64)
+    if (mode == SPEC_SOURCE) DGP_PLANE(SPEC_SOURCE);
+    if (mode == SPEC_CFIELD) DGP_PLANE(SPEC_CFIELD);
   }
 #undef DGP_PLANE
 }
 
 template <typename T>
-bool plane_ok(int n) { return n <= (sizeof(T) == 4 ? 128 : 64); }
+bool plane_ok(int n) { return n <= 64; }
 
 template <typename T>
 void launch_plane(int n, SpecMode mode, const cx<T>* in, size_t in_stride, cx<T>* out, size_t out_stride, int nout,
@@ -180,9 +183,6 @@ void launch_plane(int n, SpecMode mode, const cx<T>* in, size_t in_stride, cx<T>
   case NN: plane_n<T, NN>(mode, in, in_stride, out, out_stride, nout, batch, cf, mean_out, ctl, s); break;
   switch (n) {
     C(8) C(16) C(32) C(64)
-    case 128:
-      if constexpr (sizeof(T) == 4) plane_n<T, 128>(mode, in, in_stride, out, out_stride, nout, batch, cf, mean_out, ctl, s);
-      break;
     default: break;
   }
 #undef C

@@ -432,6 +432,14 @@ struct LdsPair {
   int c;
   __device__ __forceinline__ cx<T> load(int e) const { return base[(e >> 1) * SP + 2 * c + (e & 1)]; }
   __device__ __forceinline__ void store(int e, cx<T> v) const { base[(e >> 1) * SP + 2 * c + (e & 1)] = v; }
+  // (S even; with Ns = 1 e is even, else Ns is)
+  template <int S>
+  __device__ __forceinline__ cx<T> load_q(int j, int q) const { return base[(j >> 1) * SP + 2 * c + (j & 1) + q * (S / 2) * SP]; }
+  template <int Ns>
+  __device__ __forceinline__ void store_q(int e, int q, cx<T> v) const {
+    if constexpr (Ns == 1) base[(e >> 1) * SP + 2 * c + (q >> 1) * SP + (q & 1)] = v;
+    else base[(e >> 1) * SP + 2 * c + (e & 1) + q * (Ns / 2) * SP] = v;
+  }
   __device__ __forceinline__ void sync() const { wave_sync(); }
 };
 
