@@ -196,7 +196,8 @@ struct dgp_plan {
   double* partial32 = nullptr;
   int groups32 = 0;
   // control
-  SolveCtl* ctl = nullptr;           // device [B]
+  SolveCtl* ctl = nullptr;           // device [2][B]: the current set and the one a deciding launch writes
+  int ctl_set = 0;                   // the current set
   SolveCtl* ctl_host = nullptr;      // pinned [B]
   double* mean_u = nullptr;          // [B]
   double* means_host = nullptr;      // pinned [B]: <u> of the returned iterates
@@ -390,7 +391,7 @@ static int plan_alloc(dgp_plan* pl) {
     pl->groups32 = relax_groups(pl->n, 4);
     TRY(dalloc(pl, &pl->partial32, B * pl->groups32 * 2));
   }
-  TRY(dalloc(pl, &pl->ctl, B));
+  TRY(dalloc(pl, &pl->ctl, 2 * B));
   TRY(halloc(pl, &pl->ctl_host, B));
   TRY(dalloc(pl, &pl->mean_u, B));
   TRY(halloc(pl, &pl->means_host, B));
@@ -578,36 +579,47 @@ static int setup_source(dgp_plan* pl, const dgp_params* p, const double* delta, 
   return DGP_OK;
 }
 
-// enqueue one relaxation pass on the iterate whose axis-0..1 spectrum is in spec_u
+static SolveCtl* ctl_now(dgp_plan* pl) { return pl->ctl + (size_t)pl->ctl_set * pl->batch; }
+static SolveCtl* ctl_other(dgp_plan* pl) { return pl->ctl + (size_t)(1 - pl->ctl_set) * pl->batch; }
+
+// enqueue one relaxation pass on the iterate whose axis-0..1 spectrum is in spec_u.  decided: the previous pass (if any) has been decided; otherwise this pass's plane launch
+// decides it (meshes of plane_ok only).  decide: decide this pass with a launch of its own.
 template <typename T>
-static int enqueue_pass(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const SolveCfg& cfg, hipStream_t s) {
+static int enqueue_pass(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const SolveCfg& cfg, bool decided, bool decide,
+                        hipStream_t s) {
   const int n = pl->n, B = pl->batch;
   const size_t fs = (size_t)B * pl->hs;
   const SpecCoef cf = spec_coef(pl, p);
   if (plane_ok<T>(n)) {
     Timed t(pl, s, tcls<T>(DGP_T_FANOUT));
-    launch_plane<T>(n, SPEC_HSPLIT, w.spec_u, fs, w.spec6, fs, 6, B, cf, pl->mean_u, pl->ctl, s);
+    if (decided) {
+      launch_plane<T>(n, SPEC_HSPLIT, w.spec_u, fs, w.spec6, fs, 6, B, cf, pl->mean_u, ctl_now(pl), s);
+    } else {
+      const PassDecision d{w.partial, w.groups, ctl_now(pl), ctl_other(pl), cfg};
+      launch_plane<T>(n, SPEC_HSPLIT, w.spec_u, fs, w.spec6, fs, 6, B, cf, pl->mean_u, ctl_now(pl), s, &d);
+      pl->ctl_set = 1 - pl->ctl_set;
+    }
   } else {
     {
       Timed t(pl, s, tcls<T>(DGP_T_AXIS1_FWD));
-      launch_p2<T>(n, w.spec_u, 1, B, -1, pl->ctl, s);
+      launch_p2<T>(n, w.spec_u, 1, B, -1, ctl_now(pl), s);
     }
     {
       Timed t(pl, s, tcls<T>(DGP_T_FANOUT));
-      launch_p3<T>(n, SPEC_HSPLIT, w.spec_u, fs, 1, w.spec6, fs, 3, B, cf, nullptr, pl->mean_u, pl->ctl, s);
+      launch_p3<T>(n, SPEC_HSPLIT, w.spec_u, fs, 1, w.spec6, fs, 3, B, cf, nullptr, pl->mean_u, ctl_now(pl), s);
     }
     {
       Timed t(pl, s, tcls<T>(DGP_T_AXIS1_INV));
-      launch_p2_split<T>(n, w.spec6, fs, B, pl->ctl, s);
+      launch_p2_split<T>(n, w.spec6, fs, B, ctl_now(pl), s);
     }
   }
   {
     TimedLaunch t(pl, tcls<T>(DGP_T_RELAX));
-    launch_relax<T>(n, w.spec6, w.U, w.S, w.spec_u, w.partial, pl->mean_u, B, cfg, pl->ctl, s, t.a, t.b);
+    launch_relax<T>(n, w.spec6, w.U, w.S, w.spec_u, w.partial, pl->mean_u, B, cfg, ctl_now(pl), s, t.a, t.b);
   }
-  {
+  if (decide) {
     Timed t(pl, s, tcls<T>(DGP_T_FINALIZE));
-    launch_finalize(w.partial, w.groups, pl->ctl, cfg, s);
+    launch_finalize(w.partial, w.groups, ctl_now(pl), ctl_other(pl), cfg, s);
   }
   LAUNCHCHK();
   return DGP_OK;
@@ -628,9 +640,13 @@ static int run_loop(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const SolveCfg&
   int chunk = std::min(first > 0 ? first : 2, cfg.max_iter + 1);
   if (cfg.fixed && cfg.tol < 0.0) chunk = cfg.max_iter + 1;   // every pass is known in advance
   for (;;) {
-    for (int i = 0; i < chunk && k <= cfg.max_iter; ++i, ++k) TRY(enqueue_pass<T>(pl, p, w, cfg, s));
+    // on the meshes of the plane kernels a pass inside the chunk is decided by the next one's launch
+    const int m = std::min(chunk, cfg.max_iter + 1 - k);
+    const bool merge = plane_ok<T>(pl->n);
+    for (int i = 0; i < m; ++i) TRY(enqueue_pass<T>(pl, p, w, cfg, !merge || i == 0, !merge || i == m - 1, s));
+    k += m;
     if (!check) return DGP_OK;
-    HIPCHK(hipMemcpyAsync(pl->ctl_host, pl->ctl, sizeof(SolveCtl) * B, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(pl->ctl_host, ctl_now(pl), sizeof(SolveCtl) * B, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     timing_flush(pl);
     int active = 0, next = cap;
@@ -670,9 +686,9 @@ static int status_rank(int st) { return st == DGP_OK ? 0 : (st == DGP_NOT_CONVER
 template <typename T>
 static int collect_enqueue(dgp_plan* pl, Ws<T>& w, double* u_state, hipStream_t s) {
   const int B = pl->batch;
-  launch_take_result<T>(pl->ctl, w.U, B, pl->n3, u_state, pl->red, pl->vec + B, s);
+  launch_take_result<T>(ctl_now(pl), w.U, B, pl->n3, u_state, pl->red, pl->vec + B, s);
   HIPCHK(hipMemcpyAsync(pl->means_host, pl->vec + B, sizeof(double) * B, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(pl->ctl_host, pl->ctl, sizeof(SolveCtl) * B, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(pl->ctl_host, ctl_now(pl), sizeof(SolveCtl) * B, hipMemcpyDeviceToHost, s));
   LAUNCHCHK();
   return DGP_OK;
 }
@@ -734,7 +750,7 @@ static int solve64(dgp_plan* pl, const dgp_params* p, const double* delta, doubl
     launch_fill_zero(w.U, (size_t)B * pl->n3, s);
   }
   launch_absmean<double>(pl->n3, w.S, B, pl->red, pl->vec, nullptr, s);
-  launch_ctl_init(pl->ctl, pl->vec, B, s);
+  launch_ctl_init(ctl_now(pl), ctl_other(pl), pl->vec, B, s);
   // a pass starts from the axis-0 spectrum of its iterate (what the fused pass writes)
   launch_p1_fwd<double>(pl->n, w.U, w.spec_u, B, nullptr, s);
   const SolveCfg cfg = solve_cfg(pl, p, p->tol, p->max_iter);
@@ -761,7 +777,7 @@ static int solve_spherical(dgp_plan* pl, const dgp_params* p, const double* delt
   const int B = pl->batch;
   TRY(setup_source(pl, p, delta, w, false, s));
   launch_absmean<double>(pl->n3, w.S, B, pl->red, pl->vec, nullptr, s);
-  launch_spherical(pl->n3, B, w.S, w.U, p->alpha, p->lambda, pl->partial, pl->ctl, pl->vec, s);
+  launch_spherical(pl->n3, B, w.S, w.U, p->alpha, p->lambda, pl->partial, ctl_now(pl), pl->vec, s);
   return collect_enqueue<double>(pl, w, u_state, s);
 }
 
@@ -812,7 +828,7 @@ int solve32_polish(dgp_plan* pl, const dgp_params* p, const double* delta, doubl
   }
   // eps = <|S|> of the float64 source; it stays in the control blocks for both phases
   launch_absmean<double>(n3, w.S, B, pl->red, pl->vec, nullptr, s);
-  launch_ctl_init(pl->ctl, pl->vec, B, s);
+  launch_ctl_init(ctl_now(pl), ctl_other(pl), pl->vec, B, s);
   launch_p1_fwd<float>(pl->n, w32.U, w32.spec_u, B, nullptr, s);
   const double switch_tol = std::max(p->tol, double(DGP_SWITCH_TOL));
   const SolveCfg cfg32 = solve_cfg(pl, p, switch_tol, p->max_iter);
@@ -823,7 +839,7 @@ int solve32_polish(dgp_plan* pl, const dgp_params* p, const double* delta, doubl
     TRY(run_loop<float>(pl, p, w32, cfg32, s, pl->hint32 + 1, false));
   else
     TRY(run_loop<float>(pl, p, w32, cfg32, s, 0, true));
-  launch_handoff(pl->ctl, w32.U, B, n3, w.U, s);
+  launch_handoff(ctl_now(pl), ctl_other(pl), w32.U, B, n3, w.U, s);
   launch_p1_fwd<double>(pl->n, w.U, w.spec_u, B, nullptr, s);
   const SolveCfg cfg = solve_cfg(pl, p, p->tol, p->max_iter);
   TRY(run_loop<double>(pl, p, w, cfg, s, pl->hint64, true));

@@ -44,7 +44,9 @@ struct SpecCoef {
   int nbins;        // power spectrum: number of bins
 };
 
-// Per-batch-element control block of the relaxation (device memory).
+// Per-batch-element control block of the relaxation (device memory).  A solve's blocks come in two sets,
+// [2][batch]: a launch that decides the previous pass while it starts the next one (launch_plane) reads
+// one set and writes the other; both sets hold the whole history.
 constexpr int kMaxHist = 256;
 constexpr int kStatusInvalid = 3;
 struct SolveCtl {
@@ -71,6 +73,8 @@ struct SolveCtl {
   double hist[kMaxHist];       // r of the iterate evaluated by pass n
   double hist_bad[kMaxHist];   // bad-point fraction of the update computed by pass n
 };
+
+constexpr size_t kCtlHeadBytes = offsetof(SolveCtl, hist);   // what changes from pass to pass, the histories apart
 
 struct SolveCfg {
   double lam, w, alpha, gamma, omega, tol;
@@ -170,9 +174,20 @@ void launch_p3(int n, SpecMode mode, const cx<T>* in, size_t in_stride, int nin,
 // whose plane fits the LDS (plane_ok); `in` as the axis-0 pass left it, output o to out + o * out_stride
 template <typename T>
 bool plane_ok(int n);
+// convergence decision of the previous pass, made by a launch_plane that starts the next one: the pass's
+// partial sums, the control blocks it ran with (prev) and those that the decision goes to (next)
+struct PassDecision {
+  const double* partial;
+  int groups;
+  SolveCtl* prev;
+  SolveCtl* next;
+  SolveCfg cfg;
+};
+// ctl: control blocks (null: no element is skipped); with a decision, its prev blocks
 template <typename T>
 void launch_plane(int n, SpecMode mode, const cx<T>* in, size_t in_stride, cx<T>* out, size_t out_stride, int nout,
-                  int batch, const SpecCoef& cf, double* mean_out, const SolveCtl* ctl, hipStream_t s);
+                  int batch, const SpecCoef& cf, double* mean_out, const SolveCtl* ctl, hipStream_t s,
+                  const PassDecision* decision = nullptr);
 int p3_row_groups(int n);   // workgroups per batch element of the float64 axis-2 pass
 // binned power spectrum of [batch] axis-0/1 spectra: sums[b][nbins] of |f|^2 (times 1/kbar^4 with
 // coef.power_c) over the modes with thr[bin] <= |n|^2 < thr[bin + 1]; partial: p3_row_groups(n) x batch x
@@ -188,15 +203,16 @@ void launch_relax(int n, const cx<T>* spec6, T* ubuf, const T* s_field, cx<T>* s
                   hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 int relax_groups(int n, int elem_bytes);   // workgroups per batch element of the fused pass
 
-void launch_finalize(const double* partial, int groups, SolveCtl* ctl, const SolveCfg& cfg, hipStream_t s);
+void launch_finalize(const double* partial, int groups, SolveCtl* ctl, SolveCtl* other, const SolveCfg& cfg,
+                     hipStream_t s);
 
 // reductions: per-batch mean of |x| and mean of x (double results)
 template <typename T>
 void launch_absmean(size_t n3, const T* x, int batch, double* scratch, double* abs_mean, double* mean,
                     hipStream_t s);
 size_t absmean_scratch_doubles(size_t n3, int batch);
-// control blocks: eps from abs_mean[b], buffer roles reset
-void launch_ctl_init(SolveCtl* ctl, const double* eps, int batch, hipStream_t s);
+// control blocks: eps from abs_mean[b], buffer roles reset (and the histories of both sets)
+void launch_ctl_init(SolveCtl* ctl, SolveCtl* other, const double* eps, int batch, hipStream_t s);
 // spherical approximation (Eqs. FullDGP2sph, SphPoi): u = the first w = 1/3 update from u = 0,
 // u = 2 S / (alpha + sqrt(alpha^2 + (8/3) lam S)) (vertex where the discriminant is negative),
 // for [batch][n3] S into u; then the control blocks record a decided one-update solve
@@ -207,7 +223,7 @@ void launch_spherical(size_t n3, int batch, const double* S, double* u, double a
 // pass that met the switch tolerance unless it met bad points, else the checked iterate;
 // the latest iterate if the phase was still running) converted into dst[B][n3], then the
 // control re-initialised for the float64 phase with the float32 counts kept
-void launch_handoff(SolveCtl* ctl, const float* U32, int batch, size_t n3, double* dst, hipStream_t s);
+void launch_handoff(SolveCtl* ctl, SolveCtl* other, const float* U32, int batch, size_t n3, double* dst, hipStream_t s);
 // the returned iterate of every element, as float64, into dst[B][n3], and its mean into
 // mean[B] (scratch: absmean_scratch_doubles(n3, batch) doubles)
 template <typename T>

@@ -7,6 +7,7 @@
 // outputs), and a pass takes one launch instead of three.  On meshes this small a launch is bound
 // by its latency chain (load, exchanges, store), so the outputs of a plane are spread over several
 // workgroups, each repeating the forward transforms, while the device is not full.
+#include "control.h"
 #include "dgp_internal.h"
 #include "spectral.h"
 
@@ -50,6 +51,60 @@ struct PlaneRow {   // exchanges of row r (inside one wavefront)
   __device__ __forceinline__ void sync() const { wave_sync(); }
 };
 
+// Decision of the previous pass at the start of a relaxation plane launch: every workgroup adds the
+// partial sums of its element (while its plane is being loaded) and so knows whether the element is
+// done; the workgroup with `write` records the decision in the next control blocks.  A launch of its
+// own for this takes 3.5 us and a gap, of a 26-31 us pass.  Returns whether the element is done.
+template <int NT>
+__device__ __forceinline__ bool decide_pass(const PassDecision& d, int b, bool write) {
+  SolveCtl& C = d.prev[b];
+  if (C.done) {
+    if (write) {
+      const auto* src = reinterpret_cast<const long long*>(&C);
+      auto* dst = reinterpret_cast<long long*>(&d.next[b]);
+      for (int i = threadIdx.x; i < int(kCtlHeadBytes / 8); i += NT) dst[i] = src[i];
+    }
+    return true;
+  }
+  constexpr int WW = NT < 64 ? NT : 64, NW = (NT + 63) / 64;
+  __shared__ double wr[NW], wb[NW];
+  double sr = 0.0, sb = 0.0;
+  const double2* p = reinterpret_cast<const double2*>(d.partial) + (size_t)b * d.groups;
+  for (int g = threadIdx.x; g < d.groups; g += NT) {
+    const double2 v = p[g];
+    sr += v.x;
+    sb += v.y;
+  }
+  sr = wave_sum<WW>(sr);
+  sb = wave_sum<WW>(sb);
+  if ((threadIdx.x & 63) == 0) {
+    wr[threadIdx.x >> 6] = sr;
+    wb[threadIdx.x >> 6] = sb;
+  }
+  lds_barrier();
+  sr = wr[0];
+  sb = wb[0];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) {
+    sr += wr[i];
+    sb += wb[i];
+  }
+  if (write && threadIdx.x == 0) {
+    SolveCtl& D = d.next[b];
+    const int n = C.iters;
+    const auto* src = reinterpret_cast<const long long*>(&C);
+    auto* dst = reinterpret_cast<long long*>(&D);
+#pragma unroll
+    for (int i = 0; i < int(kCtlHeadBytes / 8); ++i) dst[i] = src[i];
+    ctl_decide(D, sr, sb, d.cfg);
+    if (n < kMaxHist) {   // (no other workgroup reads the histories)
+      C.hist[n] = D.hist[n];
+      C.hist_bad[n] = D.hist_bad[n];
+    }
+  }
+  return ctl_decides(C, ctl_residual(C, sr, d.cfg), d.cfg);
+}
+
 // `in`: axis-0 transformed spectra [batch][N/2+1][N][N] (SPEC_FORCES: delta, then u in_stride behind it);
 // output o, inverse transformed along axes 2 and 1, to out + o * out_stride.  Workgroup
 // (g, k0, b) forms the outputs g * per .. g * per + per - 1 (below nout).
@@ -58,12 +113,21 @@ struct PlaneRow {   // exchanges of row r (inside one wavefront)
 template <typename T, int N, SpecMode MODE>
 __global__ void __launch_bounds__((PlaneGeo<T, N>::kThreads))
 k_plane(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, size_t out_stride, int nout, int per,
-        const cx<T>* __restrict__ tw, SpecCoef cf, double* __restrict__ mean_out, const SolveCtl* __restrict__ ctl) {
+        const cx<T>* __restrict__ tw, SpecCoef cf, double* __restrict__ mean_out, const SolveCtl* __restrict__ ctl,
+        PassDecision dec) {
   using G = PlaneGeo<T, N>;
   using P = typename G::P;
   constexpr int R = G::R, TT = G::kT, H = N / 2 + 1;
   const int b = blockIdx.z, k0 = blockIdx.y;
-  if (ctl != nullptr && ctl[b].done != 0) return;
+  if constexpr (MODE == SPEC_HSPLIT) {
+    if (dec.prev != nullptr) {
+      if (decide_pass<G::kThreads>(dec, b, blockIdx.x == 0 && k0 == 0)) return;
+    } else if (ctl != nullptr && ctl[b].done != 0) {
+      return;
+    }
+  } else {
+    if (ctl != nullptr && ctl[b].done != 0) return;
+  }
   int tid = threadIdx.x;
   __shared__ cx<T> lds[N * G::kLD];
   __shared__ cx<T> twl[N];   // (the first twiddled stage would wait on a cold global load)
@@ -156,14 +220,14 @@ k_plane(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out,
 // as keep at most 512 workgroups (each repeats the forward transforms).
 template <typename T, int N>
 static void plane_n(SpecMode mode, const cx<T>* in, size_t is, cx<T>* out, size_t os, int nout, int batch,
-                    const SpecCoef& cf, double* mean, const SolveCtl* ctl, hipStream_t s) {
+                    const SpecCoef& cf, double* mean, const SolveCtl* ctl, hipStream_t s, const PassDecision& dec) {
   using G = PlaneGeo<T, N>;
   constexpr int H = N / 2 + 1;
   int per = 1;
   while (per < nout && batch * H * ((nout + per - 1) / per) > 512) ++per;
   const dim3 grid((nout + per - 1) / per, H, batch), blk(G::kThreads);
   const cx<T>* tw = twiddles<T>(N);
-#define DGP_PLANE(M) hipLaunchKernelGGL((k_plane<T, N, M>), grid, blk, 0, s, in, is, out, os, nout, per, tw, cf, mean, ctl)
+#define DGP_PLANE(M) hipLaunchKernelGGL((k_plane<T, N, M>), grid, blk, 0, s, in, is, out, os, nout, per, tw, cf, mean, ctl, dec)
   if (mode == SPEC_HSPLIT) DGP_PLANE(SPEC_HSPLIT);
   if (mode == SPEC_FORCES) DGP_PLANE(SPEC_FORCES);
   if constexpr (sizeof(T) == 8) {   // (the source and C are formed in float64)
@@ -178,9 +242,11 @@ bool plane_ok(int n) { return n <= 64; }
 
 template <typename T>
 void launch_plane(int n, SpecMode mode, const cx<T>* in, size_t in_stride, cx<T>* out, size_t out_stride, int nout,
-                  int batch, const SpecCoef& cf, double* mean_out, const SolveCtl* ctl, hipStream_t s) {
+                  int batch, const SpecCoef& cf, double* mean_out, const SolveCtl* ctl, hipStream_t s,
+                  const PassDecision* decision) {
+  const PassDecision dec = decision ? *decision : PassDecision{};
 #define C(NN) \
-  case NN: plane_n<T, NN>(mode, in, in_stride, out, out_stride, nout, batch, cf, mean_out, ctl, s); break;
+  case NN: plane_n<T, NN>(mode, in, in_stride, out, out_stride, nout, batch, cf, mean_out, ctl, s, dec); break;
   switch (n) {
     C(8) C(16) C(32) C(64)
     default: break;
@@ -191,8 +257,8 @@ void launch_plane(int n, SpecMode mode, const cx<T>* in, size_t in_stride, cx<T>
 template bool plane_ok<double>(int);
 template bool plane_ok<float>(int);
 template void launch_plane<double>(int, SpecMode, const cx<double>*, size_t, cx<double>*, size_t, int, int,
-                                   const SpecCoef&, double*, const SolveCtl*, hipStream_t);
+                                   const SpecCoef&, double*, const SolveCtl*, hipStream_t, const PassDecision*);
 template void launch_plane<float>(int, SpecMode, const cx<float>*, size_t, cx<float>*, size_t, int, int,
-                                  const SpecCoef&, double*, const SolveCtl*, hipStream_t);
+                                  const SpecCoef&, double*, const SolveCtl*, hipStream_t, const PassDecision*);
 
 }  // namespace dgp

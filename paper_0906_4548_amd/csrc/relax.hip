@@ -23,6 +23,7 @@
 
 #include <hip/hip_ext.h>
 
+#include "control.h"
 #include "dgp_internal.h"
 
 namespace dgp {
@@ -100,20 +101,6 @@ struct RelaxGeo {
   static constexpr bool kRemat = N >= DGP_RELAX_REMAT_MIN;
   static constexpr bool kPark = N >= DGP_RELAX_PARK_MIN;
 };
-
-// sum over the W lanes of a wavefront segment (butterfly order, deterministic)
-template <int W>
-__device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-  for (int o = W / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, W);
-  return x;
-}
-template <int W>
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-  for (int o = W / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, W);
-  return x;
-}
 
 // Per-point residual and update in float64 (Eqs. FullDGP2, Bwpara, nabla^2Cwpara).  The + root
 // 2 B' / (alpha + sqrt(Delta)) is formed without branches: the hardware estimates of
@@ -822,11 +809,11 @@ k_relax_small(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ u
 // passes, one workgroup walking the batch: 10.6 us, now 4.3 us; one 32^3 element 4.3 -> 3.7 us).
 template <int NT>
 __global__ void __launch_bounds__(NT)
-k_finalize(const double* __restrict__ partial, int groups, SolveCtl* __restrict__ ctl, SolveCfg cfg) {
+k_finalize(const double* __restrict__ partial, int groups, SolveCtl* __restrict__ ctl, SolveCtl* __restrict__ other,
+           SolveCfg cfg) {
   __shared__ double sr[NT / 64], sb[NT / 64];
   const int b = blockIdx.x;
   if (ctl[b].done) return;
-  const double n3 = double(cfg.n) * cfg.n * cfg.n;
   double ar = 0.0, ab = 0.0;
   const double2* pb = reinterpret_cast<const double2*>(partial) + (size_t)b * groups;
   for (int g = threadIdx.x; g < groups; g += NT) {
@@ -846,60 +833,12 @@ k_finalize(const double* __restrict__ partial, int groups, SolveCtl* __restrict_
     sr[0] += sr[i];
     sb[0] += sb[i];
   }
-  SolveCtl& C = ctl[b];
-  // eps = 0 only for a uniform delta (S = 0), whose exact solution u = 0 has R = 0
-  const double r = C.eps > 0.0 ? sr[0] / (n3 * C.eps) : (sr[0] == 0.0 ? 0.0 : __builtin_huge_val());
-  const int nbad = int(sb[0]);
-  const int n = C.iters;
+  const int n = ctl[b].iters;
+  ctl_decide(ctl[b], sr[0], sb[0], cfg);
   if (n < kMaxHist) {
-    C.hist[n] = r;
-    C.hist_bad[n] = double(nbad) / n3;
+    other[b].hist[n] = ctl[b].hist[n];
+    other[b].hist_bad[n] = ctl[b].hist_bad[n];
   }
-  C.passes += 1;
-  bool done = false;
-  if (r != r) {   // a non-finite iterate (non-finite warm start, or divergence): nothing to return
-    C.status = kStatusInvalid;
-    C.result = C.cur;
-    C.resid = r;
-    done = true;
-  } else if (r <= cfg.tol) {
-    C.status = 0;
-    C.result = C.cur;
-    C.resid = r;
-    C.final_bad = nbad;   // that pass's update sits in buffer C.out
-    done = true;
-  } else if (r < C.resid_min) {
-    C.resid_min = r;
-    C.best = C.cur;
-  } else if (C.bad_seen && !cfg.fixed) {
-    C.status = 2;
-    C.result = C.best;
-    C.resid = C.resid_min;
-    done = true;
-  }
-  if (r < C.resid_min) C.resid_min = r;
-  if (!done && n + C.iters1 >= cfg.max_iter) {
-    if (cfg.fixed) {   // the requested number of updates: the last iterate
-      C.status = 0;
-      C.result = C.cur;
-      C.resid = r;
-    } else {
-      C.status = 1;
-      C.result = C.best;
-      C.resid = C.resid_min;
-    }
-    done = true;
-  }
-  if (!done) {
-    C.last_bad = nbad;
-    C.bad_frac = double(nbad) / n3;
-    if (nbad > 0) C.bad_seen = 1;
-    C.iters = n + 1;
-    const int nc = C.out;
-    C.cur = nc;
-    C.out = 3 - nc - C.best;
-  }
-  C.done = done ? 1 : 0;
 }
 
 // Per-batch mean of |x| and of x, deterministic two-level reduction.
@@ -1020,9 +959,10 @@ int relax_groups(int n, int elem_bytes) {
   return (n / (2 * tp)) * n;
 }
 
-void launch_finalize(const double* partial, int groups, SolveCtl* ctl, const SolveCfg& cfg, hipStream_t s) {
-  if (groups <= 1024) hipLaunchKernelGGL(k_finalize<256>, dim3(cfg.batch), dim3(256), 0, s, partial, groups, ctl, cfg);
-  else hipLaunchKernelGGL(k_finalize<1024>, dim3(cfg.batch), dim3(1024), 0, s, partial, groups, ctl, cfg);
+void launch_finalize(const double* partial, int groups, SolveCtl* ctl, SolveCtl* other, const SolveCfg& cfg,
+                     hipStream_t s) {
+  if (groups <= 1024) hipLaunchKernelGGL(k_finalize<256>, dim3(cfg.batch), dim3(256), 0, s, partial, groups, ctl, other, cfg);
+  else hipLaunchKernelGGL(k_finalize<1024>, dim3(cfg.batch), dim3(1024), 0, s, partial, groups, ctl, other, cfg);
 }
 
 // (one wavefront per control block: the lanes clear the histories, lane 0 continues)
@@ -1059,10 +999,11 @@ __device__ __forceinline__ void mark_invalid_input(SolveCtl& C) {
   }
 }
 
-__global__ void __launch_bounds__(64) k_ctl_init(SolveCtl* __restrict__ ctl, const double* __restrict__ eps) {
+__global__ void __launch_bounds__(64) k_ctl_init(SolveCtl* __restrict__ ctl, SolveCtl* __restrict__ other, const double* __restrict__ eps) {
   const int b = blockIdx.x;
   SolveCtl& C = ctl[b];
   ctl_reset_history(C);
+  ctl_reset_history(other[b]);
   if (threadIdx.x != 0) return;
   ctl_reset(C);
   C.eps = eps[b];
@@ -1114,9 +1055,10 @@ k_take_buffer(const SolveCtl* __restrict__ ctl, const T* __restrict__ U, int bat
 }
 
 // keeps eps (the float64 source's) and records the float32 phase's counts
-__global__ void __launch_bounds__(64) k_ctl_phase2(SolveCtl* __restrict__ ctl) {
+__global__ void __launch_bounds__(64) k_ctl_phase2(SolveCtl* __restrict__ ctl, SolveCtl* __restrict__ other) {
   SolveCtl& C = ctl[blockIdx.x];
   ctl_reset_history(C);
+  ctl_reset_history(other[blockIdx.x]);
   if (threadIdx.x != 0) return;
   const int src = handoff_buffer(C);
   const bool invalid = C.status == kStatusInvalid;
@@ -1140,10 +1082,10 @@ static unsigned copy_groups(size_t n3) {
   return unsigned(g > 4096 ? 4096 : g);
 }
 
-void launch_handoff(SolveCtl* ctl, const float* U32, int batch, size_t n3, double* dst, hipStream_t s) {
+void launch_handoff(SolveCtl* ctl, SolveCtl* other, const float* U32, int batch, size_t n3, double* dst, hipStream_t s) {
   hipLaunchKernelGGL((k_take_buffer<float>), dim3(copy_groups(n3), batch), dim3(256), 0, s, ctl, U32, batch, n3, dst,
                      1, nullptr);
-  hipLaunchKernelGGL(k_ctl_phase2, dim3(batch), dim3(64), 0, s, ctl);
+  hipLaunchKernelGGL(k_ctl_phase2, dim3(batch), dim3(64), 0, s, ctl, other);
 }
 
 // ------------------------------------------------------------------ spherical approximation
@@ -1223,8 +1165,8 @@ template void launch_take_result<double>(const SolveCtl*, const double*, int, si
 template void launch_take_result<float>(const SolveCtl*, const float*, int, size_t, double*, double*, double*,
                                         hipStream_t);
 
-void launch_ctl_init(SolveCtl* ctl, const double* eps, int batch, hipStream_t s) {
-  hipLaunchKernelGGL(k_ctl_init, dim3(batch), dim3(64), 0, s, ctl, eps);
+void launch_ctl_init(SolveCtl* ctl, SolveCtl* other, const double* eps, int batch, hipStream_t s) {
+  hipLaunchKernelGGL(k_ctl_init, dim3(batch), dim3(64), 0, s, ctl, other, eps);
 }
 
 
