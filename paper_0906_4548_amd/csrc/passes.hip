@@ -329,18 +329,25 @@ k_p2_adj_split(cx<double>* __restrict__ data, size_t fstride, int batch, double 
   const T n0 = T(k0);
   const bool q0 = k0 == N / 2;
   LdsCol<T, TY> L{lds, c};
-  cx<T> acc[R];
+  cx<T> acc[R], nx[R];   // nx: the next input's tile, one transform ahead
 #pragma unroll
-  for (int q = 0; q < R; ++q) acc[q] = mk(T(0), T(0));
+  for (int q = 0; q < R; ++q) {
+    acc[q] = mk(T(0), T(0));
+    nx[q] = data[slot * fstride + off + (size_t)(t + q * TT) * N];
+  }
 #pragma unroll 1
   for (int i = 0; i < 3 - role; ++i) {
     const cx<T>* twq = tw;
     asm volatile("" : "+s"(twq), "+v"(t));
     const int f = slot + i;
-    const cx<T>* src = data + f * fstride + off;
     cx<T> v[R];
 #pragma unroll
-    for (int q = 0; q < R; ++q) v[q] = src[(size_t)(t + q * TT) * N];
+    for (int q = 0; q < R; ++q) v[q] = nx[q];
+    if (i < 2 - role) {
+      const cx<T>* src = data + (f + 1) * fstride + off;
+#pragma unroll
+      for (int q = 0; q < R; ++q) nx[q] = src[(size_t)(t + q * TT) * N];
+    }
     fft<T, N, P, -1>(v, twq, L, t);
 #pragma unroll
     for (int q = 0; q < R; ++q) {
@@ -413,7 +420,7 @@ k_p2_force_split(cx<T>* __restrict__ data, size_t fstride, int batch, int with_p
 template <typename T, int N, SpecMode MODE>
 __global__ void __launch_bounds__((Geo<T, N>::kP3))
 k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, size_t out_stride,
-     const cx<T>* __restrict__ tw, SpecCoef cf, const double* __restrict__ bin_coef,
+     const cx<T>* __restrict__ twg, SpecCoef cf, const double* __restrict__ bin_coef,
      double* __restrict__ mean_out, const SolveCtl* __restrict__ ctl) {
   using P = typename Geo<T, N>::P3;
   constexpr int R = P::R;
@@ -428,6 +435,13 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
   const int rr = valid ? row : 0;
   const int k0 = rr / N, k1 = rr % N;
   __shared__ cx<T> lds[RW * LdsRow<T, N>::kStride];
+  // twiddles: float32 from LDS (256^3 split pass 54 vs 46 us), float64 from the table into registers,
+  // whose LDS exchanges bound the pass already (91 vs 97 us with the LDS copy)
+  constexpr bool TWLDS = sizeof(T) == 4;
+  __shared__ cx<T> twl[TWLDS ? N : 1];
+  if constexpr (TWLDS)
+    for (int i = threadIdx.x; i < N; i += G::kThreads) twl[i] = twg[i];   // ordered by load_row's barrier
+  const cx<T>* tw = TWLDS ? twl : twg;
   // a row's N/R threads are consecutive lanes; when they fit in one wavefront its exchanges are wave-local
   LdsRow<T, N, (TT <= 64 && 64 % TT == 0 && DGP_P3_WAVE_SYNC)> L{lds, c};
   const size_t roff = (size_t)b * ROWS * N + (size_t)rr * N;
@@ -436,6 +450,7 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
   auto load_row = [&](const cx<T>* src) {
 #pragma unroll
     for (int q = 0; q < R; ++q) v[q] = valid ? src[roff + t + q * TT] : mk(T(0), T(0));
+    if constexpr (TWLDS) lds_barrier();
   };
   auto store_row = [&](cx<T>* dst, cx<T> (&w)[R]) {
     if (valid) {
@@ -460,25 +475,27 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
     // the three group sums of k_p2_adj_split (slots 0, 3, 5: the axis-1 and axis-0 factors and
     // the 2 lam weights applied) times the rest of each multiplier: 1/|n|^2, n2/|n|^2 (0 at the
     // Nyquist index of axis 2) and gamma/kbar
-    cx<T> acc[R];
+    cx<T> acc[R], nx[R];   // nx: the next group's row, one transform ahead
 #pragma unroll
     for (int q = 0; q < R; ++q) acc[q] = mk(T(0), T(0));
+    load_row(in);
 #pragma unroll 1
     for (int g = 0; g < 3; ++g) {
-      load_row(in + (g == 0 ? 0 : g == 1 ? 3 : 5) * in_stride);
+      if (g < 2) {
+        const cx<T>* src = in + (g == 0 ? 3 : 5) * in_stride;
+#pragma unroll
+        for (int q = 0; q < R; ++q) nx[q] = valid ? src[roff + t + q * TT] : mk(T(0), T(0));
+      }
       fft<T, N, P, -1>(v, tw, L, t);
 #pragma unroll
       for (int q = 0; q < R; ++q) {
         const Mode3 m = mode_of(N, k0, k1, t + q * TT);
-        if (m.msq == 0) continue;
-        const double ik2 = 1.0 / double(m.msq);
-        double mult;
-        if (g == 0) mult = ik2;
-        else if (g == 1) mult = m.q2 ? 0.0 : double(m.n2) * ik2;
-        else mult = cf.gamma / (cf.kappa * kf * sqrt(double(m.msq)));
-        const T mm = T(mult * cf.inv_n3);
+        const T mm = g == 2 ? T(-cf.gamma) * nonlocal_mult<T>(cf, m)
+                            : inv_square<T>(cf, m) * (g == 0 ? T(1) : m.q2 ? T(0) : T(m.n2));
         acc[q] = acc[q] + scale(v[q], mm);
       }
+#pragma unroll
+      for (int q = 0; q < R; ++q) v[q] = nx[q];
     }
     fft<T, N, P, +1>(acc, tw, L, t);
     store_row(out, acc);
