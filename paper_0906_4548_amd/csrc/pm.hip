@@ -85,8 +85,6 @@ struct DepGeo {
   static constexpr int kCap = (kRecompute ? 3 : 4) * CH;    // cells of the LDS histogram (8 bytes each)
   static_assert(CH % 256 == 0, "chunk must be a multiple of the workgroup size");
 };
-// the interpolation adjoint's scatter (up to three components per cell in LDS) keeps its own
-constexpr int kIgChunk = 512, kIgPPT = kIgChunk / 256, kIgCap = 2048;
 
 // offset of cell i from the reference cell r on a periodic axis of n cells, in [-n/2, n/2)
 __device__ __forceinline__ int periodic_offset(int i, int r, int n) {
@@ -809,64 +807,71 @@ k_interp_scale(const ulonglong2* __restrict__ part, int blocks, unsigned long lo
   st[2] = (unsigned long long)(long long)e;
 }
 
-template <typename P, int NC>
+// Bound by the global atomics of the flush (one per touched box cell and component), the conversions and
+// the LDS atomics together.  A chunk of 1024 particles with one component after another in a 24 KB
+// histogram takes fewer of the first than one of 512 with all components at once (2.1M particles in
+// 8^3 blocks, three components, 128^3: 113 -> 98 us; 2048 particles 104 us); 512 below 2^18 particles,
+// where 1024 would leave the device idle.
+template <typename P, int CH, int NC>
 __global__ void __launch_bounds__(256)
 k_interp_grad_mesh_bin(const P* __restrict__ pos, long long np, int n, double scale, const double* __restrict__ g,
                        const unsigned long long* __restrict__ st, unsigned long long* __restrict__ acc) {
 #pragma clang fp contract(off)
-  __shared__ unsigned long long hist[NC * kIgCap];
+  constexpr int PPT = CH / 256, CAP = 3 * CH;
+  __shared__ unsigned long long hist[CAP];
   const size_t n3 = (size_t)n * n * n;
   const int e = (int)(long long)st[2];
-  const long long p0 = xcd_chunk() * kIgChunk;
-  P xs[kIgPPT][3];
-  load_chunk<kIgPPT>(pos, np, p0, xs);
-  Cic cr, cs[kIgPPT];
-  int off[kIgPPT][3], bx[6];
-  const bool binned = chunk_box<kIgPPT>(pos, xs, np, n, scale, p0, kIgCap, cr, cs, off, bx);
+  const long long p0 = xcd_chunk() * CH;
+  P xs[PPT][3];
+  load_chunk<PPT>(pos, np, p0, xs);
+  Cic cr, cs[PPT];
+  int off[PPT][3], bx[6];
+  const bool binned = chunk_box<PPT>(pos, xs, np, n, scale, p0, CAP, cr, cs, off, bx);
   const int vol = bx[3] * bx[4] * bx[5];
-  if (binned)
-    for (int i = threadIdx.x; i < vol; i += 256)
+#pragma unroll 1
+  for (int m = 0; m < NC; ++m) {
+    const double* const gm = g + (size_t)m * np;
+    unsigned long long* const am = acc + (size_t)m * n3;
+    if (binned)
+      for (int i = threadIdx.x; i < vol; i += 256) hist[i] = 0ull;
+    lds_barrier();
 #pragma unroll
-      for (int m = 0; m < NC; ++m) hist[m * kIgCap + i] = 0ull;
-  lds_barrier();
+    for (int k = 0; k < PPT; ++k) {
+      const long long p = p0 + threadIdx.x + k * 256;
+      if (p >= np) continue;
+      const double gk = gm[p];
+      // the cell and weights again from the position (the chunk box's arithmetic), opaque so that they
+      // are not held across the components
+      P x[3] = {xs[k][0], xs[k][1], xs[k][2]};
 #pragma unroll
-  for (int k = 0; k < kIgPPT; ++k) {
-    const long long p = p0 + threadIdx.x + k * 256;
-    if (p >= np) continue;
-    const Cic& c = cs[k];
-    double gm[NC];
+      for (int d = 0; d < 3; ++d) asm volatile("" : "+v"(x[d]));
+      const double s3[3] = {double(x[0]) * scale, double(x[1]) * scale, double(x[2]) * scale};
+      const Cic c = cic_at(s3, n);
+      const int ox = periodic_offset(c.i0[0], cr.i0[0], n) - bx[0], oy = periodic_offset(c.i0[1], cr.i0[1], n) - bx[1],
+                oz = periodic_offset(c.i0[2], cr.i0[2], n) - bx[2];
 #pragma unroll
-    for (int m = 0; m < NC; ++m) gm[m] = g[(size_t)m * np + p];
+      for (int a = 0; a < 2; ++a) {
+        const double wx = a ? c.w1[0] : c.w0[0];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      const double wx = a ? c.w1[0] : c.w0[0];
+        for (int b = 0; b < 2; ++b) {
+          const double wxy = wx * (b ? c.w1[1] : c.w0[1]);
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const double wxy = wx * (b ? c.w1[1] : c.w0[1]);
-#pragma unroll
-        for (int cc = 0; cc < 2; ++cc) {
-          const double wgt = wxy * (cc ? c.w1[2] : c.w0[2]);
-          const int li = ((off[k][0] + a - bx[0]) * bx[4] + (off[k][1] + b - bx[1])) * bx[5] + (off[k][2] + cc - bx[2]);
-          const size_t gi = corner_index(c, a, b, cc, n);
-#pragma unroll
-          for (int m = 0; m < NC; ++m) {
-            const unsigned long long q = (unsigned long long)(long long)rint(ldexp(gm[m] * wgt, e));
-            if (binned) atomicAdd(&hist[m * kIgCap + li], q);
-            else atomicAdd(&acc[(size_t)m * n3 + gi], q);
+          for (int cc = 0; cc < 2; ++cc) {
+            const double wgt = wxy * (cc ? c.w1[2] : c.w0[2]);
+            const unsigned long long q = (unsigned long long)(long long)rint(ldexp(gk * wgt, e));
+            if (binned) atomicAdd(&hist[((ox + a) * bx[4] + (oy + b)) * bx[5] + (oz + cc)], q);
+            else atomicAdd(&am[corner_index(c, a, b, cc, n)], q);
           }
         }
       }
     }
-  }
-  if (!binned) return;
-  lds_barrier();
-  for (int i = threadIdx.x; i < vol; i += 256) {
-    const size_t gi = box_cell(i, cr, bx, n);
-#pragma unroll
-    for (int m = 0; m < NC; ++m) {
-      const unsigned long long v = hist[m * kIgCap + i];
-      if (v != 0ull) atomicAdd(&acc[(size_t)m * n3 + gi], v);
+    if (!binned) continue;
+    lds_barrier();
+    for (int i = threadIdx.x; i < vol; i += 256) {
+      const unsigned long long v = hist[i];
+      if (v != 0ull) atomicAdd(&am[box_cell(i, cr, bx, n)], v);
     }
+    lds_barrier();   // before the next component clears the histogram
   }
 }
 
@@ -1057,8 +1062,12 @@ static void interp_bwd_t(int n, double box, const double* mesh, const P* pos, lo
   hipLaunchKernelGGL(k_max_abs_and_mass, dim3(blocks), dim3(256), 0, s, g, (size_t)NC * np, grid, n3,
                      reinterpret_cast<ulonglong2*>(red), bad);
   hipLaunchKernelGGL(k_interp_scale, dim3(1), dim3(64), 0, s, reinterpret_cast<const ulonglong2*>(red), blocks, st);
-  const unsigned gch = unsigned((np + kIgChunk - 1) / kIgChunk);
-  hipLaunchKernelGGL((k_interp_grad_mesh_bin<P, NC>), dim3(gch), dim3(256), 0, s, pos, np, n, scale, g, st, acc);
+  if (np >= (1ll << 18))
+    hipLaunchKernelGGL((k_interp_grad_mesh_bin<P, 1024, NC>), dim3(unsigned((np + 1023) / 1024)), dim3(256), 0, s, pos, np,
+                       n, scale, g, st, acc);
+  else
+    hipLaunchKernelGGL((k_interp_grad_mesh_bin<P, 512, NC>), dim3(unsigned((np + 511) / 512)), dim3(256), 0, s, pos, np, n,
+                       scale, g, st, acc);
   hipLaunchKernelGGL(k_fixed_to_double, dim3(grid_strided(NC * n3)), dim3(256), 0, s, acc, NC * n3, st, bad);
 }
 

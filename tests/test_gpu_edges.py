@@ -75,3 +75,19 @@ def test_deposit_tile_sort_bit_exact(dgp):
             for _ in range(2):   # the second pass over a workspace that the first one used
                 plan.deposit(to_dev(pos, torch.float32 if pos.dtype == np.float32 else torch.float64), g)
             assert np.array_equal(g.cpu().numpy().reshape(n, n, n), ref), name
+
+
+# both sides of the chunk rule (2^18 particles), ragged, compact and spread chunks
+@pytest.mark.parametrize("np_,block,nc", [(2 ** 18 - 1, 8, 3), (2 ** 18 + 13, 8, 3), (2 ** 18 + 13, 0, 2), (300, 0, 1)])
+def test_interp_mesh_gradient_chunks(dgp, np_, block, nc):
+    from oracle import adjoint
+    n, box = 32, 64.0
+    side = 72
+    pos = inputs.zeldovich_load(side, box, 12, rms_disp=0.8, block=block)[0][:, :np_].copy()
+    g = np.random.default_rng(np_).standard_normal((nc, np_))
+    mesh = np.random.default_rng(3).standard_normal((nc, n, n, n))
+    _, ref = adjoint.interp_backward(mesh, pos, g, box)
+    with dgp.Plan(n, box) as plan:
+        gm = torch.zeros((nc, n, n, n), dtype=torch.float64, device="cuda")
+        plan.interp_backward(None, to_dev(pos), to_dev(g), None, gm)
+    assert rel_l2(gm.cpu().numpy(), ref) <= 1e-12
