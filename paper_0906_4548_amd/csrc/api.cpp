@@ -185,7 +185,7 @@ struct dgp_plan {
   double* U = nullptr;               // [3][B][n3]
   double* S = nullptr;               // [B][n3]
   cx<double>* spec_u = nullptr;      // [B][hs]
-  cx<double>* spec6 = nullptr;       // [8][B][hs]; fields 6, 7: axis-0/1 spectra of delta (kept) and u
+  cx<double>* spec6 = nullptr;       // [9][B][hs]; fields 6, 7: axis-0/1 spectra of delta (kept) and u; 8: spec_u
   double* partial = nullptr;         // [B][groups][2]
   int groups64 = 0;
   // float32 solve workspace (precision form)
@@ -206,7 +206,6 @@ struct dgp_plan {
   double* red = nullptr;             // reduction scratch
   // PM (batch 1)
   long long* grid = nullptr;         // [n3]
-  double* delta = nullptr;           // [n3]
   double* mesh3 = nullptr;           // [3][n3] force mesh (float64 plans)
   float* mesh3_32 = nullptr;         // [3][n3] force mesh (precision-form plans)
   // power spectrum
@@ -379,8 +378,10 @@ static int plan_alloc(dgp_plan* pl) {
   const size_t B = pl->batch, n3 = pl->n3, hs = pl->hs;
   TRY(dalloc(pl, &pl->U, 3 * B * n3));
   TRY(dalloc(pl, &pl->S, B * n3));
-  TRY(dalloc(pl, &pl->spec_u, B * hs));
-  TRY(dalloc(pl, &pl->spec6, 8 * B * hs));   // 6 pass spectra + the delta and u spectra of the PM step
+  // 6 pass spectra, the delta and u spectra of the PM step, and the iterate's spectrum (the set-up writes
+  // the spectra of S and of the linear solution side by side into the last two)
+  TRY(dalloc(pl, &pl->spec6, 9 * B * hs));
+  pl->spec_u = pl->dry ? nullptr : pl->spec6 + 8 * B * hs;
   pl->groups64 = relax_groups(pl->n, 8);
   TRY(dalloc(pl, &pl->partial, B * pl->groups64 * 2));
   if (pl->precision == DGP_FP32) {
@@ -396,10 +397,9 @@ static int plan_alloc(dgp_plan* pl) {
   TRY(dalloc(pl, &pl->mean_u, B));
   TRY(halloc(pl, &pl->means_host, B));
   TRY(dalloc(pl, &pl->vec, 4 * B));
-  TRY(dalloc(pl, &pl->red, absmean_scratch_doubles(n3, (int)B) + 16));
+  TRY(dalloc(pl, &pl->red, std::max(absmean_scratch_doubles(n3, (int)B), B * p1_groups(pl->n)) + 16));
   if (B == 1) {
     TRY(dalloc(pl, &pl->grid, n3));
-    TRY(dalloc(pl, &pl->delta, n3));
     if (pl->precision == DGP_FP32)
       TRY(dalloc(pl, &pl->mesh3_32, 3 * n3));
     else
@@ -509,6 +509,7 @@ static SpecCoef spec_coef(const dgp_plan* pl, const dgp_params* p) {
   c.inv_eta_nl = nl ? 1.0 / p->eta : 0.0;
   c.force_scale = kCOverH0 * kCOverH0;
   c.inv_n3 = 1.0 / double(pl->n3);
+  c.inv_n2 = 1.0 / (double(pl->n) * pl->n);
   c.lam2 = 2.0 * p->lambda;
   c.nl_scale = c.inv_n3 / (c.kappa * c.kf);
   c.force_mode = p->force_mode;
@@ -555,26 +556,46 @@ struct Ws {
 static Ws<double> ws64(dgp_plan* pl) { return {pl->U, pl->S, pl->spec_u, pl->spec6, pl->partial, pl->groups64}; }
 static Ws<float> ws32(dgp_plan* pl) { return {pl->U32, pl->S32, pl->spec_u32, pl->spec6_32, pl->partial32, pl->groups32}; }
 
+// A density contrast: a float64 field, or (a step's) fixed-point deposit counts and their scale, whose
+// contrast the first transform forms on load (the field itself is not written: at 512^3, 2 GB of traffic)
+struct Contrast {
+  const double* field;
+  const long long* counts;
+  double scale;
+  const int* bad;
+};
+
+static void fwd_axis0(int n, const Contrast& d, cx<double>* out, int batch, hipStream_t s) {
+  if (d.counts) launch_p1_fwd_counts(n, d.counts, d.scale, d.bad, out, s);
+  else launch_p1_fwd<double>(n, d.field, out, batch, nullptr, s);
+}
+static void fwd_axis0(int n, const Contrast& d, cx<float>* out, int batch, hipStream_t s) {
+  if (d.counts) launch_p1_fwd_counts(n, d.counts, d.scale, d.bad, out, s);
+  else launch_p1_fwd_from64(n, d.field, out, batch, nullptr, s);
+}
+
 // S and the linear guess from delta (float64; S32 / U32 receive their float32 roundings when
-// given).  The axis-0/1 spectrum of delta (axis-0 where the plane kernels serve the mesh) stays in
-// spectral field 6, where the PM step's force computation picks it up.
-static int setup_source(dgp_plan* pl, const dgp_params* p, const double* delta, Ws<double>& w, bool want_linear,
+// given), and the partial sums of |S| (pl->red).  The axis-0/1 spectrum of delta (axis-0 where the
+// plane kernels serve the mesh) stays in spectral field 6, where the PM step's force computation picks
+// it up, and the linear guess's axis-0 spectrum in field 8, spec_u, where a float64 solve's first pass
+// starts from it (transforming the guess again: 68 us at 256^3).
+static int setup_source(dgp_plan* pl, const dgp_params* p, const Contrast& delta, Ws<double>& w, bool want_linear,
                         hipStream_t s, float* S32 = nullptr, float* U32 = nullptr) {
   const int n = pl->n, B = pl->batch;
   const size_t fs = (size_t)B * pl->hs;
   const SpecCoef cf = spec_coef(pl, p);
   Timed tm(pl, s, DGP_T_SETUP);
-  cx<double>* dspec = w.spec6 + 6 * fs;
+  cx<double>*const dspec = w.spec6 + 6 * fs, *const sspec = w.spec6 + 7 * fs;
+  fwd_axis0(n, delta, dspec, B, s);
   if (plane_ok<double>(n)) {
-    launch_p1_fwd<double>(n, delta, dspec, B, nullptr, s);
-    launch_plane<double>(n, SPEC_SOURCE, dspec, fs, w.spec6, fs, want_linear ? 2 : 1, B, cf, nullptr, nullptr, s);
+    launch_plane<double>(n, SPEC_SOURCE, dspec, fs, sspec, fs, want_linear ? 2 : 1, B, cf, nullptr, nullptr, s);
   } else {
-    TRY(fwd3<double>(pl, delta, dspec, B, nullptr, s));
-    launch_p3<double>(n, SPEC_SOURCE, dspec, fs, 1, w.spec6, fs, 2, B, cf, nullptr, nullptr, nullptr, s);
-    launch_p2<double>(n, w.spec6, 2, B, +1, nullptr, s);
+    launch_p2<double>(n, dspec, 1, B, -1, nullptr, s);
+    launch_p3<double>(n, SPEC_SOURCE, dspec, fs, 1, sspec, fs, 2, B, cf, nullptr, nullptr, nullptr, s);
+    launch_p2<double>(n, sspec, want_linear ? 2 : 1, B, +1, nullptr, s);
   }
-  launch_p1_inv<double>(n, w.spec6, w.S, B, nullptr, s, S32);
-  if (want_linear) launch_p1_inv<double>(n, w.spec6 + fs, w.U, B, nullptr, s, U32);
+  launch_p1_inv<double>(n, sspec, w.S, B, nullptr, s, S32, 1.0, pl->red);
+  if (want_linear) launch_p1_inv<double>(n, w.spec_u, w.U, B, nullptr, s, U32, 1.0 / n);
   LAUNCHCHK();
   return DGP_OK;
 }
@@ -582,8 +603,8 @@ static int setup_source(dgp_plan* pl, const dgp_params* p, const double* delta, 
 static SolveCtl* ctl_now(dgp_plan* pl) { return pl->ctl + (size_t)pl->ctl_set * pl->batch; }
 static SolveCtl* ctl_other(dgp_plan* pl) { return pl->ctl + (size_t)(1 - pl->ctl_set) * pl->batch; }
 
-// enqueue one relaxation pass on the iterate whose axis-0..1 spectrum is in spec_u.  decided: the previous pass (if any) has been decided; otherwise this pass's plane launch
-// decides it (meshes of plane_ok only).  decide: decide this pass with a launch of its own.
+// enqueue one relaxation pass on the iterate whose axis-0 spectrum is in spec_u.  decided: the previous
+// pass (if any) has been decided; otherwise this pass's plane launch decides it (meshes of plane_ok only).  decide: decide this pass with a launch of its own.
 template <typename T>
 static int enqueue_pass(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const SolveCfg& cfg, bool decided, bool decide,
                         hipStream_t s) {
@@ -681,14 +702,14 @@ static int max_passes(const dgp_plan* pl) {
 static int status_rank(int st) { return st == DGP_OK ? 0 : (st == DGP_NOT_CONVERGED ? 2 : 1); }
 
 // Enqueue the copy of the decided iterates into u_state (the device picks each
-// element's buffer), their means, and the copies of the control blocks and means to
-// pinned host memory.  collect_finish reads them once the stream has been synchronised.
+// element's buffer), their means, and the copy of the means to pinned host memory (the control
+// blocks are there from the solve's last look at them).  collect_finish reads them once the stream
+// has been synchronised.
 template <typename T>
 static int collect_enqueue(dgp_plan* pl, Ws<T>& w, double* u_state, hipStream_t s) {
   const int B = pl->batch;
   launch_take_result<T>(ctl_now(pl), w.U, B, pl->n3, u_state, pl->red, pl->vec + B, s);
   HIPCHK(hipMemcpyAsync(pl->means_host, pl->vec + B, sizeof(double) * B, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(pl->ctl_host, ctl_now(pl), sizeof(SolveCtl) * B, hipMemcpyDeviceToHost, s));
   LAUNCHCHK();
   return DGP_OK;
 }
@@ -740,7 +761,7 @@ static int c_field(dgp_plan* pl, const dgp_params* p, const double* u, double* c
 }
 
 // plain float64 solve from the chosen initial iterate
-static int solve64(dgp_plan* pl, const dgp_params* p, const double* delta, double* u_state, hipStream_t s) {
+static int solve64(dgp_plan* pl, const dgp_params* p, const Contrast& delta, double* u_state, hipStream_t s) {
   Ws<double> w = ws64(pl);
   const int B = pl->batch;
   TRY(setup_source(pl, p, delta, w, p->init == DGP_INIT_LINEAR, s));
@@ -749,22 +770,22 @@ static int solve64(dgp_plan* pl, const dgp_params* p, const double* delta, doubl
   } else if (p->init == DGP_INIT_ZERO) {
     launch_fill_zero(w.U, (size_t)B * pl->n3, s);
   }
-  launch_absmean<double>(pl->n3, w.S, B, pl->red, pl->vec, nullptr, s);
-  launch_ctl_init(ctl_now(pl), ctl_other(pl), pl->vec, B, s);
-  // a pass starts from the axis-0 spectrum of its iterate (what the fused pass writes)
-  launch_p1_fwd<double>(pl->n, w.U, w.spec_u, B, nullptr, s);
+  launch_ctl_init(ctl_now(pl), ctl_other(pl), pl->red, p1_groups(pl->n), pl->n3, B, s);
+  // a pass starts from the axis-0 spectrum of its iterate (what the fused pass writes); the linear
+  // guess's is there already
+  if (p->init != DGP_INIT_LINEAR) launch_p1_fwd<double>(pl->n, w.U, w.spec_u, B, nullptr, s);
   const SolveCfg cfg = solve_cfg(pl, p, p->tol, p->max_iter);
   TRY(run_loop<double>(pl, p, w, cfg, s, pl->hint64, true));
   pl->hint64 = max_passes(pl);
   return collect_enqueue<double>(pl, w, u_state, s);
 }
 
-int solve32_polish(dgp_plan* pl, const dgp_params* p, const double* delta, double* u_state, hipStream_t s);
+int solve32_polish(dgp_plan* pl, const dgp_params* p, const Contrast& delta, double* u_state, hipStream_t s);
 
 // Enqueue a solve in the plan's form; ends with collect_enqueue (no final synchronisation).
-static int solve_spherical(dgp_plan* pl, const dgp_params* p, const double* delta, double* u_state, hipStream_t s);
+static int solve_spherical(dgp_plan* pl, const dgp_params* p, const Contrast& delta, double* u_state, hipStream_t s);
 
-static int solve_enqueue(dgp_plan* pl, const dgp_params* p, const double* delta, double* u_state, hipStream_t s) {
+static int solve_enqueue(dgp_plan* pl, const dgp_params* p, const Contrast& delta, double* u_state, hipStream_t s) {
   if (p->spherical) return solve_spherical(pl, p, delta, u_state, s);
   return pl->precision == DGP_FP32 ? solve32_polish(pl, p, delta, u_state, s) : solve64(pl, p, delta, u_state, s);
 }
@@ -772,12 +793,12 @@ static int solve_enqueue(dgp_plan* pl, const dgp_params* p, const double* delta,
 // Spherical approximation (Eqs. FullDGP2sph, SphPoi): the source in float64, then the first
 // w = 1/3 update from u = 0, which at u = 0 is a pointwise function of S (the nonlocal linear
 // terms enter through S, as in the paper's spherical runs).
-static int solve_spherical(dgp_plan* pl, const dgp_params* p, const double* delta, double* u_state, hipStream_t s) {
+static int solve_spherical(dgp_plan* pl, const dgp_params* p, const Contrast& delta, double* u_state, hipStream_t s) {
   Ws<double> w = ws64(pl);
   const int B = pl->batch;
   TRY(setup_source(pl, p, delta, w, false, s));
-  launch_absmean<double>(pl->n3, w.S, B, pl->red, pl->vec, nullptr, s);
-  launch_spherical(pl->n3, B, w.S, w.U, p->alpha, p->lambda, pl->partial, ctl_now(pl), pl->vec, s);
+  launch_spherical(pl->n3, B, w.S, w.U, p->alpha, p->lambda, pl->partial, ctl_now(pl), pl->red, p1_groups(pl->n), s);
+  HIPCHK(hipMemcpyAsync(pl->ctl_host, ctl_now(pl), sizeof(SolveCtl) * B, hipMemcpyDeviceToHost, s));
   return collect_enqueue<double>(pl, w, u_state, s);
 }
 
@@ -788,7 +809,7 @@ extern "C" int dgp_solve_field(dgp_plan* pl, const dgp_params* p, const double* 
   if (!delta || !u_state) return fail(DGP_E_INVALID, "delta and u_state are required");
   hipStream_t s = static_cast<hipStream_t>(stream);
   HIPCHK(hipEventRecord(pl->ev0, s));
-  TRY(solve_enqueue(pl, p, delta, u_state, s));
+  TRY(solve_enqueue(pl, p, Contrast{delta, nullptr, 0.0, nullptr}, u_state, s));
   if (c_out) TRY(c_field(pl, p, u_state, c_out, s));
   HIPCHK(hipEventRecord(pl->ev1, s));
   HIPCHK(hipEventSynchronize(pl->ev1));
@@ -809,7 +830,7 @@ extern "C" int dgp_solve_field(dgp_plan* pl, const dgp_params* p, const double* 
 // continues with float64 passes, from the update that the last float32 pass
 // computed, until the float64 residual meets tol.  The returned residual is always
 // a float64 evaluation.
-int solve32_polish(dgp_plan* pl, const dgp_params* p, const double* delta, double* u_state, hipStream_t s) {
+int solve32_polish(dgp_plan* pl, const dgp_params* p, const Contrast& delta, double* u_state, hipStream_t s) {
   const int B = pl->batch;
   const size_t n3 = pl->n3;
   Ws<float> w32 = ws32(pl);
@@ -827,8 +848,7 @@ int solve32_polish(dgp_plan* pl, const dgp_params* p, const double* delta, doubl
     launch_fill_zero(w32.U, (size_t)B * n3 / 2, s);   // n3 is even
   }
   // eps = <|S|> of the float64 source; it stays in the control blocks for both phases
-  launch_absmean<double>(n3, w.S, B, pl->red, pl->vec, nullptr, s);
-  launch_ctl_init(ctl_now(pl), ctl_other(pl), pl->vec, B, s);
+  launch_ctl_init(ctl_now(pl), ctl_other(pl), pl->red, p1_groups(pl->n), n3, B, s);
   launch_p1_fwd<float>(pl->n, w32.U, w32.spec_u, B, nullptr, s);
   const double switch_tol = std::max(p->tol, double(DGP_SWITCH_TOL));
   const SolveCfg cfg32 = solve_cfg(pl, p, switch_tol, p->max_iter);
@@ -867,16 +887,13 @@ static size_t spec6_bytes(const dgp_plan* pl) { return 8 * (size_t)pl->batch * p
 // (a non-finite position raises the plan's flag and turns delta into NaN, which the solve's
 // source then reports as invalid input)
 static int deposit_impl(dgp_plan* pl, const void* pos, int fp32, long long np, long long* grid, double* delta,
-                        bool remove_mean, hipStream_t s) {
+                        hipStream_t s) {
   Timed tm(pl, s, DGP_T_DEPOSIT);
   launch_deposit(pl->n, pl->box, pos, fp32, np, grid, pl->flag, pl->spec6, spec6_bytes(pl), s);
   if (delta) {
-    if (remove_mean) {   // the mean of the counts (deterministic reduction), removed in the same pass
-      launch_absmean<long long>(pl->n3, grid, 1, pl->red, nullptr, pl->vec, s);
-      launch_counts_to_delta(pl->n, grid, np, delta, pl->flag, s, pl->vec);
-    } else {
-      launch_counts_to_delta(pl->n, grid, np, delta, pl->flag, s);
-    }
+    // the mean of the counts (deterministic reduction), removed in the same pass
+    launch_absmean<long long>(pl->n3, grid, 1, pl->red, nullptr, pl->vec, s);
+    launch_counts_to_delta(pl->n, grid, np, delta, pl->flag, s, pl->vec);
   }
   LAUNCHCHK();
   return DGP_OK;
@@ -887,7 +904,7 @@ extern "C" int dgp_deposit(dgp_plan* pl, const void* pos, int pos_is_fp32, long 
   if (!pl || !pos || np < 1) return fail(DGP_E_INVALID, "plan, pos and np >= 1 are required");
   TRY(require_batch1(pl));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  TRY(deposit_impl(pl, pos, pos_is_fp32, np, grid_fixed ? grid_fixed : pl->grid, delta, true, s));
+  TRY(deposit_impl(pl, pos, pos_is_fp32, np, grid_fixed ? grid_fixed : pl->grid, delta, s));
   if (!grid_fixed && !delta) return DGP_OK;
   return DGP_OK;
 }
@@ -897,7 +914,7 @@ extern "C" int dgp_deposit(dgp_plan* pl, const void* pos, int pos_is_fp32, long 
 // into mesh3_32 (the field solve itself stays polished to the float64 tolerance).
 // delta_ready: spectral field 6 already holds the float64 axis-0/1 spectrum of delta (left
 // there by the solve's setup on the same delta).
-static int force_mesh(dgp_plan* pl, const dgp_params* p, const double* delta, const double* u, double* phi_n,
+static int force_mesh(dgp_plan* pl, const dgp_params* p, const Contrast& delta, const double* u, double* phi_n,
                       bool delta_ready, hipStream_t s) {
   Timed tm(pl, s, DGP_T_FORCES);
   const int n = pl->n;
@@ -916,7 +933,7 @@ static int force_mesh(dgp_plan* pl, const dgp_params* p, const double* delta, co
     if (delta_ready)
       launch_convert<float>(2 * fs, pl->spec6 + 6 * fs, 0, reinterpret_cast<float*>(fin), s);
     else
-      launch_p1_fwd_from64(n, delta, fin, 1, nullptr, s);
+      fwd_axis0(n, delta, fin, 1, s);
     if (use_u) launch_p1_fwd_from64(n, u, fin + fs, 1, nullptr, s);
     if (plane) {
       launch_plane<float>(n, SPEC_FORCES, fin, fs, pl->spec6_32, fs, phi_n ? 4 : 3, 1, cf, nullptr, nullptr, s);
@@ -937,7 +954,7 @@ static int force_mesh(dgp_plan* pl, const dgp_params* p, const double* delta, co
     return DGP_OK;
   }
   cx<double>* fin = pl->spec6 + 6 * fs;   // delta, then u
-  if (!delta_ready) launch_p1_fwd<double>(n, delta, fin, 1, nullptr, s);
+  if (!delta_ready) fwd_axis0(n, delta, fin, 1, s);
   if (use_u) launch_p1_fwd<double>(n, u, fin + fs, 1, nullptr, s);
   if (plane) {
     launch_plane<double>(n, SPEC_FORCES, fin, fs, pl->spec6, fs, phi_n ? 4 : 3, 1, cf, nullptr, nullptr, s);
@@ -970,7 +987,7 @@ extern "C" int dgp_pm_forces(dgp_plan* pl, const dgp_params* p, const double* de
   if (!delta || !pos || !force || np < 1) return fail(DGP_E_INVALID, "delta, pos, force and np >= 1 are required");
   if (p->force_mode == DGP_FORCE_NLDGP && !u_state) return fail(DGP_E_INVALID, "u_state is required for nlDGP forces");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  TRY(force_mesh(pl, p, delta, u_state, phi_n, false, s));
+  TRY(force_mesh(pl, p, Contrast{delta, nullptr, 0.0, nullptr}, u_state, phi_n, false, s));
   int mfp32 = 0;
   const void* mesh = mesh_of(pl, &mfp32);
   launch_interp(pl->n, pl->box, mesh, mfp32, 3, pos, pos_is_fp32, np, force, s);
@@ -986,14 +1003,15 @@ extern "C" int dgp_step(dgp_plan* pl, const dgp_params* p, void* pos, void* vel,
   if (!pos || !vel || !u_state || np < 1) return fail(DGP_E_INVALID, "pos, vel, u_state and np >= 1 are required");
   if (!std::isfinite(dlna)) return fail(DGP_E_INVALID, "dlna must be finite");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  TRY(deposit_impl(pl, pos, is_fp32, np, pl->grid, pl->delta, false, s));
+  TRY(deposit_impl(pl, pos, is_fp32, np, pl->grid, nullptr, s));
+  const Contrast delta{nullptr, pl->grid, counts_scale(pl->n, np), pl->flag};
   const bool solve = p->force_mode == DGP_FORCE_NLDGP;
   if (solve) {
     HIPCHK(hipEventRecord(pl->ev0, s));
-    TRY(solve_enqueue(pl, p, pl->delta, u_state, s));
+    TRY(solve_enqueue(pl, p, delta, u_state, s));
     HIPCHK(hipEventRecord(pl->ev1, s));
   }
-  TRY(force_mesh(pl, p, pl->delta, u_state, nullptr, solve, s));
+  TRY(force_mesh(pl, p, delta, u_state, nullptr, solve, s));
   const double a = p->a;
   double (*const hub)(double, double) = p->force_mode == DGP_FORCE_GR ? hubble_E_lcdm : hubble_E;
   const double e_n = hub(p->omega_m0, a);

@@ -37,6 +37,7 @@ struct SpecCoef {
   double inv_eta_nl;// 1/eta in the sqrt(-lap) phi term (0 if nonlocal off)
   double force_scale;  // (c/H0)^2
   double inv_n3;    // 1/N^3 (inverse-transform normalisation, folded into the multiplier)
+  double inv_n2;    // 1/N^2
   double lam2;      // 2 lam (adjoint combine)
   double nl_scale;  // 1/(N^3 kappa kf): the nonlocal term's -1/kbar, normalised, is -nl_scale/|n|
   int force_mode;   // ForceMode
@@ -147,7 +148,13 @@ void launch_p1_fwd(int n, const T* in, cx<T>* out, int batch, const SolveCtl* ct
 void launch_p1_fwd_from64(int n, const double* in, cx<float>* out, int batch, const SolveCtl* ctl, hipStream_t s);
 template <typename T>
 void launch_p1_inv(int n, const cx<T>* in, T* out, int batch, const SolveCtl* ctl, hipStream_t s,
-                   float* out32 = nullptr);   // out32: optional float32 copy of out
+                   float* out32 = nullptr,    // optional float32 copy of out
+                   double scale = 1.0,        // factor of the output (a power of two)
+                   double* part = nullptr);   // optional sums of |out| per workgroup, [batch][p1_groups(n)] (float64 T)
+// axis-0 forward pass of a deposit's density contrast, formed from its counts on load (NaN when *bad)
+template <typename T>
+void launch_p1_fwd_counts(int n, const long long* grid, double qscale, const int* bad, cx<T>* out, hipStream_t s);
+int p1_groups(int n);
 // nf fields, each [batch][H][N][N]; DIR -1 forward, +1 inverse
 template <typename T>
 void launch_p2(int n, cx<T>* data, int nf, int batch, int dir, const SolveCtl* ctl, hipStream_t s);
@@ -211,14 +218,16 @@ template <typename T>
 void launch_absmean(size_t n3, const T* x, int batch, double* scratch, double* abs_mean, double* mean,
                     hipStream_t s);
 size_t absmean_scratch_doubles(size_t n3, int batch);
-// control blocks: eps from abs_mean[b], buffer roles reset (and the histories of both sets)
-void launch_ctl_init(SolveCtl* ctl, SolveCtl* other, const double* eps, int batch, hipStream_t s);
+// control blocks: eps[b] = the sum of part[b][0 .. groups) / n3 (the partial sums of |S|), buffer roles reset
+// (and the histories of both sets)
+void launch_ctl_init(SolveCtl* ctl, SolveCtl* other, const double* part, int groups, size_t n3, int batch,
+                     hipStream_t s);
 // spherical approximation (Eqs. FullDGP2sph, SphPoi): u = the first w = 1/3 update from u = 0,
 // u = 2 S / (alpha + sqrt(alpha^2 + (8/3) lam S)) (vertex where the discriminant is negative),
 // for [batch][n3] S into u; then the control blocks record a decided one-update solve
 // (per-workgroup bad counts go through `partial`, which must hold batch x 4096 x 2 doubles)
 void launch_spherical(size_t n3, int batch, const double* S, double* u, double alpha, double lam, double* partial,
-                      SolveCtl* ctl, const double* eps, hipStream_t s);
+                      SolveCtl* ctl, const double* eps_part, int eps_groups, hipStream_t s);
 // end of the float32 phase: per element, the warm start for float64 (the update of the
 // pass that met the switch tolerance unless it met bad points, else the checked iterate;
 // the latest iterate if the phase was still running) converted into dst[B][n3], then the
@@ -266,11 +275,11 @@ void launch_nonelliptic(size_t n3, int batch, const double* u, const double* h5,
 // bytes, 256-byte aligned, that the tile sort may use; the result is the same without it
 void launch_deposit(int n, double box, const void* pos, int pos_fp32, long long np, long long* grid, int* bad,
                     void* scratch, size_t scratch_bytes, hipStream_t s);
-// delta = Q 2^-40 N^3/np - 1 (NaN everywhere when *bad is set)
-// delta from the fixed-point counts; mean_q (optional, device): the mean of the counts, whose delta
-// value is subtracted in the same pass (mean removal)
+double counts_scale(int n, long long np);   // density contrast of a count: count * counts_scale - 1
+// delta = Q 2^-40 N^3/np - 1 (NaN everywhere when *bad is set) minus its mean; mean_q (device): the mean
+// of the counts
 void launch_counts_to_delta(int n, const long long* grid, long long np, double* delta, const int* bad, hipStream_t s,
-                            const double* mean_q = nullptr);
+                            const double* mean_q);
 // zero `words` 8-byte words (a fill kernel: no memset node in captured streams)
 void launch_fill_zero(void* p, size_t words, hipStream_t s);
 // out[k][p] = CIC interpolation of component k of mesh [nc][n3] (nc in 1..3), float64 (mesh_fp32 = 0)

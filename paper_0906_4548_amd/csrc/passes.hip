@@ -17,6 +17,9 @@
 //   k_d = kf * n_d with signed mode numbers n_d in [-N/2, N/2); kbar = kappa |k|;
 //   k = 0 multipliers of 1/kbar, 1/k^2, k_i k_j / k^2 are 0; a multiplier odd in
 //   component d (mixed Hessian terms, the gradient) is 0 at the Nyquist index of d.
+#include <type_traits>
+
+#include "control.h"
 #include "dgp_internal.h"
 #include "spectral.h"
 
@@ -77,12 +80,20 @@ __device__ __forceinline__ bool batch_done(const SolveCtl* ctl, int b) {
   return ctl != nullptr && ctl[b].done != 0;
 }
 
+// density contrast of a cell's fixed-point count (the rounding of the deposit's delta)
+__device__ __forceinline__ double contrast(long long count, double qscale) {
+#pragma clang fp contract(off)
+  return double(count) * qscale - 1.0;
+}
+
 // ------------------------------------------------------------------ axis 0, forward (real -> complex)
-// I: element type of the real input (float64 input to a float32 transform is rounded on load)
+// I: element type of the real input (float64 input to a float32 transform is rounded on load); int64
+// input is a deposit's fixed-point counts, whose density contrast count qscale - 1 (NaN everywhere when
+// *bad is set) is formed on load
 template <typename T, int N, typename I = T>
 __global__ void __launch_bounds__((Geo<T, N>::kP1))
 k_p1_fwd(const I* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restrict__ tw,
-         const SolveCtl* __restrict__ ctl) {
+         const SolveCtl* __restrict__ ctl, double qscale, const int* __restrict__ bad) {
   using P = typename Geo<T, N>::P;
   constexpr int R = P::R;
   using G = P1Tile<T, N, R>;
@@ -99,7 +110,13 @@ k_p1_fwd(const I* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restr
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     const cx<I> x = *reinterpret_cast<const cx<I>*>(src + (size_t)(t + q * TT) * N * N);
-    v[q] = mk(T(x.x), T(x.y));
+    if constexpr (std::is_integral<I>::value) v[q] = mk(T(contrast(x.x, qscale)), T(contrast(x.y, qscale)));
+    else v[q] = mk(T(x.x), T(x.y));
+  }
+  if constexpr (std::is_integral<I>::value) {
+    if (*bad != 0)
+#pragma unroll
+      for (int q = 0; q < R; ++q) v[q] = mk(T(__builtin_nan("")), T(__builtin_nan("")));
   }
   LdsCol<T, TP> L{lds, c};
   fft<T, N, P, -1>(v, tw, L, t);
@@ -123,7 +140,7 @@ k_p1_fwd(const I* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restr
 template <typename T, int N>
 __global__ void __launch_bounds__((Geo<T, N>::kP1))
 k_p1_inv(const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ tw,
-         const SolveCtl* __restrict__ ctl, float* __restrict__ out32) {
+         const SolveCtl* __restrict__ ctl, float* __restrict__ out32, T scale, double* __restrict__ part) {
   using P = typename Geo<T, N>::P;
   constexpr int R = P::R;
   using G = P1Tile<T, N, R>;
@@ -159,6 +176,8 @@ k_p1_inv(const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restr
   }
   LdsCol<T, TP> L{lds, c};
   fft<T, N, P, +1>(v, tw, L, t);
+#pragma unroll
+  for (int q = 0; q < R; ++q) v[q] = mk(v[q].x * scale, v[q].y * scale);
   T* dst = out + (size_t)b * N * N * N + (size_t)i1 * N + i2;
 #pragma unroll
   for (int q = 0; q < R; ++q) store_stream(reinterpret_cast<cx<T>*>(dst + (size_t)(t + q * TT) * N * N), v[q]);
@@ -167,6 +186,20 @@ k_p1_inv(const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restr
 #pragma unroll
     for (int q = 0; q < R; ++q)
       *reinterpret_cast<float2*>(d32 + (size_t)(t + q * TT) * N * N) = make_float2(float(v[q].x), float(v[q].y));
+  }
+  if (part) {   // optional sum of |out| of the workgroup's tile
+    double sa = 0.0;
+#pragma unroll
+    for (int q = 0; q < R; ++q) sa += fabs(double(v[q].x)) + fabs(double(v[q].y));
+    constexpr int NT = G::kThreads, WW = NT < 64 ? NT : 64, NW = (NT + 63) / 64;
+    __shared__ double ws[NW];
+    sa = wave_sum<WW>(sa);
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = sa;
+    lds_barrier();
+    if (threadIdx.x == 0) {
+      for (int i = 1; i < NW; ++i) sa += ws[i];
+      part[((size_t)b * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = sa;
+    }
   }
 }
 
@@ -763,17 +796,18 @@ k_power_final(const double* __restrict__ partial, int groups, int nbins, double*
 
 // ------------------------------------------------------------------ launchers
 template <typename T, int N, typename I = T>
-static void p1_fwd_n(const I* in, cx<T>* out, int batch, const SolveCtl* ctl, const cx<T>* tw, hipStream_t s) {
+static void p1_fwd_n(const I* in, cx<T>* out, int batch, const SolveCtl* ctl, const cx<T>* tw, hipStream_t s,
+                     double qscale = 0.0, const int* bad = nullptr) {
   using G = P1Tile<T, N, Geo<T, N>::R>;
   dim3 grid(N / (2 * G::kTP), N, batch);
-  hipLaunchKernelGGL((k_p1_fwd<T, N, I>), grid, dim3(G::kThreads), 0, s, in, out, tw, ctl);
+  hipLaunchKernelGGL((k_p1_fwd<T, N, I>), grid, dim3(G::kThreads), 0, s, in, out, tw, ctl, qscale, bad);
 }
 template <typename T, int N>
 static void p1_inv_n(const cx<T>* in, T* out, int batch, const SolveCtl* ctl, const cx<T>* tw, float* out32,
-                     hipStream_t s) {
+                     double scale, double* part, hipStream_t s) {
   using G = P1Tile<T, N, Geo<T, N>::R>;
   dim3 grid(N / (2 * G::kTP), N, batch);
-  hipLaunchKernelGGL((k_p1_inv<T, N>), grid, dim3(G::kThreads), 0, s, in, out, tw, ctl, out32);
+  hipLaunchKernelGGL((k_p1_inv<T, N>), grid, dim3(G::kThreads), 0, s, in, out, tw, ctl, out32, T(scale), part);
 }
 template <typename T, int N>
 static void p2_n(cx<T>* data, int nf, int batch, int dir, const SolveCtl* ctl, const cx<T>* tw, hipStream_t s) {
@@ -853,9 +887,17 @@ void launch_p1_fwd_from64(int n, const double* in, cx<float>* out, int batch, co
 #undef C
 }
 template <typename T>
-void launch_p1_inv(int n, const cx<T>* in, T* out, int batch, const SolveCtl* ctl, hipStream_t s, float* out32) {
+void launch_p1_fwd_counts(int n, const long long* grid, double qscale, const int* bad, cx<T>* out, hipStream_t s) {
   const cx<T>* tw = twiddles<T>(n);
-#define C(NN) p1_inv_n<T, NN>(in, out, batch, ctl, tw, out32, s)
+#define C(NN) p1_fwd_n<T, NN, long long>(grid, out, 1, nullptr, tw, s, qscale, bad)
+  DGP_DISPATCH_N(n, C)
+#undef C
+}
+template <typename T>
+void launch_p1_inv(int n, const cx<T>* in, T* out, int batch, const SolveCtl* ctl, hipStream_t s, float* out32,
+                   double scale, double* part) {
+  const cx<T>* tw = twiddles<T>(n);
+#define C(NN) p1_inv_n<T, NN>(in, out, batch, ctl, tw, out32, scale, part, s)
   DGP_DISPATCH_N(n, C)
 #undef C
 }
@@ -913,6 +955,14 @@ void launch_power(int n, const cx<double>* in, int batch, const SpecCoef& coef, 
   hipLaunchKernelGGL(k_power_final, dim3(batch, (coef.nbins + 63) / 64), dim3(1024), 0, s, partial, g, coef.nbins, sums);
 }
 
+int p1_groups(int n) {   // workgroups per batch element of the float64 axis-0 passes
+  int r = 0;
+#define C(NN) r = NN / (2 * P1Tile<double, NN, Geo<double, NN>::R>::kTP) * NN
+  DGP_DISPATCH_N(n, C)
+#undef C
+  return r;
+}
+
 int p3_row_groups(int n) {   // row groups of the float64 axis-2 pass (bounds the P(k) partials)
   int r = 0;
 #define C(NN)                                                          \
@@ -927,8 +977,12 @@ int p3_row_groups(int n) {   // row groups of the float64 axis-2 pass (bounds th
 
 template void launch_p1_fwd<double>(int, const double*, cx<double>*, int, const SolveCtl*, hipStream_t);
 template void launch_p1_fwd<float>(int, const float*, cx<float>*, int, const SolveCtl*, hipStream_t);
-template void launch_p1_inv<double>(int, const cx<double>*, double*, int, const SolveCtl*, hipStream_t, float*);
-template void launch_p1_inv<float>(int, const cx<float>*, float*, int, const SolveCtl*, hipStream_t, float*);
+template void launch_p1_fwd_counts<double>(int, const long long*, double, const int*, cx<double>*, hipStream_t);
+template void launch_p1_fwd_counts<float>(int, const long long*, double, const int*, cx<float>*, hipStream_t);
+template void launch_p1_inv<double>(int, const cx<double>*, double*, int, const SolveCtl*, hipStream_t, float*,
+                                    double, double*);
+template void launch_p1_inv<float>(int, const cx<float>*, float*, int, const SolveCtl*, hipStream_t, float*,
+                                   double, double*);
 template void launch_p2<double>(int, cx<double>*, int, int, int, const SolveCtl*, hipStream_t);
 template void launch_p2<float>(int, cx<float>*, int, int, int, const SolveCtl*, hipStream_t);
 template void launch_p2_split<double>(int, cx<double>*, size_t, int, const SolveCtl*, hipStream_t);

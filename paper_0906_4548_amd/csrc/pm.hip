@@ -510,14 +510,14 @@ k_tile_halo(int n, TileSort ts, unsigned long long* __restrict__ grid) {
   }
 }
 
-// delta = counts * qscale - 1; with mean_q (the mean of the fixed-point counts, a deterministic
-// reduction of the grid), minus the mean of delta, qscale <q> - 1, in the same pass
+// delta = counts * qscale - 1 minus its mean, qscale <q> - 1 (mean_q: the mean of the fixed-point counts,
+// a deterministic reduction of the grid), in one pass
 __global__ void __launch_bounds__(256)
 k_counts_to_delta(const long long* __restrict__ grid, size_t n3, double qscale, double* __restrict__ delta,
                   const int* __restrict__ bad, const double* __restrict__ mean_q) {
 #pragma clang fp contract(off)
   const bool nan_out = *bad != 0;   // a non-finite position: delta is undefined, mark it so
-  const double m = mean_q ? *mean_q * qscale - 1.0 : 0.0;
+  const double m = *mean_q * qscale - 1.0;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n3; i += (size_t)gridDim.x * 256) {
     const double d = double(grid[i]) * qscale;
     delta[i] = nan_out ? __builtin_nan("") : (d - 1.0) - m;
@@ -974,10 +974,12 @@ void launch_deposit(int n, double box, const void* pos, int pos_fp32, long long 
   else deposit_t<double, 1024>(n, box, p64, np, out, bad, scratch, scratch_bytes, s);
 }
 
+double counts_scale(int n, long long np) { return ldexp(double((size_t)n * n * n) / double(np), -40); }
+
 void launch_counts_to_delta(int n, const long long* grid, long long np, double* delta, const int* bad, hipStream_t s,
                             const double* mean_q) {
   const size_t n3 = (size_t)n * n * n;
-  const double qscale = ldexp(double(n3) / double(np), -40);
+  const double qscale = counts_scale(n, np);
   hipLaunchKernelGGL(k_counts_to_delta, dim3(grid_strided(n3)), dim3(256), 0, s, grid, n3, qscale, delta, bad, mean_q);
 }
 

@@ -999,14 +999,34 @@ __device__ __forceinline__ void mark_invalid_input(SolveCtl& C) {
   }
 }
 
-__global__ void __launch_bounds__(64) k_ctl_init(SolveCtl* __restrict__ ctl, SolveCtl* __restrict__ other, const double* __restrict__ eps) {
+// eps of one element: sum of the |S| partial sums over n3, by a whole workgroup of NT threads (every
+// thread returns it; fixed order)
+template <int NT>
+__device__ __forceinline__ double eps_of(const double* __restrict__ part, int groups, size_t n3) {
+  __shared__ double w[NT / 64];
+  double s = 0.0;
+  for (int g = threadIdx.x; g < groups; g += NT) s += part[g];
+  s = wave_sum<64>(s);
+  if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = s;
+  __syncthreads();
+  s = w[0];
+  for (int i = 1; i < NT / 64; ++i) s += w[i];
+  return s / double(n3);
+}
+
+__global__ void __launch_bounds__(1024)
+k_ctl_init(SolveCtl* __restrict__ ctl, SolveCtl* __restrict__ other, const double* __restrict__ part, int groups,
+           size_t n3) {
   const int b = blockIdx.x;
+  const double eps = eps_of<1024>(part + (size_t)b * groups, groups, n3);
   SolveCtl& C = ctl[b];
-  ctl_reset_history(C);
-  ctl_reset_history(other[b]);
+  if (threadIdx.x < 64) {
+    ctl_reset_history(C);
+    ctl_reset_history(other[b]);
+  }
   if (threadIdx.x != 0) return;
   ctl_reset(C);
-  C.eps = eps[b];
+  C.eps = eps;
   C.iters1 = 0;
   C.passes1 = 0;
   C.phase1_done = 1;
@@ -1117,9 +1137,10 @@ k_spherical(size_t n3, const double* __restrict__ S, double* __restrict__ u, dou
 }
 
 __global__ void __launch_bounds__(256)
-k_ctl_spherical(SolveCtl* __restrict__ ctl, const double* __restrict__ eps, const double* __restrict__ partial,
-                int groups, size_t n3) {
+k_ctl_spherical(SolveCtl* __restrict__ ctl, const double* __restrict__ eps_part, int eps_groups,
+                const double* __restrict__ partial, int groups, size_t n3) {
   const int b = blockIdx.x;
+  const double eps = eps_of<256>(eps_part + (size_t)b * eps_groups, eps_groups, n3);
   if (threadIdx.x < 64) ctl_reset_history(ctl[b]);
   double nb = 0.0;
   for (int g = threadIdx.x; g < groups; g += 256) nb += partial[(size_t)b * groups + g];
@@ -1130,7 +1151,7 @@ k_ctl_spherical(SolveCtl* __restrict__ ctl, const double* __restrict__ eps, cons
   if (threadIdx.x != 0) return;
   SolveCtl& C = ctl[b];
   ctl_reset(C);
-  C.eps = eps[b];
+  C.eps = eps;
   C.iters1 = 0;
   C.passes1 = 0;
   C.phase1_done = 1;
@@ -1146,10 +1167,10 @@ k_ctl_spherical(SolveCtl* __restrict__ ctl, const double* __restrict__ eps, cons
 }
 
 void launch_spherical(size_t n3, int batch, const double* S, double* u, double alpha, double lam, double* partial,
-                      SolveCtl* ctl, const double* eps, hipStream_t s) {
+                      SolveCtl* ctl, const double* eps_part, int eps_groups, hipStream_t s) {
   const int g = int(std::min<size_t>(4096, (n3 + 255) / 256));
   hipLaunchKernelGGL(k_spherical, dim3(g, batch), dim3(256), 0, s, n3, S, u, alpha, lam, partial);
-  hipLaunchKernelGGL(k_ctl_spherical, dim3(batch), dim3(256), 0, s, ctl, eps, partial, g, n3);
+  hipLaunchKernelGGL(k_ctl_spherical, dim3(batch), dim3(256), 0, s, ctl, eps_part, eps_groups, partial, g, n3);
 }
 
 template <typename T>
@@ -1165,8 +1186,9 @@ template void launch_take_result<double>(const SolveCtl*, const double*, int, si
 template void launch_take_result<float>(const SolveCtl*, const float*, int, size_t, double*, double*, double*,
                                         hipStream_t);
 
-void launch_ctl_init(SolveCtl* ctl, SolveCtl* other, const double* eps, int batch, hipStream_t s) {
-  hipLaunchKernelGGL(k_ctl_init, dim3(batch), dim3(64), 0, s, ctl, other, eps);
+void launch_ctl_init(SolveCtl* ctl, SolveCtl* other, const double* part, int groups, size_t n3, int batch,
+                     hipStream_t s) {
+  hipLaunchKernelGGL(k_ctl_init, dim3(batch), dim3(1024), 0, s, ctl, other, part, groups, n3);
 }
 
 
@@ -1191,8 +1213,6 @@ template void launch_relax<double>(int, const cx<double>*, double*, const double
 template void launch_relax<float>(int, const cx<float>*, float*, const float*, cx<float>*, double*,
                                   const double*, int, const SolveCfg&, const SolveCtl*, hipStream_t, hipEvent_t,
                                   hipEvent_t);
-template void launch_absmean<double>(size_t, const double*, int, double*, double*, double*, hipStream_t);
-template void launch_absmean<float>(size_t, const float*, int, double*, double*, double*, hipStream_t);
 template void launch_absmean<long long>(size_t, const long long*, int, double*, double*, double*, hipStream_t);
 
 }  // namespace dgp

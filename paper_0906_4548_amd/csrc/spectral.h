@@ -53,8 +53,9 @@ __device__ __forceinline__ T nonlocal_mult(const SpecCoef& cf, const Mode3& m) {
   }
 }
 
-// multipliers, times 1/N^3 (0 at k = 0), of S = A (1 - beta/kbar) delta and of the linear solution
-// S / (alpha - gamma/kbar)
+// multipliers (0 at k = 0) of S = A (1 - beta/kbar) delta, times 1/N^3, and of the linear solution
+// S / (alpha - gamma/kbar), times 1/N^2: after the inverse transforms of axes 2 and 1 that is the
+// linear solution's forward axis-0 spectrum
 template <typename T>
 __device__ __forceinline__ void source_mults(const SpecCoef& cf, const Mode3& m, T& ms, T& ml) {
   ms = T(0);
@@ -63,7 +64,7 @@ __device__ __forceinline__ void source_mults(const SpecCoef& cf, const Mode3& m,
     const double ikb = 1.0 / (cf.kappa * cf.kf * sqrt(double(m.msq)));
     const double sv = cf.A * (1.0 - cf.beta * ikb);
     ms = T(sv * cf.inv_n3);
-    ml = T(sv / (cf.alpha - cf.gamma * ikb) * cf.inv_n3);
+    ml = T(sv / (cf.alpha - cf.gamma * ikb) * cf.inv_n2);
   }
 }
 
