@@ -127,10 +127,10 @@ k_adj_step(const cx<double>* __restrict__ qspec, double* __restrict__ mubuf, siz
   // the new multiplier and its first two products, formed where h00 and h11 are read
   cx<T> m[R], p0[R], p1[R], v[R];
   if constexpr (UPDATE) {
-    const cx<T>* src = qspec + (size_t)b * H * NN + (size_t)i1 * N + i2;
+    const cx<T>* src = qspec + (size_t)b * H * NN + SpecRows<N>::col(i1) + i2;
     for (int kk = t; kk < H; kk += TT) {
-      lds[kk * 2 * TP + 2 * c] = src[(size_t)kk * NN];
-      lds[kk * 2 * TP + 2 * c + 1] = src[(size_t)kk * NN + 1];
+      lds[kk * 2 * TP + 2 * c] = src[(size_t)kk * SpecRows<N>::kPlane];
+      lds[kk * 2 * TP + 2 * c + 1] = src[(size_t)kk * SpecRows<N>::kPlane + 1];
     }
     lds_barrier();
 #pragma unroll
@@ -197,7 +197,7 @@ k_adj_step(const cx<double>* __restrict__ qspec, double* __restrict__ mubuf, siz
       sh += hx * m[q].x + hy * m[q].y;
     }
   }
-  cx<T>* dst0 = spec6 + (size_t)b * H * NN + (size_t)i1 * N + i2;
+  cx<T>* dst0 = spec6 + (size_t)b * H * NN + SpecRows<N>::col(i1) + i2;
   cx<T> nx[R];   // the next product's Hessian entry, one field ahead
 #pragma unroll 1
   for (int f = 0; f < 6; ++f) {
@@ -223,8 +223,8 @@ k_adj_step(const cx<double>* __restrict__ qspec, double* __restrict__ mubuf, siz
     for (int kk = t; kk < H; kk += TT) {
       const cx<T> zk = lds[kk * TP + c];
       const cx<T> zn = lds[((N - kk) & (N - 1)) * TP + c];
-      store_stream(&dst[(size_t)kk * NN], mk(T(0.5) * (zk.x + zn.x), T(0.5) * (zk.y - zn.y)));
-      store_stream(&dst[(size_t)kk * NN + 1], mk(T(0.5) * (zk.y + zn.y), T(0.5) * (zn.x - zk.x)));
+      store_stream(&dst[(size_t)kk * SpecRows<N>::kPlane], mk(T(0.5) * (zk.x + zn.x), T(0.5) * (zk.y - zn.y)));
+      store_stream(&dst[(size_t)kk * SpecRows<N>::kPlane + 1], mk(T(0.5) * (zk.y + zn.y), T(0.5) * (zn.x - zk.x)));
     }
   }
   red[0][threadIdx.x] = sr;

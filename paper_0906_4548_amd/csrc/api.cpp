@@ -594,8 +594,8 @@ static int setup_source(dgp_plan* pl, const dgp_params* p, const Contrast& delta
     launch_p3<double>(n, SPEC_SOURCE, dspec, fs, 1, sspec, fs, 2, B, cf, nullptr, nullptr, nullptr, s);
     launch_p2<double>(n, sspec, want_linear ? 2 : 1, B, +1, nullptr, s);
   }
-  launch_p1_inv<double>(n, sspec, w.S, B, nullptr, s, S32, 1.0, pl->red);
-  if (want_linear) launch_p1_inv<double>(n, w.spec_u, w.U, B, nullptr, s, U32, 1.0 / n);
+  launch_p1_inv<double>(n, sspec, w.S, B, nullptr, s, S32, 1.0, pl->red, true);
+  if (want_linear) launch_p1_inv<double>(n, w.spec_u, w.U, B, nullptr, s, U32, 1.0 / n, nullptr, true);
   LAUNCHCHK();
   return DGP_OK;
 }
@@ -708,7 +708,7 @@ static int status_rank(int st) { return st == DGP_OK ? 0 : (st == DGP_NOT_CONVER
 template <typename T>
 static int collect_enqueue(dgp_plan* pl, Ws<T>& w, double* u_state, hipStream_t s) {
   const int B = pl->batch;
-  launch_take_result<T>(ctl_now(pl), w.U, B, pl->n3, u_state, pl->red, pl->vec + B, s);
+  launch_take_result<T>(ctl_now(pl), w.U, B, pl->n, u_state, pl->red, pl->vec + B, s);
   HIPCHK(hipMemcpyAsync(pl->means_host, pl->vec + B, sizeof(double) * B, hipMemcpyDeviceToHost, s));
   LAUNCHCHK();
   return DGP_OK;
@@ -766,14 +766,14 @@ static int solve64(dgp_plan* pl, const dgp_params* p, const Contrast& delta, dou
   const int B = pl->batch;
   TRY(setup_source(pl, p, delta, w, p->init == DGP_INIT_LINEAR, s));
   if (p->init == DGP_INIT_WARM) {
-    HIPCHK(hipMemcpyAsync(w.U, u_state, sizeof(double) * B * pl->n3, hipMemcpyDeviceToDevice, s));
+    launch_take_field(pl->n, u_state, w.U, B, s);
   } else if (p->init == DGP_INIT_ZERO) {
     launch_fill_zero(w.U, (size_t)B * pl->n3, s);
   }
   launch_ctl_init(ctl_now(pl), ctl_other(pl), pl->red, p1_groups(pl->n), pl->n3, B, s);
   // a pass starts from the axis-0 spectrum of its iterate (what the fused pass writes); the linear
   // guess's is there already
-  if (p->init != DGP_INIT_LINEAR) launch_p1_fwd<double>(pl->n, w.U, w.spec_u, B, nullptr, s);
+  if (p->init != DGP_INIT_LINEAR) launch_p1_fwd<double>(pl->n, w.U, w.spec_u, B, nullptr, s, true);
   const SolveCfg cfg = solve_cfg(pl, p, p->tol, p->max_iter);
   TRY(run_loop<double>(pl, p, w, cfg, s, pl->hint64, true));
   pl->hint64 = max_passes(pl);
@@ -841,7 +841,7 @@ int solve32_polish(dgp_plan* pl, const dgp_params* p, const Contrast& delta, dou
   // phase 2 if phase 1 accepts the initial guess as it is)
   TRY(setup_source(pl, p, delta, w, p->init == DGP_INIT_LINEAR, s, w32.S, w32.U));
   if (p->init == DGP_INIT_WARM) {
-    HIPCHK(hipMemcpyAsync(w.U, u_state, sizeof(double) * B * n3, hipMemcpyDeviceToDevice, s));
+    launch_take_field(pl->n, u_state, w.U, B, s);
     launch_convert<float>(B * n3, u_state, 0, w32.U, s);
   } else if (p->init == DGP_INIT_ZERO) {
     launch_fill_zero(w.U, (size_t)B * n3, s);
@@ -859,8 +859,8 @@ int solve32_polish(dgp_plan* pl, const dgp_params* p, const Contrast& delta, dou
     TRY(run_loop<float>(pl, p, w32, cfg32, s, pl->hint32 + 1, false));
   else
     TRY(run_loop<float>(pl, p, w32, cfg32, s, 0, true));
-  launch_handoff(ctl_now(pl), ctl_other(pl), w32.U, B, n3, w.U, s);
-  launch_p1_fwd<double>(pl->n, w.U, w.spec_u, B, nullptr, s);
+  launch_handoff(ctl_now(pl), ctl_other(pl), w32.U, B, pl->n, w.U, s);
+  launch_p1_fwd<double>(pl->n, w.U, w.spec_u, B, nullptr, s, true);
   const SolveCfg cfg = solve_cfg(pl, p, p->tol, p->max_iter);
   TRY(run_loop<double>(pl, p, w, cfg, s, pl->hint64, true));
   // learn the pass counts for the next solve on this plan

@@ -138,19 +138,55 @@ __device__ __forceinline__ void xcd_tile(int& bx, int& by) {
   by = l / gx;
 }
 
+// Row order of a spectrum: row (k0, i1) at rows' index ((i1 / kG) H + k0) kG + i1 % kG, i.e. the axis-1
+// rows in groups of kG that hold every k0.  Up to 256^3 one group holds all (plane k0 after plane).  At
+// 512^3 a column's planes would be 4 MB apart (float64), which the kernels with one axis-0 column per
+// transform stream badly, so four rows make a group and a column's rows lie 32 KB apart.  float64
+// relaxation 3567 -> 2860 us, axis-0 inverse pass 627 -> 592 us, float32 axis-1 split pass 1264 -> 1125
+// us; the float64 axis-1 passes, whose columns are now the scattered ones, 1936 -> 2030 and 413 -> 435
+// us (a pass of the solve 6.75 -> 6.15 ms).  Groups of 2 to 128 rows are within 2 %.  At 256^3 the split
+// pass loses (218 -> 285 us) more than the relaxation gains (366 -> 356 us), as at 128^3 (224 -> 244 us).
+constexpr int kRowGroup = 4, kRowGroupMin = 512;
+template <int N>
+struct SpecRows {
+  static constexpr int kH = N / 2 + 1;
+  static constexpr int kG = N >= kRowGroupMin ? kRowGroup : N;
+  static constexpr unsigned kPlane = kG * N;   // elements from k0 to k0 + 1
+  __host__ __device__ static constexpr size_t col(int i1) {   // element offset of row (0, i1)
+    return kG == N ? size_t(i1) * N : size_t(i1 / kG) * (size_t(kH) * kPlane) + size_t(i1 % kG) * N;
+  }
+  // the k0 and i1 of a row index
+  __host__ __device__ static constexpr int k0_of(int row) { return kG == N ? row / N : (row / kG) % kH; }
+  __host__ __device__ static constexpr int i1_of(int row) {
+    return kG == N ? row % N : row / (kG * kH) * kG + row % kG;
+  }
+};
+// Row order of a solve's own real fields (iterates, S), alike: row (i0, i1) at ((i1 / kG) N + i0) kG + i1 % kG
+// (float64; the float32 relaxation reads its fields as fast in C order)
+template <typename T, int N>
+struct RealRows {
+  static constexpr int kG = N >= kRowGroupMin && sizeof(T) == 8 ? kRowGroup : N;
+  static constexpr size_t kPlane = size_t(kG) * N;
+  __host__ __device__ static constexpr size_t col(int i1) {
+    return kG == N ? size_t(i1) * N : size_t(i1 / kG) * (N * kPlane) + size_t(i1 % kG) * N;
+  }
+};
+
 // ------------------------------------------------------------------ launchers
 // All launchers are asynchronous on `stream`; `done` (may be null) is a per-batch
 // flag array: work for a batch element whose flag is set is skipped.
 
 template <typename T>
-void launch_p1_fwd(int n, const T* in, cx<T>* out, int batch, const SolveCtl* ctl, hipStream_t s);
+void launch_p1_fwd(int n, const T* in, cx<T>* out, int batch, const SolveCtl* ctl, hipStream_t s,
+                   bool own = false);   // own: in is a solve's own field (RealRows)
 // float32 axis-0 forward pass of a float64 real field (rounded on load)
 void launch_p1_fwd_from64(int n, const double* in, cx<float>* out, int batch, const SolveCtl* ctl, hipStream_t s);
 template <typename T>
 void launch_p1_inv(int n, const cx<T>* in, T* out, int batch, const SolveCtl* ctl, hipStream_t s,
                    float* out32 = nullptr,    // optional float32 copy of out
                    double scale = 1.0,        // factor of the output (a power of two)
-                   double* part = nullptr);   // optional sums of |out| per workgroup, [batch][p1_groups(n)] (float64 T)
+                   double* part = nullptr,    // optional sums of |out| per workgroup, [batch][p1_groups(n)] (float64 T)
+                   bool own = false);         // out is a solve's own field (RealRows)
 // axis-0 forward pass of a deposit's density contrast, formed from its counts on load (NaN when *bad)
 template <typename T>
 void launch_p1_fwd_counts(int n, const long long* grid, double qscale, const int* bad, cx<T>* out, hipStream_t s);
@@ -232,11 +268,13 @@ void launch_spherical(size_t n3, int batch, const double* S, double* u, double a
 // pass that met the switch tolerance unless it met bad points, else the checked iterate;
 // the latest iterate if the phase was still running) converted into dst[B][n3], then the
 // control re-initialised for the float64 phase with the float32 counts kept
-void launch_handoff(SolveCtl* ctl, SolveCtl* other, const float* U32, int batch, size_t n3, double* dst, hipStream_t s);
+// a caller's float64 fields into the solve's own row order
+void launch_take_field(int n, const double* in, double* out, int batch, hipStream_t s);
+void launch_handoff(SolveCtl* ctl, SolveCtl* other, const float* U32, int batch, int n, double* dst, hipStream_t s);
 // the returned iterate of every element, as float64, into dst[B][n3], and its mean into
 // mean[B] (scratch: absmean_scratch_doubles(n3, batch) doubles)
 template <typename T>
-void launch_take_result(const SolveCtl* ctl, const T* U, int batch, size_t n3, double* dst, double* scratch,
+void launch_take_result(const SolveCtl* ctl, const T* U, int batch, int n, double* dst, double* scratch,
                         double* mean, hipStream_t s);
 
 // per-batch means of the two columns of [batch][groups][2] partial sums

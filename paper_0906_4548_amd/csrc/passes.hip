@@ -2,7 +2,8 @@
 //
 // Layouts (C order, last index fastest):
 //   real field      [batch][N][N][N]          index (i0, i1, i2)
-//   spectrum        [batch][N/2+1][N][N]      complex, index (k0, k1, k2)
+//   spectrum        [batch][N/2+1][N][N]      complex, index (k0, k1, k2); from N = 512 the rows are
+//                                             grouped along axis 1 (SpecRows)
 // The real-to-complex step runs along axis 0 (the slowest), so the half axis is
 // k0 and every pass moves whole N x N planes: no odd-sized inner dimension.
 //   axis-0 pass (p1): strided columns, two real columns packed as one complex
@@ -80,6 +81,13 @@ __device__ __forceinline__ bool batch_done(const SolveCtl* ctl, int b) {
   return ctl != nullptr && ctl[b].done != 0;
 }
 
+// rows of the real side of an axis-0 pass: a solve's own fields (OWN) or C order
+template <typename T, int N, bool OWN>
+struct P1Rows {
+  static constexpr size_t kPlane = OWN ? RealRows<T, N>::kPlane : size_t(N) * N;
+  __device__ static size_t col(int i1) { return OWN ? RealRows<T, N>::col(i1) : size_t(i1) * N; }
+};
+
 // density contrast of a cell's fixed-point count (the rounding of the deposit's delta)
 __device__ __forceinline__ double contrast(long long count, double qscale) {
 #pragma clang fp contract(off)
@@ -90,7 +98,7 @@ __device__ __forceinline__ double contrast(long long count, double qscale) {
 // I: element type of the real input (float64 input to a float32 transform is rounded on load); int64
 // input is a deposit's fixed-point counts, whose density contrast count qscale - 1 (NaN everywhere when
 // *bad is set) is formed on load
-template <typename T, int N, typename I = T>
+template <typename T, int N, typename I = T, bool OWN = false>
 __global__ void __launch_bounds__((Geo<T, N>::kP1))
 k_p1_fwd(const I* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restrict__ tw,
          const SolveCtl* __restrict__ ctl, double qscale, const int* __restrict__ bad) {
@@ -105,11 +113,12 @@ k_p1_fwd(const I* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restr
   const int c = threadIdx.x % TP, t = threadIdx.x / TP;
   const int i2 = (tile * TP + c) * 2;
   __shared__ cx<T> lds[N * TP];
-  const I* src = in + (size_t)b * N * N * N + (size_t)i1 * N + i2;
+  using RR = P1Rows<T, N, OWN>;
+  const I* src = in + (size_t)b * N * N * N + RR::col(i1) + i2;
   cx<T> v[R];
 #pragma unroll
   for (int q = 0; q < R; ++q) {
-    const cx<I> x = *reinterpret_cast<const cx<I>*>(src + (size_t)(t + q * TT) * N * N);
+    const cx<I> x = *reinterpret_cast<const cx<I>*>(src + (t + q * TT) * RR::kPlane);
     if constexpr (std::is_integral<I>::value) v[q] = mk(T(contrast(x.x, qscale)), T(contrast(x.y, qscale)));
     else v[q] = mk(T(x.x), T(x.y));
   }
@@ -124,20 +133,20 @@ k_p1_fwd(const I* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restr
 #pragma unroll
   for (int q = 0; q < R; ++q) lds[(t + q * TT) * TP + c] = v[q];
   __syncthreads();
-  cx<T>* dst = out + (size_t)b * H * N * N + (size_t)i1 * N + i2;
+  cx<T>* dst = out + (size_t)b * H * N * N + SpecRows<N>::col(i1) + i2;
   for (int k = t; k < H; k += TT) {
     const cx<T> zk = lds[k * TP + c];
     const cx<T> zn = lds[((N - k) & (N - 1)) * TP + c];
     // x_a(k) = (Z(k) + conj Z(N-k)) / 2,  x_b(k) = (Z(k) - conj Z(N-k)) / (2i)
     const cx<T> xa = mk(T(0.5) * (zk.x + zn.x), T(0.5) * (zk.y - zn.y));
     const cx<T> xb = mk(T(0.5) * (zk.y + zn.y), T(0.5) * (zn.x - zk.x));
-    store_stream(&dst[(size_t)k * N * N], xa);   // read by the next pass
-    store_stream(&dst[(size_t)k * N * N + 1], xb);
+    store_stream(&dst[(size_t)k * SpecRows<N>::kPlane], xa);   // read by the next pass
+    store_stream(&dst[(size_t)k * SpecRows<N>::kPlane + 1], xb);
   }
 }
 
 // ------------------------------------------------------------------ axis 0, inverse (complex -> real)
-template <typename T, int N>
+template <typename T, int N, bool OWN = false>
 __global__ void __launch_bounds__((Geo<T, N>::kP1))
 k_p1_inv(const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ tw,
          const SolveCtl* __restrict__ ctl, float* __restrict__ out32, T scale, double* __restrict__ part) {
@@ -153,10 +162,10 @@ k_p1_inv(const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restr
   const int c = threadIdx.x % TP, t = threadIdx.x / TP;
   const int i2 = (tile * TP + c) * 2;
   __shared__ cx<T> lds[LSZ];
-  const cx<T>* src = in + (size_t)b * H * N * N + (size_t)i1 * N + i2;
+  const cx<T>* src = in + (size_t)b * H * N * N + SpecRows<N>::col(i1) + i2;
   for (int k = t; k < H; k += TT) {
-    lds[k * 2 * TP + 2 * c] = src[(size_t)k * N * N];
-    lds[k * 2 * TP + 2 * c + 1] = src[(size_t)k * N * N + 1];
+    lds[k * 2 * TP + 2 * c] = src[(size_t)k * SpecRows<N>::kPlane];
+    lds[k * 2 * TP + 2 * c + 1] = src[(size_t)k * SpecRows<N>::kPlane + 1];
   }
   __syncthreads();
   cx<T> v[R];
@@ -178,9 +187,10 @@ k_p1_inv(const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restr
   fft<T, N, P, +1>(v, tw, L, t);
 #pragma unroll
   for (int q = 0; q < R; ++q) v[q] = mk(v[q].x * scale, v[q].y * scale);
-  T* dst = out + (size_t)b * N * N * N + (size_t)i1 * N + i2;
+  using RR = P1Rows<T, N, OWN>;
+  T* dst = out + (size_t)b * N * N * N + RR::col(i1) + i2;
 #pragma unroll
-  for (int q = 0; q < R; ++q) store_stream(reinterpret_cast<cx<T>*>(dst + (size_t)(t + q * TT) * N * N), v[q]);
+  for (int q = 0; q < R; ++q) store_stream(reinterpret_cast<cx<T>*>(dst + (t + q * TT) * RR::kPlane), v[q]);
   if (out32) {   // optional float32 rounding of the same output
     float* d32 = out32 + (size_t)b * N * N * N + (size_t)i1 * N + i2;
 #pragma unroll
@@ -216,14 +226,14 @@ k_p2(cx<T>* __restrict__ data, int batch, const cx<T>* __restrict__ tw, const So
   const int k0 = blockIdx.y;
   const int c = threadIdx.x % TY, t = threadIdx.x / TY;
   __shared__ cx<T> lds[N * TY];
-  cx<T>* base = data + ((size_t)fb * H + k0) * N * N + blockIdx.x * TY + c;
+  cx<T>* base = data + (size_t)fb * H * N * N + (size_t)k0 * SpecRows<N>::kPlane + blockIdx.x * TY + c;
   cx<T> v[R];
 #pragma unroll
-  for (int q = 0; q < R; ++q) v[q] = base[(size_t)(t + q * TT) * N];
+  for (int q = 0; q < R; ++q) v[q] = base[SpecRows<N>::col(t + q * TT)];
   LdsCol<T, TY> L{lds, c};
   fft<T, N, P, DIR>(v, tw, L, t);
 #pragma unroll
-  for (int q = 0; q < R; ++q) base[(size_t)(t + q * TT) * N] = v[q];
+  for (int q = 0; q < R; ++q) base[SpecRows<N>::col(t + q * TT)] = v[q];
 }
 
 // Axis-1 inverse pass of the split Hessian.  The axis-2 pass wrote C' = u/|n|^2 to slot 0, i n2 C'
@@ -303,7 +313,7 @@ k_p2_split(cx<T>* __restrict__ data, size_t fstride, int batch, const cx<T>* __r
   int t = threadIdx.x / TY;
   __shared__ cx<T> lds[N * TY];
   const int slot = role == 0 ? 0 : role == 1 ? 3 : 5;
-  const size_t off = ((size_t)b * H + k0) * N * N + blockIdx.x * TY + c;
+  const size_t off = (size_t)b * H * N * N + (size_t)k0 * SpecRows<N>::kPlane + blockIdx.x * TY + c;
   const cx<T>* src = data + slot * fstride + off;
   const T n0 = T(k0);
   const bool q0 = k0 == N / 2;
@@ -312,8 +322,8 @@ k_p2_split(cx<T>* __restrict__ data, size_t fstride, int batch, const cx<T>* __r
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     if constexpr (sizeof(T) == 4 ? DGP_P2S_STREAM_LOAD_F32 : DGP_P2S_STREAM_LOAD_F64)
-      v[q] = load_stream(&src[(size_t)(t + q * TT) * N]);
-    else v[q] = src[(size_t)(t + q * TT) * N];
+      v[q] = load_stream(&src[SpecRows<N>::col(t + q * TT)]);
+    else v[q] = src[SpecRows<N>::col(t + q * TT)];
   }
 #pragma unroll 1
   for (int o = 2 - role; o >= 0; --o) {
@@ -328,8 +338,8 @@ k_p2_split(cx<T>* __restrict__ data, size_t fstride, int batch, const cx<T>* __r
     cx<T>* dst = data + (slot + o) * fstride + off;
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      if constexpr (DGP_P2S_STREAM_STORE) store_stream(&dst[(size_t)(t + q * TT) * N], w[q]);
-      else dst[(size_t)(t + q * TT) * N] = w[q];
+      if constexpr (DGP_P2S_STREAM_STORE) store_stream(&dst[SpecRows<N>::col(t + q * TT)], w[q]);
+      else dst[SpecRows<N>::col(t + q * TT)] = w[q];
     }
   }
 }
@@ -358,7 +368,7 @@ k_p2_adj_split(cx<double>* __restrict__ data, size_t fstride, int batch, double 
   int t = threadIdx.x / TY;
   __shared__ cx<T> lds[N * TY];
   const int slot = role == 0 ? 0 : role == 1 ? 3 : 5;
-  const size_t off = ((size_t)b * H + k0) * N * N + blockIdx.x * TY + c;
+  const size_t off = (size_t)b * H * N * N + (size_t)k0 * SpecRows<N>::kPlane + blockIdx.x * TY + c;
   const T n0 = T(k0);
   const bool q0 = k0 == N / 2;
   LdsCol<T, TY> L{lds, c};
@@ -366,7 +376,7 @@ k_p2_adj_split(cx<double>* __restrict__ data, size_t fstride, int batch, double 
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     acc[q] = mk(T(0), T(0));
-    nx[q] = data[slot * fstride + off + (size_t)(t + q * TT) * N];
+    nx[q] = data[slot * fstride + off + SpecRows<N>::col(t + q * TT)];
   }
 #pragma unroll 1
   for (int i = 0; i < 3 - role; ++i) {
@@ -379,7 +389,7 @@ k_p2_adj_split(cx<double>* __restrict__ data, size_t fstride, int batch, double 
     if (i < 2 - role) {
       const cx<T>* src = data + (f + 1) * fstride + off;
 #pragma unroll
-      for (int q = 0; q < R; ++q) nx[q] = src[(size_t)(t + q * TT) * N];
+      for (int q = 0; q < R; ++q) nx[q] = src[SpecRows<N>::col(t + q * TT)];
     }
     fft<T, N, P, -1>(v, twq, L, t);
 #pragma unroll
@@ -399,7 +409,7 @@ k_p2_adj_split(cx<double>* __restrict__ data, size_t fstride, int batch, double 
   }
   cx<T>* dst = data + slot * fstride + off;
 #pragma unroll
-  for (int q = 0; q < R; ++q) dst[(size_t)(t + q * TT) * N] = acc[q];
+  for (int q = 0; q < R; ++q) dst[SpecRows<N>::col(t + q * TT)] = acc[q];
 }
 
 // Axis-1 inverse pass of the force mesh: the axis-2 pass wrote phi to slot 0 and g2 to slot 2;
@@ -421,13 +431,13 @@ k_p2_force_split(cx<T>* __restrict__ data, size_t fstride, int batch, int with_p
   int t = threadIdx.x / TY;
   __shared__ cx<T> lds[N * TY];
   const int slot = role == 0 ? 0 : 2;
-  const size_t off = ((size_t)b * H + k0) * N * N + blockIdx.x * TY + c;
+  const size_t off = (size_t)b * H * N * N + (size_t)k0 * SpecRows<N>::kPlane + blockIdx.x * TY + c;
   const cx<T>* src = data + slot * fstride + off;
   const T f0 = k0 == N / 2 ? T(0) : T(fk * double(k0));   // (c/H0)^2 k0
   LdsCol<T, TY> L{lds, c};
   cx<T> v[R];
 #pragma unroll
-  for (int q = 0; q < R; ++q) v[q] = src[(size_t)(t + q * TT) * N];
+  for (int q = 0; q < R; ++q) v[q] = src[SpecRows<N>::col(t + q * TT)];
   // outputs of role 0: o = 2 phi (slot 3, when asked for), 1 g1 (slot 1), 0 g0 (slot 0)
 #pragma unroll 1
   for (int o = role == 0 ? (with_phi ? 2 : 1) : 0; o >= 0; --o) {
@@ -445,7 +455,7 @@ k_p2_force_split(cx<T>* __restrict__ data, size_t fstride, int batch, int with_p
     fft<T, N, P, +1>(w, twq, L, t);
     cx<T>* dst = data + (role == 1 ? 2 : o == 2 ? 3 : o) * fstride + off;
 #pragma unroll
-    for (int q = 0; q < R; ++q) dst[(size_t)(t + q * TT) * N] = w[q];
+    for (int q = 0; q < R; ++q) dst[SpecRows<N>::col(t + q * TT)] = w[q];
   }
 }
 
@@ -466,7 +476,7 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
   const int row = blockIdx.x * RW + c;
   const bool valid = row < ROWS;
   const int rr = valid ? row : 0;
-  const int k0 = rr / N, k1 = rr % N;
+  const int k0 = SpecRows<N>::k0_of(rr), k1 = SpecRows<N>::i1_of(rr);
   __shared__ cx<T> lds[RW * LdsRow<T, N>::kStride];
   // twiddles: float32 from LDS (256^3 split pass 54 vs 46 us), float64 from the table into registers,
   // whose LDS exchanges bound the pass already (91 vs 97 us with the LDS copy)
@@ -478,17 +488,21 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
   // a row's N/R threads are consecutive lanes; when they fit in one wavefront its exchanges are wave-local
   LdsRow<T, N, (TT <= 64 && 64 % TT == 0 && DGP_P3_WAVE_SYNC)> L{lds, c};
   const size_t roff = (size_t)b * ROWS * N + (size_t)rr * N;
+  // (a caller's spectrum, FWD_ONLY's output and INV_ONLY's input, is in C order)
+  const size_t coff = (size_t)b * ROWS * N + ((size_t)k0 * N + k1) * N;
 
   cx<T> v[R];
   auto load_row = [&](const cx<T>* src) {
+    const size_t o = MODE == SPEC_INV_ONLY ? coff : roff;
 #pragma unroll
-    for (int q = 0; q < R; ++q) v[q] = valid ? src[roff + t + q * TT] : mk(T(0), T(0));
+    for (int q = 0; q < R; ++q) v[q] = valid ? src[o + t + q * TT] : mk(T(0), T(0));
     if constexpr (TWLDS) lds_barrier();
   };
   auto store_row = [&](cx<T>* dst, cx<T> (&w)[R]) {
     if (valid) {
+      const size_t o = MODE == SPEC_FWD_ONLY ? coff : roff;
 #pragma unroll
-      for (int q = 0; q < R; ++q) store_stream(&dst[roff + t + q * TT], w[q]);   // read by the next pass
+      for (int q = 0; q < R; ++q) store_stream(&dst[o + t + q * TT], w[q]);   // read by the next pass
     }
   };
   const double kf = cf.kf;
@@ -735,7 +749,7 @@ k_power(const cx<double>* __restrict__ in, const cx<double>* __restrict__ tw, Sp
 #pragma unroll
     for (int q = 0; q < R; ++q) v[q] = src[q * TT];
     fft<T, N, P, -1>(v, tw, L, t);
-    const int k0 = row / N, k1 = row % N, n1 = k1 < N / 2 ? k1 : k1 - N;
+    const int k0 = SpecRows<N>::k0_of(row), k1 = SpecRows<N>::i1_of(row), n1 = k1 < N / 2 ? k1 : k1 - N;
     const int s2 = k0 * k0 + n1 * n1;
     lds_barrier();
 #pragma unroll
@@ -752,7 +766,7 @@ k_power(const cx<double>* __restrict__ in, const cx<double>* __restrict__ tw, Sp
     for (int r = wv; r < RW; r += 4) {
       const int rw = tile * RW + r;
       if (rw >= ROWS) break;
-      const int r0 = rw / N, r1 = rw % N, m1 = r1 < N / 2 ? r1 : r1 - N;
+      const int r0 = SpecRows<N>::k0_of(rw), r1 = SpecRows<N>::i1_of(rw), m1 = r1 < N / 2 ? r1 : r1 - N;
       const int s = r0 * r0 + m1 * m1;
       const double mult = (r0 == 0 || r0 == N / 2) ? 1.0 : 2.0;
 #pragma unroll
@@ -797,16 +811,29 @@ k_power_final(const double* __restrict__ partial, int groups, int nbins, double*
 // ------------------------------------------------------------------ launchers
 template <typename T, int N, typename I = T>
 static void p1_fwd_n(const I* in, cx<T>* out, int batch, const SolveCtl* ctl, const cx<T>* tw, hipStream_t s,
-                     double qscale = 0.0, const int* bad = nullptr) {
+                     bool own = false, double qscale = 0.0, const int* bad = nullptr) {
   using G = P1Tile<T, N, Geo<T, N>::R>;
   dim3 grid(N / (2 * G::kTP), N, batch);
+  if constexpr (RealRows<T, N>::kG != N && std::is_same<T, I>::value) {
+    if (own) {
+      hipLaunchKernelGGL((k_p1_fwd<T, N, I, true>), grid, dim3(G::kThreads), 0, s, in, out, tw, ctl, qscale, bad);
+      return;
+    }
+  }
   hipLaunchKernelGGL((k_p1_fwd<T, N, I>), grid, dim3(G::kThreads), 0, s, in, out, tw, ctl, qscale, bad);
 }
 template <typename T, int N>
 static void p1_inv_n(const cx<T>* in, T* out, int batch, const SolveCtl* ctl, const cx<T>* tw, float* out32,
-                     double scale, double* part, hipStream_t s) {
+                     double scale, double* part, bool own, hipStream_t s) {
   using G = P1Tile<T, N, Geo<T, N>::R>;
   dim3 grid(N / (2 * G::kTP), N, batch);
+  if constexpr (RealRows<T, N>::kG != N) {
+    if (own) {
+      hipLaunchKernelGGL((k_p1_inv<T, N, true>), grid, dim3(G::kThreads), 0, s, in, out, tw, ctl, out32, T(scale),
+                         part);
+      return;
+    }
+  }
   hipLaunchKernelGGL((k_p1_inv<T, N>), grid, dim3(G::kThreads), 0, s, in, out, tw, ctl, out32, T(scale), part);
 }
 template <typename T, int N>
@@ -874,9 +901,9 @@ const cx<T>* twiddles(int n);   // defined in api.cpp: device table exp(-2 pi i 
   }
 
 template <typename T>
-void launch_p1_fwd(int n, const T* in, cx<T>* out, int batch, const SolveCtl* ctl, hipStream_t s) {
+void launch_p1_fwd(int n, const T* in, cx<T>* out, int batch, const SolveCtl* ctl, hipStream_t s, bool own) {
   const cx<T>* tw = twiddles<T>(n);
-#define C(NN) p1_fwd_n<T, NN>(in, out, batch, ctl, tw, s)
+#define C(NN) p1_fwd_n<T, NN>(in, out, batch, ctl, tw, s, own)
   DGP_DISPATCH_N(n, C)
 #undef C
 }
@@ -889,15 +916,15 @@ void launch_p1_fwd_from64(int n, const double* in, cx<float>* out, int batch, co
 template <typename T>
 void launch_p1_fwd_counts(int n, const long long* grid, double qscale, const int* bad, cx<T>* out, hipStream_t s) {
   const cx<T>* tw = twiddles<T>(n);
-#define C(NN) p1_fwd_n<T, NN, long long>(grid, out, 1, nullptr, tw, s, qscale, bad)
+#define C(NN) p1_fwd_n<T, NN, long long>(grid, out, 1, nullptr, tw, s, false, qscale, bad)
   DGP_DISPATCH_N(n, C)
 #undef C
 }
 template <typename T>
 void launch_p1_inv(int n, const cx<T>* in, T* out, int batch, const SolveCtl* ctl, hipStream_t s, float* out32,
-                   double scale, double* part) {
+                   double scale, double* part, bool own) {
   const cx<T>* tw = twiddles<T>(n);
-#define C(NN) p1_inv_n<T, NN>(in, out, batch, ctl, tw, out32, scale, part, s)
+#define C(NN) p1_inv_n<T, NN>(in, out, batch, ctl, tw, out32, scale, part, own, s)
   DGP_DISPATCH_N(n, C)
 #undef C
 }
@@ -975,14 +1002,14 @@ int p3_row_groups(int n) {   // row groups of the float64 axis-2 pass (bounds th
   return r;
 }
 
-template void launch_p1_fwd<double>(int, const double*, cx<double>*, int, const SolveCtl*, hipStream_t);
-template void launch_p1_fwd<float>(int, const float*, cx<float>*, int, const SolveCtl*, hipStream_t);
+template void launch_p1_fwd<double>(int, const double*, cx<double>*, int, const SolveCtl*, hipStream_t, bool);
+template void launch_p1_fwd<float>(int, const float*, cx<float>*, int, const SolveCtl*, hipStream_t, bool);
 template void launch_p1_fwd_counts<double>(int, const long long*, double, const int*, cx<double>*, hipStream_t);
 template void launch_p1_fwd_counts<float>(int, const long long*, double, const int*, cx<float>*, hipStream_t);
 template void launch_p1_inv<double>(int, const cx<double>*, double*, int, const SolveCtl*, hipStream_t, float*,
-                                    double, double*);
+                                    double, double*, bool);
 template void launch_p1_inv<float>(int, const cx<float>*, float*, int, const SolveCtl*, hipStream_t, float*,
-                                   double, double*);
+                                   double, double*, bool);
 template void launch_p2<double>(int, cx<double>*, int, int, int, const SolveCtl*, hipStream_t);
 template void launch_p2<float>(int, cx<float>*, int, int, int, const SolveCtl*, hipStream_t);
 template void launch_p2_split<double>(int, cx<double>*, size_t, int, const SolveCtl*, hipStream_t);

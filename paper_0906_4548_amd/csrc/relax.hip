@@ -205,9 +205,9 @@ k_relax(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf, c
   __shared__ cx<T> twl[N];
   for (int i = threadIdx.x; i < N; i += G::kThreads) twl[i] = tw[i];
 
-  const size_t col = (size_t)b * H * N * N + (size_t)i1 * N + i2;
+  const size_t col = (size_t)b * H * N * N + SpecRows<N>::col(i1) + i2;
   typedef float f4 __attribute__((ext_vector_type(4)));
-  const size_t col0 = (size_t)b * H * N * N + (size_t)i1 * N + (size_t)tile * TP * 2;
+  const size_t col0 = (size_t)b * H * N * N + SpecRows<N>::col(i1) + (size_t)tile * TP * 2;
   // element q of thread t is row e = t + q TT of the Hermitian-extended column pair; rows e > N/2
   // come from row N - e (conjugated when used); streaming loads (the last use of these spectra in
   // the pass).  With paired lanes, threads t > TT/2 load their elements in reverse slot order, so
@@ -222,7 +222,7 @@ k_relax(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf, c
       const bool rev = PAIRED && t > TT / 2;
       const int e = t + (rev ? R - 1 - q : q) * TT;
       const unsigned r = e <= N / 2 ? e : N - e;
-      const f4* a = reinterpret_cast<const f4*>(src + (r * unsigned(N * N) + 2u * c) * unsigned(sizeof(cx<T>)));
+      const f4* a = reinterpret_cast<const f4*>(src + (r * SpecRows<N>::kPlane + 2u * c) * unsigned(sizeof(cx<T>)));
       const f4 x = __builtin_nontemporal_load(a);
       pd[q][0] = mk(T(x.x), T(x.y));
       pd[q][1] = mk(T(x.z), T(x.w));
@@ -284,15 +284,15 @@ k_relax(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf, c
     }
   }
   // pointwise residual and update; v holds Nf (field addresses formed after the field loop)
-  const T* uin = ubuf + ((size_t)cur * cfg.batch + b) * N3 + (size_t)i1 * N + i2;
-  const T* sp = sfield + (size_t)b * N3 + (size_t)i1 * N + i2;
+  const T* uin = ubuf + ((size_t)cur * cfg.batch + b) * N3 + RealRows<T, N>::col(i1) + i2;
+  const T* sp = sfield + (size_t)b * N3 + RealRows<T, N>::col(i1) + i2;
   const PointCoef pc = point_coef(cfg, mean_u[b]);
-  T* uout = ubuf + ((size_t)nxt * cfg.batch + b) * N3 + (size_t)i1 * N + i2;
+  T* uout = ubuf + ((size_t)nxt * cfg.batch + b) * N3 + RealRows<T, N>::col(i1) + i2;
   double abs_r = 0.0;
   int nbad = 0;
 #pragma unroll
   for (int q = 0; q < R; ++q) {
-    const size_t off = (size_t)(t + q * TT) * N * N;
+    const size_t off = (t + q * TT) * RealRows<T, N>::kPlane;
     up[q] = *reinterpret_cast<const cx<T>*>(uin + off);
     spv[q] = *reinterpret_cast<const cx<T>*>(sp + off);
   }
@@ -309,7 +309,7 @@ k_relax(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf, c
   if constexpr (RG::kRemat) asm volatile("" : "+v"(t), "+v"(c));   // the epilogue's addresses from here
 #pragma unroll
   for (int q = 0; q < R; ++q) {
-    const size_t off = (size_t)(t + q * TT) * N * N;
+    const size_t off = (t + q * TT) * RealRows<T, N>::kPlane;
     const cx<T> o = mk(T(un[q][0]), T(un[q][1]));
     store_stream(reinterpret_cast<cx<T>*>(uout + off), o);   // read again next pass only
     v[q] = o;
@@ -334,8 +334,8 @@ k_relax(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf, c
   for (int k = t; k < H; k += TT) {
     const cx<T> zk = lds[k * TP + c];
     const cx<T> zn = lds[((N - k) & (N - 1)) * TP + c];
-    dst[(size_t)k * N * N] = mk(T(0.5) * (zk.x + zn.x), T(0.5) * (zk.y - zn.y));
-    dst[(size_t)k * N * N + 1] = mk(T(0.5) * (zk.y + zn.y), T(0.5) * (zn.x - zk.x));
+    dst[(size_t)k * SpecRows<N>::kPlane] = mk(T(0.5) * (zk.x + zn.x), T(0.5) * (zk.y - zn.y));
+    dst[(size_t)k * SpecRows<N>::kPlane + 1] = mk(T(0.5) * (zk.y + zn.y), T(0.5) * (zn.x - zk.x));
   }
   // per-wavefront sums added in wavefront order (deterministic)
   if (threadIdx.x == 0) {
@@ -459,7 +459,7 @@ k_relax_w(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf,
     twp = twl;
   }
 
-  const size_t col0 = (size_t)b * H * NN + (size_t)i1 * N + i2;
+  const size_t col0 = (size_t)b * H * NN + SpecRows<N>::col(i1) + i2;
   cx<T> pf[NPF][2];
   // every thread loads NPF pairs, indices past the tile clamped to its last pair, so the
   // staging registers are assigned unconditionally and stay in registers
@@ -469,7 +469,7 @@ k_relax_w(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf,
     for (int r = 0; r < NPF; ++r) {
       const int idx = min(int(threadIdx.x) + r * NT, H * TP - 1);
       const int k = idx / TP, p = idx % TP;
-      const cx<T>* q = src + (size_t)k * NN + 2 * p;
+      const cx<T>* q = src + (size_t)k * SpecRows<N>::kPlane + 2 * p;
       pf[r][0] = mk(q[0].x, q[0].y);   // member-wise: a 16-byte struct copy would stay in private memory
       pf[r][1] = mk(q[1].x, q[1].y);
     }
@@ -546,15 +546,15 @@ k_relax_w(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf,
     // inverse transform (first barrier); the second barrier orders the reads before the forward
     // transform's exchanges in tile 1
     constexpr int NU = (N * TP + NT - 1) / NT;
-    const T* ur = ubuf + ((size_t)cur * cfg.batch + b) * N3 + (size_t)i1 * N + i2;
-    const T* sr = sfield + (size_t)b * N3 + (size_t)i1 * N + i2;
+    const T* ur = ubuf + ((size_t)cur * cfg.batch + b) * N3 + RealRows<T, N>::col(i1) + i2;
+    const T* sr = sfield + (size_t)b * N3 + RealRows<T, N>::col(i1) + i2;
     cx<T> lu[NU], ls[NU];
 #pragma unroll
     for (int r = 0; r < NU; ++r) {
       const int idx = min(int(threadIdx.x) + r * NT, N * TP - 1);
       const int e = idx / TP, p = idx % TP;
-      lu[r] = *reinterpret_cast<const cx<T>*>(ur + (size_t)e * NN + 2 * p);
-      ls[r] = *reinterpret_cast<const cx<T>*>(sr + (size_t)e * NN + 2 * p);
+      lu[r] = *reinterpret_cast<const cx<T>*>(ur + e * RealRows<T, N>::kPlane + 2 * p);
+      ls[r] = *reinterpret_cast<const cx<T>*>(sr + e * RealRows<T, N>::kPlane + 2 * p);
     }
     T* sst = reinterpret_cast<T*>(lds + W::kTile);
     lds_barrier();
@@ -576,13 +576,13 @@ k_relax_w(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf,
     }
     lds_barrier();
   } else {
-    const T* uin = ubuf + ((size_t)cur * cfg.batch + b) * N3 + (size_t)i1 * N + i2 + 2 * c;
-    const T* sp = sfield + (size_t)b * N3 + (size_t)i1 * N + i2 + 2 * c;
+    const T* uin = ubuf + ((size_t)cur * cfg.batch + b) * N3 + RealRows<T, N>::col(i1) + i2 + 2 * c;
+    const T* sp = sfield + (size_t)b * N3 + RealRows<T, N>::col(i1) + i2 + 2 * c;
 #pragma unroll
     for (int q = 0; q < R; ++q) {
       const int e = t + q * TT;
-      up[q] = *reinterpret_cast<const cx<T>*>(uin + (size_t)e * NN);
-      spv[q] = *reinterpret_cast<const cx<T>*>(sp + (size_t)e * NN);
+      up[q] = *reinterpret_cast<const cx<T>*>(uin + e * RealRows<T, N>::kPlane);
+      spv[q] = *reinterpret_cast<const cx<T>*>(sp + e * RealRows<T, N>::kPlane);
     }
   }
   double un[R][2];
@@ -608,11 +608,11 @@ k_relax_w(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf,
   }
   lds_barrier();
   // u^(n+1) out of tile 0 (coalesced); the spectrum into tile 1, column-major with one pad
-  T* uout = ubuf + ((size_t)nxt * cfg.batch + b) * N3 + (size_t)i1 * N + i2;
+  T* uout = ubuf + ((size_t)nxt * cfg.batch + b) * N3 + RealRows<T, N>::col(i1) + i2;
   for (int idx = threadIdx.x; idx < N * TP; idx += NT) {
     const int e = idx / TP, p = idx % TP;
     const cx<T> o = mk(ust[e * (2 * TP + 1) + 2 * p], ust[e * (2 * TP + 1) + 2 * p + 1]);
-    *reinterpret_cast<cx<T>*>(uout + (size_t)e * NN + 2 * p) = o;
+    *reinterpret_cast<cx<T>*>(uout + e * RealRows<T, N>::kPlane + 2 * p) = o;
   }
   cx<T>* zt = lds + W::kTile;
 #pragma unroll
@@ -623,8 +623,8 @@ k_relax_w(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf,
     const int k = idx / TP, p = idx % TP;
     const cx<T> zk = zt[p * (N + 1) + k];
     const cx<T> zn = zt[p * (N + 1) + ((N - k) & (N - 1))];
-    dst[(size_t)k * NN + 2 * p] = mk(T(0.5) * (zk.x + zn.x), T(0.5) * (zk.y - zn.y));
-    dst[(size_t)k * NN + 2 * p + 1] = mk(T(0.5) * (zk.y + zn.y), T(0.5) * (zn.x - zk.x));
+    dst[(size_t)k * SpecRows<N>::kPlane + 2 * p] = mk(T(0.5) * (zk.x + zn.x), T(0.5) * (zk.y - zn.y));
+    dst[(size_t)k * SpecRows<N>::kPlane + 2 * p + 1] = mk(T(0.5) * (zk.y + zn.y), T(0.5) * (zn.x - zk.x));
   }
   if (threadIdx.x == 0) {
     double sr = 0.0;
@@ -1041,12 +1041,35 @@ __device__ __forceinline__ int handoff_buffer(const SolveCtl& C) {
   return (C.status == 0 && C.final_bad == 0) ? C.out : C.result;
 }
 
+// log2 of the row group of a solve's own fields (RealRows) at mesh size 2^logn
+template <typename T>
+__host__ __device__ constexpr int own_group(int logn) {
+  return sizeof(T) == 8 && (1 << logn) >= kRowGroupMin ? __builtin_ctz(kRowGroup) : logn;
+}
+// where the element i (C order) of such a field lies, for row groups of 2^lg
+__device__ __forceinline__ size_t own_index(size_t i, int logn, int lg) {
+  if (lg == logn) return i;
+  const size_t n1 = (size_t(1) << logn) - 1, i2 = i & n1, i1 = (i >> logn) & n1, i0 = i >> (2 * logn);
+  return (((((i1 >> lg) << logn) + i0) << lg) + (i1 & ((size_t(1) << lg) - 1))) << logn | i2;
+}
+
+// copies a field of the caller's into the solve's own row order
+__global__ void __launch_bounds__(256)
+k_take_field(const double* __restrict__ in, double* __restrict__ out, int logn) {
+  const size_t n3 = size_t(1) << (3 * logn), b = (size_t)blockIdx.y * n3;
+  const int lg = own_group<double>(logn);
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n3; i += (size_t)gridDim.x * 256)
+    out[b + own_index(i, logn, lg)] = in[b + i];
+}
+
 // copies the selected buffer; with part != nullptr it also leaves per-workgroup sums of |x|
 // and x (the layout k_absmean_final reads)
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_take_buffer(const SolveCtl* __restrict__ ctl, const T* __restrict__ U, int batch, size_t n3, double* __restrict__ dst,
+k_take_buffer(const SolveCtl* __restrict__ ctl, const T* __restrict__ U, int batch, int logn, double* __restrict__ dst,
               int handoff, double* __restrict__ part) {
+  const size_t n3 = size_t(1) << (3 * logn);
+  const int sg = own_group<T>(logn), dg = handoff ? own_group<double>(logn) : logn;
   const int b = blockIdx.y;
   const int src = handoff ? handoff_buffer(ctl[b]) : ctl[b].result;
   if (src < 0) return;   // (handoff only: no reduction is requested there)
@@ -1054,8 +1077,8 @@ k_take_buffer(const SolveCtl* __restrict__ ctl, const T* __restrict__ U, int bat
   double* out = dst + (size_t)b * n3;
   double sa = 0.0, sm = 0.0;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n3; i += (size_t)gridDim.x * 256) {
-    const double v = double(in[i]);
-    out[i] = v;
+    const double v = double(in[own_index(i, logn, sg)]);
+    out[own_index(i, logn, dg)] = v;
     sa += fabs(v);
     sm += v;
   }
@@ -1102,10 +1125,15 @@ static unsigned copy_groups(size_t n3) {
   return unsigned(g > 4096 ? 4096 : g);
 }
 
-void launch_handoff(SolveCtl* ctl, SolveCtl* other, const float* U32, int batch, size_t n3, double* dst, hipStream_t s) {
-  hipLaunchKernelGGL((k_take_buffer<float>), dim3(copy_groups(n3), batch), dim3(256), 0, s, ctl, U32, batch, n3, dst,
-                     1, nullptr);
+void launch_handoff(SolveCtl* ctl, SolveCtl* other, const float* U32, int batch, int n, double* dst, hipStream_t s) {
+  hipLaunchKernelGGL((k_take_buffer<float>), dim3(copy_groups((size_t)n * n * n), batch), dim3(256), 0, s, ctl, U32,
+                     batch, __builtin_ctz(n), dst, 1, nullptr);
   hipLaunchKernelGGL(k_ctl_phase2, dim3(batch), dim3(64), 0, s, ctl, other);
+}
+
+void launch_take_field(int n, const double* in, double* out, int batch, hipStream_t s) {
+  hipLaunchKernelGGL(k_take_field, dim3(copy_groups((size_t)n * n * n), batch), dim3(256), 0, s, in, out,
+                     __builtin_ctz(n));
 }
 
 // ------------------------------------------------------------------ spherical approximation
@@ -1174,16 +1202,18 @@ void launch_spherical(size_t n3, int batch, const double* S, double* u, double a
 }
 
 template <typename T>
-void launch_take_result(const SolveCtl* ctl, const T* U, int batch, size_t n3, double* dst, double* scratch,
+void launch_take_result(const SolveCtl* ctl, const T* U, int batch, int n, double* dst, double* scratch,
                         double* mean, hipStream_t s) {
+  const size_t n3 = (size_t)n * n * n;
   const int g = absmean_groups(n3);
-  hipLaunchKernelGGL((k_take_buffer<T>), dim3(g, batch), dim3(256), 0, s, ctl, U, batch, n3, dst, 0, scratch);
+  hipLaunchKernelGGL((k_take_buffer<T>), dim3(g, batch), dim3(256), 0, s, ctl, U, batch, __builtin_ctz(n), dst, 0,
+                     scratch);
   hipLaunchKernelGGL(k_absmean_final, dim3(batch), dim3(256), 0, s, scratch, g, n3, nullptr, mean);
 }
 
-template void launch_take_result<double>(const SolveCtl*, const double*, int, size_t, double*, double*, double*,
+template void launch_take_result<double>(const SolveCtl*, const double*, int, int, double*, double*, double*,
                                          hipStream_t);
-template void launch_take_result<float>(const SolveCtl*, const float*, int, size_t, double*, double*, double*,
+template void launch_take_result<float>(const SolveCtl*, const float*, int, int, double*, double*, double*,
                                         hipStream_t);
 
 void launch_ctl_init(SolveCtl* ctl, SolveCtl* other, const double* part, int groups, size_t n3, int batch,

@@ -91,3 +91,65 @@ def test_interp_mesh_gradient_chunks(dgp, np_, block, nc):
         gm = torch.zeros((nc, n, n, n), dtype=torch.float64, device="cuda")
         plan.interp_backward(None, to_dev(pos), to_dev(g), None, gm)
     assert rel_l2(gm.cpu().numpy(), ref) <= 1e-12
+
+
+# batches whose elements share a workgroup's plane or leave it ragged; every element alone runs the same
+# arithmetic (float64: last-place rounding; mixed: the float64 polish from float32 iterates that agree)
+@pytest.mark.parametrize("n,batch", [(8, 3), (16, 11), (32, 7), (64, 3), (128, 2)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_solve_batch_elements_and_source_mean(dgp, n, batch, prec):
+    box, op = 2.0 * n, oracle_params()
+    d = np.stack([inputs.lognormal_delta(n, box, 0.8, 40 + b) for b in range(batch)])
+    p = gpu_params(dgp, tol=1e-10)
+    u = torch.zeros((batch, n, n, n), dtype=torch.float64, device="cuda")
+    with dgp.Plan(n, box, batch=batch, precision=prec) as plan:
+        _, info = plan.solve_field(p, to_dev(d), u)
+    for b in range(batch):
+        u1 = torch.zeros((1, n, n, n), dtype=torch.float64, device="cuda")
+        with dgp.Plan(n, box, precision=prec) as plan:
+            _, one = plan.solve_field(p, to_dev(d[b:b + 1]), u1)
+        assert one[0]["passes"] == info[b]["passes"] and one[0]["status"] == info[b]["status"]
+        assert rel_l2(u[b].cpu().numpy(), u1[0].cpu().numpy()) <= (1e-12 if prec == 0 else 1e-9)
+        _, ref = fld.solve(d[b], box, op, fixed_iters=0)
+        assert abs(info[b]["eps"] - ref.eps) <= 1e-12 * ref.eps
+
+
+# the row groups of 512^3: raw transforms and the power spectrum against torch, the solve's own fields
+# through their copies in and out (the same iterates from a warm start; a rolled input, also spherical)
+def test_row_groups_512(dgp):
+    n, box = 512, 1024.0
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    f = torch.randn((n, n, n), dtype=torch.float64, device="cuda", generator=gen) * 0.1
+    ref = torch.fft.rfftn(f, dim=(1, 2, 0))
+    spec = torch.zeros((n // 2 + 1, n, n), dtype=torch.complex128, device="cuda")
+
+    def rel(x, y):
+        return float((x - y).norm() / y.norm())
+    for prec, tol in ((0, 1e-13), (1, 1e-5)):
+        with dgp.Plan(n, box, precision=prec) as plan:
+            plan.fft_forward(f, spec)
+            assert rel(spec, ref) <= tol
+            back = torch.zeros_like(f)
+            plan.fft_inverse(spec, back)
+            assert rel(back, f) <= tol
+    w = torch.full((n // 2 + 1, 1, 1), 2.0, dtype=torch.float64, device="cuda")
+    w[0] = w[-1] = 1.0
+    m = torch.fft.fftfreq(n, 1.0 / n, dtype=torch.float64, device="cuda")
+    k2 = m[:n // 2 + 1, None, None] ** 2 + m[None, :, None] ** 2 + m[None, None, :] ** 2
+    total = float((w * ref.abs() ** 2 * ((k2 >= 1) & (k2 < (n // 2) ** (12 / 7)))).sum())   # six bins of seven
+    del ref, spec, k2, w
+    with dgp.Plan(n, box) as plan:
+        pk, cnt = plan.power_spectrum(gpu_params(dgp), f, nbins=7)
+        got = float(np.sum((pk * cnt)[..., :6])) * n ** 6 / box ** 3
+        assert abs(got - total) <= 1e-11 * total
+        u2, u1 = torch.zeros_like(f), torch.zeros_like(f)
+        plan.solve_field(gpu_params(dgp, tol=0.0, max_iter=2), f, u2)
+        plan.solve_field(gpu_params(dgp, tol=0.0, max_iter=1), f, u1)
+        plan.solve_field(gpu_params(dgp, tol=0.0, max_iter=1, init=dgp.INIT_WARM), f, u1)
+        assert rel(u1, u2) <= 1e-12
+        roll = ((1, 6, 3), (0, 1, 2))
+        fr = f.roll(*roll).contiguous()
+        for kw in ({"tol": 0.0, "max_iter": 2}, {"spherical": 1, "init": dgp.INIT_ZERO}):
+            plan.solve_field(gpu_params(dgp, **kw), f, u1)
+            plan.solve_field(gpu_params(dgp, **kw), fr, u2)
+            assert rel(u2, u1.roll(*roll)) <= 1e-12
