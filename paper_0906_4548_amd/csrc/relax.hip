@@ -841,32 +841,42 @@ k_finalize(const double* __restrict__ partial, int groups, SolveCtl* __restrict_
   }
 }
 
-// Per-batch mean of |x| and of x, deterministic two-level reduction.
+// Per-batch sums of |x| and of x per workgroup, the first level of a deterministic two-level reduction.
+// A plain read: eight independent loads per thread are in flight (256^3 counts: the mean of 256^3 counts, deposit 444 -> 433 us).
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_absmean_partial(const T* __restrict__ x, size_t n3, double* __restrict__ part) {
   const int b = blockIdx.y;
   const T* xb = x + (size_t)b * n3;
+  constexpr int U = 8;
+  const size_t step = (size_t)gridDim.x * 256;
+  size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   double sa = 0.0, sm = 0.0;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n3; i += (size_t)gridDim.x * 256) {
-    const double v = double(xb[i]);
-    sa += fabs(v);
-    sm += v;
-  }
-  __shared__ double ra[256], rm[256];
-  ra[threadIdx.x] = sa;
-  rm[threadIdx.x] = sm;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      ra[threadIdx.x] += ra[threadIdx.x + s];
-      rm[threadIdx.x] += rm[threadIdx.x + s];
+  for (; i + (U - 1) * step < n3; i += U * step) {
+    T v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = xb[i + u * step];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      sa += fabs(double(v[u]));
+      sm += double(v[u]);
     }
-    __syncthreads();
   }
+  for (; i < n3; i += step) {
+    sa += fabs(double(xb[i]));
+    sm += double(xb[i]);
+  }
+  sa = wave_sum<64>(sa);
+  sm = wave_sum<64>(sm);
+  __shared__ double ra[4], rm[4];
+  if ((threadIdx.x & 63) == 0) {
+    ra[threadIdx.x >> 6] = sa;
+    rm[threadIdx.x >> 6] = sm;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    part[((size_t)b * gridDim.x + blockIdx.x) * 2] = ra[0];
-    part[((size_t)b * gridDim.x + blockIdx.x) * 2 + 1] = rm[0];
+    part[((size_t)b * gridDim.x + blockIdx.x) * 2] = ((ra[0] + ra[1]) + ra[2]) + ra[3];
+    part[((size_t)b * gridDim.x + blockIdx.x) * 2 + 1] = ((rm[0] + rm[1]) + rm[2]) + rm[3];
   }
 }
 
