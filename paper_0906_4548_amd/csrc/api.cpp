@@ -604,7 +604,8 @@ static SolveCtl* ctl_now(dgp_plan* pl) { return pl->ctl + (size_t)pl->ctl_set * 
 static SolveCtl* ctl_other(dgp_plan* pl) { return pl->ctl + (size_t)(1 - pl->ctl_set) * pl->batch; }
 
 // enqueue one relaxation pass on the iterate whose axis-0 spectrum is in spec_u.  decided: the previous
-// pass (if any) has been decided; otherwise this pass's plane launch decides it (meshes of plane_ok only).  decide: decide this pass with a launch of its own.
+// pass (if any) has been decided; otherwise this pass's plane launch decides it (meshes of plane_ok
+// only).  decide: decide this pass with a launch of its own.
 template <typename T>
 static int enqueue_pass(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const SolveCfg& cfg, bool decided, bool decide,
                         hipStream_t s) {

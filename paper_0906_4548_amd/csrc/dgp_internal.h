@@ -217,6 +217,7 @@ void launch_p3(int n, SpecMode mode, const cx<T>* in, size_t in_stride, int nin,
 // whose plane fits the LDS (plane_ok); `in` as the axis-0 pass left it, output o to out + o * out_stride
 template <typename T>
 bool plane_ok(int n);
+constexpr int kPlaneMax = 64;   // the largest such mesh, in either precision
 // convergence decision of the previous pass, made by a launch_plane that starts the next one: the pass's
 // partial sums, the control blocks it ran with (prev) and those that the decision goes to (next)
 struct PassDecision {

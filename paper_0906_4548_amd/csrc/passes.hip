@@ -845,9 +845,11 @@ static void p2_n(cx<T>* data, int nf, int batch, int dir, const SolveCtl* ctl, c
 }
 template <typename T, int N>
 static void p2_split_n(cx<T>* data, size_t fstride, int batch, const SolveCtl* ctl, const cx<T>* tw, hipStream_t s) {
-  using G = typename P2SGeo<T, N>::G;
-  dim3 grid(N / G::kTY, N / 2 + 1, 3 * batch);
-  hipLaunchKernelGGL((k_p2_split<T, N>), grid, dim3(G::kThreads), 0, s, data, fstride, batch, tw, ctl);
+  if constexpr (N > kPlaneMax) {   // (the plane kernels serve the smaller meshes)
+    using G = typename P2SGeo<T, N>::G;
+    dim3 grid(N / G::kTY, N / 2 + 1, 3 * batch);
+    hipLaunchKernelGGL((k_p2_split<T, N>), grid, dim3(G::kThreads), 0, s, data, fstride, batch, tw, ctl);
+  }
 }
 template <int N>
 static void p2_adj_split_n(cx<double>* data, size_t fstride, int batch, double lam2, const SolveCtl* ctl,
@@ -859,9 +861,11 @@ static void p2_adj_split_n(cx<double>* data, size_t fstride, int batch, double l
 template <typename T, int N>
 static void p2_force_split_n(cx<T>* data, size_t fstride, int batch, int with_phi, double fk, const cx<T>* tw,
                              hipStream_t s) {
-  using G = typename P2SGeo<T, N>::G;
-  dim3 grid(N / G::kTY, N / 2 + 1, 2 * batch);
-  hipLaunchKernelGGL((k_p2_force_split<T, N>), grid, dim3(G::kThreads), 0, s, data, fstride, batch, with_phi, fk, tw);
+  if constexpr (N > kPlaneMax) {
+    using G = typename P2SGeo<T, N>::G;
+    dim3 grid(N / G::kTY, N / 2 + 1, 2 * batch);
+    hipLaunchKernelGGL((k_p2_force_split<T, N>), grid, dim3(G::kThreads), 0, s, data, fstride, batch, with_phi, fk, tw);
+  }
 }
 template <typename T, int N>
 static void p3_n(SpecMode mode, const cx<T>* in, size_t is, cx<T>* out, size_t os, int batch, const SpecCoef& cf,
@@ -873,14 +877,20 @@ static void p3_n(SpecMode mode, const cx<T>* in, size_t is, cx<T>* out, size_t o
 #define DGP_P3(M) hipLaunchKernelGGL((k_p3<T, N, M>), grid, blk, 0, s, in, is, out, os, tw, cf, bc, mean, ctl)
   switch (mode) {
     case SPEC_SOURCE: DGP_P3(SPEC_SOURCE); break;
-    case SPEC_CFIELD: DGP_P3(SPEC_CFIELD); break;
-    case SPEC_FORCES: DGP_P3(SPEC_FORCES); break;
     case SPEC_POWER_GRAD: DGP_P3(SPEC_POWER_GRAD); break;
     case SPEC_ADJ_COMBINE3: DGP_P3(SPEC_ADJ_COMBINE3); break;
     case SPEC_COPY: DGP_P3(SPEC_COPY); break;
     case SPEC_FWD_ONLY: DGP_P3(SPEC_FWD_ONLY); break;
     case SPEC_INV_ONLY: DGP_P3(SPEC_INV_ONLY); break;
-    case SPEC_HSPLIT: DGP_P3(SPEC_HSPLIT); break;
+    case SPEC_CFIELD:
+    case SPEC_FORCES:
+    case SPEC_HSPLIT:
+      if constexpr (N > kPlaneMax) {   // (the plane kernels serve the smaller meshes)
+        if (mode == SPEC_CFIELD) DGP_P3(SPEC_CFIELD);
+        else if (mode == SPEC_FORCES) DGP_P3(SPEC_FORCES);
+        else DGP_P3(SPEC_HSPLIT);
+      }
+      break;
   }
 #undef DGP_P3
 }

@@ -238,7 +238,7 @@ static void plane_n(SpecMode mode, const cx<T>* in, size_t is, cx<T>* out, size_
 }
 
 template <typename T>
-bool plane_ok(int n) { return n <= 64; }
+bool plane_ok(int n) { return n <= kPlaneMax; }
 
 template <typename T>
 void launch_plane(int n, SpecMode mode, const cx<T>* in, size_t in_stride, cx<T>* out, size_t out_stride, int nout,

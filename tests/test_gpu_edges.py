@@ -153,3 +153,27 @@ def test_row_groups_512(dgp):
             plan.solve_field(gpu_params(dgp, **kw), f, u1)
             plan.solve_field(gpu_params(dgp, **kw), fr, u2)
             assert rel(u2, u1.roll(*roll)) <= 1e-12
+
+
+# gathers and the deposit's adjoint by chunks: compact (staged in LDS) and spread (direct) ones, a ragged
+# last chunk, one particle
+@pytest.mark.parametrize("np_,block", [(1, 0), (255, 8), (2 ** 14 + 3, 8), (2 ** 14 + 3, 0)])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_gather_chunks(dgp, np_, block, fp32):
+    from oracle import adjoint, pm
+    n, box, side = 32, 64.0, 32
+    pos = inputs.zeldovich_load(side, box, 12, rms_disp=0.8, block=block)[0][:, :np_].copy()
+    pos = pos.astype(np.float32) if fp32 else pos
+    ref_pos = pos.astype(np.float64)
+    g = np.random.default_rng(np_).standard_normal((3, np_))
+    mesh = np.random.default_rng(3).standard_normal((3, n, n, n))
+    with dgp.Plan(n, box) as plan:
+        tp = torch.from_numpy(pos).cuda()
+        out = torch.zeros((3, np_), dtype=torch.float64, device="cuda")
+        plan.interp(to_dev(mesh), tp, out)
+        gp = torch.zeros((3, np_), dtype=torch.float64, device="cuda")
+        plan.interp_backward(to_dev(mesh), tp, to_dev(g), gp, None)
+    ref = pm.cic_interpolate(mesh, ref_pos, box)
+    refp, _ = adjoint.interp_backward(mesh, ref_pos, g, box)
+    assert rel_l2(out.cpu().numpy(), ref) <= 1e-12
+    assert rel_l2(gp.cpu().numpy(), refp) <= 1e-12
