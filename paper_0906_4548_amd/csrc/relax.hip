@@ -369,13 +369,13 @@ k_relax(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf, c
 #ifndef DGP_RELAXW_MINW_F64
 #define DGP_RELAXW_MINW_F64 3
 #endif
-// column pairs of the float64 kernel from N = 512 on
+// column pairs of the float64 kernel from N = 256 on
 #ifndef DGP_RELAXW_TP_WIDE_F64
 #define DGP_RELAXW_TP_WIDE_F64 8
 #endif
 // smallest N whose float64 relaxation kernel reads its twiddles from LDS
 #ifndef DGP_RELAXW_TWLDS_MIN
-#define DGP_RELAXW_TWLDS_MIN 512
+#define DGP_RELAXW_TWLDS_MIN 256
 #endif
 
 // float64 kernel: u and S read row-wise (consecutive lanes on one row) and redistributed through
@@ -388,22 +388,25 @@ k_relax(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf, c
 template <typename T, int N>
 struct RelaxWGeo {
   static_assert(sizeof(T) == 8, "the wave-local relaxation kernel is the float64 one");
-  // at N >= 512: radix 8 (one 512-point transform per wavefront) and 8 column pairs
-  static constexpr bool kWide = N >= 512;
+  // at N >= 256: radix 8 (one 512-point transform per wavefront, two of 256) and 8 column pairs, whose
+  // 256-byte spectral and 128-byte real row segments stream better than 4 pairs' half (256^3: 365 -> 348
+  // us, with the twiddles in LDS and two waves per SIMD; radix 4 with 8 pairs 368-438 us, radix 8 with 4
+  // pairs 370 us, 16 pairs 376 us).  At 128^3 radix 4 and 4 pairs are as fast (349 vs 350-365 us).
+  static constexpr bool kWide = N >= 256;
   using P = typename PlanPick<N, (kWide ? 0 : DGP_PLAN_RELAX)>::type;
   static constexpr int R = P::R;
   using G = AxisTile<T, N, R>;
   static constexpr int kTPSet = kWide ? DGP_RELAXW_TP_WIDE_F64 : DGP_RELAXW_TP_F64;
   static constexpr int kTP = kTPSet > 0 ? (kTPSet < N / 2 ? kTPSet : N / 2) : G::kTP;
   static constexpr int kT = G::kT, kThreads = kTP * kT, H = N / 2 + 1;
-  static constexpr int kMinWaves = kWide ? 2 : DGP_RELAXW_MINW_F64;   // the LDS tile allows one workgroup per CU from N = 512
+  static constexpr int kMinWaves = kWide ? 2 : DGP_RELAXW_MINW_F64;   // the LDS tile allows two workgroups per CU at N = 256, one at 512
   // twiddles from an LDS copy: held in registers, the loop-invariant twiddles of the six
   // inverse transforms would need 56 VGPRs across the field loop at N = 512, where the kernel
-  // already uses all 256 of a two-waves-per-SIMD allocation
+  // already uses most of the 256 of a two-waves-per-SIMD allocation
   static constexpr bool kTwLds = N >= DGP_RELAXW_TWLDS_MIN;
   // u and S read row-wise and redistributed through LDS (below N = 512: the staging registers
-  // would not fit the wide geometry's allocation)
-  static constexpr bool kUsLds = DGP_RELAXW_US_LDS && !kWide;
+  // would not fit the allocation there)
+  static constexpr bool kUsLds = DGP_RELAXW_US_LDS && N < 512;
   static_assert(kT <= 64 && 64 % kT == 0, "a transform must stay inside one wavefront");
   static constexpr int kSP = 2 * kTP + 1;                            // padded tile row, complex
   static constexpr int kTile = H * kSP;
