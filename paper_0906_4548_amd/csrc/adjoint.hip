@@ -75,13 +75,16 @@ k_adj_init(size_t n3, const double* __restrict__ g, const double* __restrict__ u
 }
 
 // Geometry of k_adj_step: radix-4 axis-0 transforms (the update holds five fields per element,
-// the products two), column pairs for 128-byte rows; registers planned for two waves per SIMD.
+// the products two); registers planned for two waves per SIMD, i.e. 512 threads per CU, which are one
+// workgroup from N = 128 on: as many column pairs as that allows make the longest row segments (8 x 128^3:
+// 4 / 8 / 16 pairs 500 / 496 / 481 us, 256^3: 4 / 8 pairs 569 / 527 us).  Smaller meshes keep 128-byte
+// rows: a single 64^3 mesh would be left with 64 workgroups.
 template <int N>
 struct AdjGeo {
   using P = typename PlanPick<N, 2>::type;
   static constexpr int R = P::R;
   using G = AxisTile<double, N, R>;
-  static constexpr int kTP = G::kTP, kT = G::kT, kThreads = G::kThreads;
+  static constexpr int kT = G::kT, kTP = N >= 128 ? 512 / kT : G::kTP, kThreads = kTP * kT;
 };
 
 // One transposed relaxation step fused with the axis-0 transforms around it, for a tile of
@@ -95,7 +98,7 @@ struct AdjGeo {
 // Per workgroup: sum |res|, sum |g| and sum h22 mu' into part[b][group][0..2].
 // Bound by HBM at two waves per SIMD, so every field is read once and ahead of the transform before
 // its use (8 x 128^3, 2.16 GB a launch: h00 and h11 read again for their products 556 us, products
-// formed with the update 519 us, loads ahead of the transforms 506 us, 4.3 TB/s).
+// formed with the update 519 us, loads ahead of the transforms 506 us, longer rows 481 us, 4.5 TB/s).
 template <int N, bool UPDATE>
 __global__ void __launch_bounds__(AdjGeo<N>::kThreads, 2)
 k_adj_step(const cx<double>* __restrict__ qspec, double* __restrict__ mubuf, size_t mu_stride,
