@@ -50,12 +50,13 @@ namespace dgp {
 #ifndef DGP_PLAN_P3_F32
 #define DGP_PLAN_P3_F32 0
 #endif
-// Column tile of the axis-0 passes: AxisTile, widened from N = 256 on, where the planes are
-// 0.5-4 MB apart and the narrow tile's row segments per plane stream poorly (at 256^3 the
+// Column tile of the axis-0 passes: AxisTile, twice as wide from N = 128 on, where the planes are
+// 0.25-4 MB apart and the narrow tile's row segments per plane stream poorly (at 256^3 the
 // float64 set-up, which also writes float32 copies, 465 -> 432 us; the float32 force mesh
-// 347 -> 331 us; a float64-form step -70 us).
+// 347 -> 331 us; a float64-form step -70 us; 8 x 128^3 float64 inverse 46.8 -> 42.8 us, forward 57.5 ->
+// 56.1 us).  Four times as wide is no faster up to 256^3 and slower at 512^3 (float32 244 -> 270-300 us).
 #ifndef DGP_P1_WIDE_MIN
-#define DGP_P1_WIDE_MIN 256
+#define DGP_P1_WIDE_MIN 128
 #endif
 template <typename T, int N, int R>
 struct P1Tile {
