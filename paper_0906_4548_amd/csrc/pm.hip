@@ -73,16 +73,17 @@ __device__ __forceinline__ Cic cic_of(const P* __restrict__ pos, long long np, l
 // particle (a box's surface grows slower than its volume) but more registers and LDS: the
 // geometry is chosen by mesh size, from the measured deposit times of the Zel'dovich loads
 // (256^3 float64 particles: 512 / 1024 / 2048 particles per chunk 357 / 299 / 322 us; 512^3
-// float32 particles: 2.84 / 2.84 / 2.45 ms).  The 2048-particle chunk recomputes each
-// particle's cell and weights after the box instead of holding them across its barriers, and
-// sizes its histogram at three cells per particle: occupancy 2 -> 3 waves per SIMD, 512^3
-// 2.43 -> 2.12 ms (the 1024-particle chunk, LDS-bound at four, gains nothing from either).
+// float32 particles: 2.84 / 2.84 / 2.45 ms).  Each particle's cell and weights are computed again
+// after the box instead of being held across its barriers (1024-particle chunks: 138 -> 58-68 VGPRs,
+// occupancy 3 -> 4 waves per SIMD; the tile counts of 15.0M float32 particles in lattice order 118 ->
+// 97 us), and the 2048-particle chunk sizes its histogram at three cells per particle (both: occupancy
+// 2 -> 3, 512^3 2.43 -> 2.12 ms).  Three cells for the 1024-particle chunk make its counts faster still (81
+// us) but send boxes of blocked loads to the direct path (256^3 step's deposit 231 -> 241 us).
 template <int CH>
 struct DepGeo {
   static constexpr int kChunk = CH;                         // particles per workgroup
   static constexpr int kPPT = CH / 256;                     // particles per thread
-  static constexpr bool kRecompute = CH >= 2048;
-  static constexpr int kCap = (kRecompute ? 3 : 4) * CH;    // cells of the LDS histogram (8 bytes each)
+  static constexpr int kCap = (CH >= 2048 ? 3 : 4) * CH;    // cells of the LDS histogram (8 bytes each)
   static_assert(CH % 256 == 0, "chunk must be a multiple of the workgroup size");
 };
 
@@ -101,7 +102,7 @@ __device__ __forceinline__ int periodic_offset(int i, int r, int n) {
 // Every thread of the (256-thread) workgroup must call it.
 template <int PPT, typename P>
 __device__ __forceinline__ bool chunk_box(const P* __restrict__ pos, const P (&xs)[PPT][3], long long np, int n,
-                                          double scale, long long p0, int cap, Cic& cr, Cic (&cs)[PPT],
+                                          double scale, long long p0, int cap, Cic& cr,
                                           int (&off)[PPT][3], int (&bx)[6]) {
   __shared__ int wlo[4][3], whi[4][3];
   __shared__ int sbox[7];
@@ -112,10 +113,10 @@ __device__ __forceinline__ bool chunk_box(const P* __restrict__ pos, const P (&x
     const long long p = p0 + threadIdx.x + k * 256;
     if (p < np) {
       const double s3[3] = {double(xs[k][0]) * scale, double(xs[k][1]) * scale, double(xs[k][2]) * scale};
-      cs[k] = cic_at(s3, n);
+      const Cic c = cic_at(s3, n);
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        off[k][d] = periodic_offset(cs[k].i0[d], cr.i0[d], n);
+        off[k][d] = periodic_offset(c.i0[d], cr.i0[d], n);
         lo[d] = min(lo[d], off[k][d]);
         hi[d] = max(hi[d], off[k][d] + 1);
       }
@@ -275,9 +276,9 @@ k_deposit_bin(const P* __restrict__ pos, long long np, int n, double scale, unsi
   P xs[kDepPPT][3];
   load_chunk<kDepPPT>(pos, np, p0, xs);
   flag_nonfinite<kDepPPT>(xs, bad);
-  Cic cr, cs[kDepPPT];
+  Cic cr;
   int off[kDepPPT][3], bx[6];
-  const bool binned = chunk_box<kDepPPT>(pos, xs, np, n, scale, p0, G::kCap, cr, cs, off, bx);
+  const bool binned = chunk_box<kDepPPT>(pos, xs, np, n, scale, p0, G::kCap, cr, off, bx);
   const int vol = bx[3] * bx[4] * bx[5];
   if constexpr (SORT) {
     static_assert(kTileBoxCap * sizeof(unsigned) <= sizeof(hist), "tile counters alias the histogram");
@@ -308,9 +309,9 @@ k_deposit_bin(const P* __restrict__ pos, long long np, int n, double scale, unsi
   for (int k = 0; k < kDepPPT; ++k) {
     const long long p = p0 + threadIdx.x + k * 256;
     if (p >= np) continue;
-    // with kRecompute the cell and weights again from the position (the chunk box's arithmetic)
+    // the cell and weights again from the position (the chunk box's arithmetic)
     const double s3[3] = {double(xs[k][0]) * scale, double(xs[k][1]) * scale, double(xs[k][2]) * scale};
-    const Cic c = G::kRecompute ? cic_at(s3, n) : cs[k];
+    const Cic c = cic_at(s3, n);
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
       const double wx = a ? c.w1[0] : c.w0[0];
@@ -401,9 +402,9 @@ k_tile_scatter(const P* __restrict__ pos, long long np, int n, double scale, Til
   if (ts.sorted[p0 / CH] == 0) return;
   P xs[PPT][3];
   load_chunk<PPT>(pos, np, p0, xs);
-  Cic cr, cs[PPT];
+  Cic cr;
   int off[PPT][3], bx[6], t0[3], te[3];
-  (void)chunk_box<PPT>(pos, xs, np, n, scale, p0, 0, cr, cs, off, bx);
+  (void)chunk_box<PPT>(pos, xs, np, n, scale, p0, 0, cr, off, bx);
   (void)tile_box(cr, bx, t0, te);   // fits: the counting pass sorted this chunk
   const int tv = te[0] * te[1] * te[2];
   for (int i = threadIdx.x; i < tv; i += 256) cnt[i] = 0u;
@@ -581,9 +582,9 @@ __device__ __forceinline__ void gather_chunk(const M* __restrict__ mesh, const P
                                              double scale, M* fl, const Apply& apply) {
 #pragma clang fp contract(off)
   const size_t n3 = (size_t)n * n * n;
-  Cic cr, cs[kGatherPPT];
+  Cic cr;
   int off[kGatherPPT][3], bx[6];
-  const bool binned = chunk_box<kGatherPPT>(pos, xs, np, n, scale, p0, kGatherCap, cr, cs, off, bx);
+  const bool binned = chunk_box<kGatherPPT>(pos, xs, np, n, scale, p0, kGatherCap, cr, off, bx);
   if (binned) {
     const int vol = bx[3] * bx[4] * bx[5];
     for (int i = threadIdx.x; i < vol; i += 256) {
@@ -824,9 +825,9 @@ k_interp_grad_mesh_bin(const P* __restrict__ pos, long long np, int n, double sc
   const long long p0 = xcd_chunk() * CH;
   P xs[PPT][3];
   load_chunk<PPT>(pos, np, p0, xs);
-  Cic cr, cs[PPT];
+  Cic cr;
   int off[PPT][3], bx[6];
-  const bool binned = chunk_box<PPT>(pos, xs, np, n, scale, p0, CAP, cr, cs, off, bx);
+  const bool binned = chunk_box<PPT>(pos, xs, np, n, scale, p0, CAP, cr, off, bx);
   const int vol = bx[3] * bx[4] * bx[5];
 #pragma unroll 1
   for (int m = 0; m < NC; ++m) {
