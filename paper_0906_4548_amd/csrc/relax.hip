@@ -845,7 +845,7 @@ k_finalize(const double* __restrict__ partial, int groups, SolveCtl* __restrict_
 }
 
 // Per-batch sums of |x| and of x per workgroup, the first level of a deterministic two-level reduction.
-// A plain read: eight independent loads per thread are in flight (256^3 counts: the mean of 256^3 counts, deposit 444 -> 433 us).
+// A plain read: eight independent loads per thread are in flight (the mean of 256^3 counts: deposit 444 -> 433 us).
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_absmean_partial(const T* __restrict__ x, size_t n3, double* __restrict__ part) {
