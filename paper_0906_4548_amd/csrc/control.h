@@ -19,6 +19,39 @@ __device__ __forceinline__ int wave_sum(int x) {
   return x;
 }
 
+// A pass's sums of |R| and of the bad points from its partial sums, by a workgroup of NT threads (every
+// thread returns them).  A pass is decided by the next pass's launch or, at the end of a chunk of
+// passes, by a launch of its own, so on the meshes where both occur both must add in the same order:
+// there each lane holds at most one partial sum (groups <= NT), consecutive 64 are added as a
+// butterfly and the wavefronts in order, whatever NT is.  (Lanes with several partial sums in one of
+// the two: the residuals of a 64^3 solve differed in the last place with the place of the host's looks.)
+template <int NT>
+__device__ __forceinline__ void pass_sums(const double* __restrict__ partial, int groups, double& sum_r, double& sum_bad) {
+  constexpr int WW = NT < 64 ? NT : 64, NW = (NT + 63) / 64;
+  __shared__ double wr[NW], wb[NW];
+  double r = 0.0, bad = 0.0;
+  const double2* p = reinterpret_cast<const double2*>(partial);
+  for (int g = threadIdx.x; g < groups; g += NT) {
+    const double2 v = p[g];
+    r += v.x;
+    bad += v.y;
+  }
+  r = wave_sum<WW>(r);
+  bad = wave_sum<WW>(bad);
+  if ((threadIdx.x & 63) == 0) {
+    wr[threadIdx.x >> 6] = r;
+    wb[threadIdx.x >> 6] = bad;
+  }
+  lds_barrier();
+  sum_r = wr[0];
+  sum_bad = wb[0];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) {
+    sum_r += wr[i];
+    sum_bad += wb[i];
+  }
+}
+
 // normalised residual of the iterate that the pass evaluated; eps = 0 only for a uniform delta
 // (S = 0), whose exact solution u = 0 has R = 0
 __device__ __forceinline__ double ctl_residual(const SolveCtl& C, double sum_r, const SolveCfg& cfg) {

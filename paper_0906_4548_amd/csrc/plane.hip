@@ -66,29 +66,8 @@ __device__ __forceinline__ bool decide_pass(const PassDecision& d, int b, bool w
     }
     return true;
   }
-  constexpr int WW = NT < 64 ? NT : 64, NW = (NT + 63) / 64;
-  __shared__ double wr[NW], wb[NW];
-  double sr = 0.0, sb = 0.0;
-  const double2* p = reinterpret_cast<const double2*>(d.partial) + (size_t)b * d.groups;
-  for (int g = threadIdx.x; g < d.groups; g += NT) {
-    const double2 v = p[g];
-    sr += v.x;
-    sb += v.y;
-  }
-  sr = wave_sum<WW>(sr);
-  sb = wave_sum<WW>(sb);
-  if ((threadIdx.x & 63) == 0) {
-    wr[threadIdx.x >> 6] = sr;
-    wb[threadIdx.x >> 6] = sb;
-  }
-  lds_barrier();
-  sr = wr[0];
-  sb = wb[0];
-#pragma unroll
-  for (int i = 1; i < NW; ++i) {
-    sr += wr[i];
-    sb += wb[i];
-  }
+  double sr, sb;
+  pass_sums<NT>(d.partial + (size_t)b * d.groups * 2, d.groups, sr, sb);
   if (write && threadIdx.x == 0) {
     SolveCtl& D = d.next[b];
     const int n = C.iters;

@@ -806,38 +806,20 @@ k_relax_small(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ u
   }
 }
 
-// Convergence control: one workgroup of NT threads per batch element (strided partial sums,
-// wavefront shuffles, a fixed-order sum over the wavefronts).  Latency bound: an element per
-// workgroup, and 256 threads where those read all partial sums in a few loads (5 x 64^3 float32
+// Convergence control: one workgroup of NT threads per batch element (pass_sums).  Latency bound: an
+// element per workgroup, with no more threads than up to 512 partial sums need (5 x 64^3 float32
 // passes, one workgroup walking the batch: 10.6 us, now 4.3 us; one 32^3 element 4.3 -> 3.7 us).
 template <int NT>
 __global__ void __launch_bounds__(NT)
 k_finalize(const double* __restrict__ partial, int groups, SolveCtl* __restrict__ ctl, SolveCtl* __restrict__ other,
            SolveCfg cfg) {
-  __shared__ double sr[NT / 64], sb[NT / 64];
   const int b = blockIdx.x;
   if (ctl[b].done) return;
-  double ar = 0.0, ab = 0.0;
-  const double2* pb = reinterpret_cast<const double2*>(partial) + (size_t)b * groups;
-  for (int g = threadIdx.x; g < groups; g += NT) {
-    const double2 v = pb[g];
-    ar += v.x;
-    ab += v.y;
-  }
-  ar = wave_sum<64>(ar);
-  ab = wave_sum<64>(ab);
-  if ((threadIdx.x & 63) == 0) {
-    sr[threadIdx.x >> 6] = ar;
-    sb[threadIdx.x >> 6] = ab;
-  }
-  __syncthreads();
+  double sr, sb;
+  pass_sums<NT>(partial + (size_t)b * groups * 2, groups, sr, sb);
   if (threadIdx.x != 0) return;
-  for (int i = 1; i < NT / 64; ++i) {
-    sr[0] += sr[i];
-    sb[0] += sb[i];
-  }
   const int n = ctl[b].iters;
-  ctl_decide(ctl[b], sr[0], sb[0], cfg);
+  ctl_decide(ctl[b], sr, sb, cfg);
   if (n < kMaxHist) {
     other[b].hist[n] = ctl[b].hist[n];
     other[b].hist_bad[n] = ctl[b].hist_bad[n];
@@ -961,6 +943,17 @@ static constexpr int relax_tp() {
   else return RelaxGeo<T, N>::G::kTP;
 }
 
+// pass_sums adds in one order in both deciders of a pass on the meshes of the plane kernels: its partial
+// sums take at most a lane each in the plane launch (N^2 / R threads) and in k_finalize (at most 512)
+template <typename T, int N>
+static constexpr bool one_partial_per_lane() {
+  constexpr int groups = N / (2 * relax_tp<T, N>()) * N;
+  return N > kPlaneMax || (groups <= N * N / Plan8<N>::R && groups <= 512);
+}
+static_assert(one_partial_per_lane<double, 8>() && one_partial_per_lane<double, 16>() && one_partial_per_lane<double, 32>() &&
+              one_partial_per_lane<double, 64>() && one_partial_per_lane<float, 8>() && one_partial_per_lane<float, 16>() &&
+              one_partial_per_lane<float, 32>() && one_partial_per_lane<float, 64>(), "the sums of a pass must not depend on the decider");
+
 int relax_groups(int n, int elem_bytes) {
   int tp = 0;
 #define C(NN)                                                                       \
@@ -974,7 +967,8 @@ int relax_groups(int n, int elem_bytes) {
 
 void launch_finalize(const double* partial, int groups, SolveCtl* ctl, SolveCtl* other, const SolveCfg& cfg,
                      hipStream_t s) {
-  if (groups <= 1024) hipLaunchKernelGGL(k_finalize<256>, dim3(cfg.batch), dim3(256), 0, s, partial, groups, ctl, other, cfg);
+  if (groups <= 256) hipLaunchKernelGGL(k_finalize<256>, dim3(cfg.batch), dim3(256), 0, s, partial, groups, ctl, other, cfg);
+  else if (groups <= 512) hipLaunchKernelGGL(k_finalize<512>, dim3(cfg.batch), dim3(512), 0, s, partial, groups, ctl, other, cfg);
   else hipLaunchKernelGGL(k_finalize<1024>, dim3(cfg.batch), dim3(1024), 0, s, partial, groups, ctl, other, cfg);
 }
 
