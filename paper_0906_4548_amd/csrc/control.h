@@ -5,15 +5,19 @@
 
 namespace dgp {
 
-// sum over the W lanes of a wavefront segment (butterfly order, deterministic)
-template <int W>
+// sum over the W lanes of a wavefront segment (butterfly order, deterministic) in a workgroup of NT
+// threads, all of which call it; a butterfly over lanes that the workgroup does not have would add
+// what a shuffle from a missing lane returns, which is undefined
+template <int W, int NT>
 __device__ __forceinline__ double wave_sum(double x) {
+  static_assert(W <= 64 && (W & (W - 1)) == 0 && NT % W == 0, "every segment must be whole");
 #pragma unroll
   for (int o = W / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, W);
   return x;
 }
-template <int W>
+template <int W, int NT>
 __device__ __forceinline__ int wave_sum(int x) {
+  static_assert(W <= 64 && (W & (W - 1)) == 0 && NT % W == 0, "every segment must be whole");
 #pragma unroll
   for (int o = W / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, W);
   return x;
@@ -36,8 +40,8 @@ __device__ __forceinline__ void pass_sums(const double* __restrict__ partial, in
     r += v.x;
     bad += v.y;
   }
-  r = wave_sum<WW>(r);
-  bad = wave_sum<WW>(bad);
+  r = wave_sum<WW, NT>(r);
+  bad = wave_sum<WW, NT>(bad);
   if ((threadIdx.x & 63) == 0) {
     wr[threadIdx.x >> 6] = r;
     wb[threadIdx.x >> 6] = bad;

@@ -204,7 +204,7 @@ k_p1_inv(const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restr
     for (int q = 0; q < R; ++q) sa += fabs(double(v[q].x)) + fabs(double(v[q].y));
     constexpr int NT = G::kThreads, WW = NT < 64 ? NT : 64, NW = (NT + 63) / 64;
     __shared__ double ws[NW];
-    sa = wave_sum<WW>(sa);
+    sa = wave_sum<WW, NT>(sa);
     if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = sa;
     lds_barrier();
     if (threadIdx.x == 0) {

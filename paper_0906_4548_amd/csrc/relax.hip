@@ -322,9 +322,9 @@ k_relax(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf, c
   lds_barrier();
 #pragma unroll
   for (int q = 0; q < R; ++q) lds[(t + q * TT) * TP + c] = v[q];
-  constexpr int WW = G::kThreads < 64 ? G::kThreads : 64;   // lanes of a (possibly partial) wavefront
-  abs_r = wave_sum<WW>(abs_r);
-  nbad = wave_sum<WW>(nbad);
+  constexpr int WW = G::kThreads < 64 ? G::kThreads : 64;
+  abs_r = wave_sum<WW, G::kThreads>(abs_r);
+  nbad = wave_sum<WW, G::kThreads>(nbad);
   if ((threadIdx.x & 63) == 0) {
     red[threadIdx.x >> 6] = abs_r;
     redi[threadIdx.x >> 6] = nbad;
@@ -412,7 +412,7 @@ struct RelaxWGeo {
   static constexpr int kTile = H * kSP;
   static constexpr int kNPF = (H * kTP + kThreads - 1) / kThreads;   // column pairs fetched per thread
   static constexpr int kWaves = (kThreads + 63) / 64;
-  static constexpr int kWidth = kThreads < 64 ? kThreads : 64;       // lanes of a (possibly partial) wavefront
+  static constexpr int kWidth = kThreads < 64 ? kThreads : 64;       // lanes of a wavefront sum
 };
 
 // Exchange slots of transform c inside its own two tile columns (2c, 2c+1).
@@ -603,8 +603,8 @@ k_relax_w(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ ubuf,
     LdsPair<T, SP> X{lds + W::kTile, c};
     fft<T, N, P, -1>(v, twp, X, t);
   }
-  abs_r = wave_sum<W::kWidth>(abs_r);
-  nbad = wave_sum<W::kWidth>(nbad);
+  abs_r = wave_sum<W::kWidth, NT>(abs_r);
+  nbad = wave_sum<W::kWidth, NT>(nbad);
   if ((threadIdx.x & 63) == 0) {
     redd[threadIdx.x >> 6] = abs_r;
     redi[threadIdx.x >> 6] = nbad;
@@ -658,7 +658,9 @@ struct RelaxSGeo {
   static constexpr int R = P::R, kT = N / R;
   static constexpr int kBase = 128 / (4 * int(sizeof(T)));   // column pairs of a 128-byte row segment
   static constexpr int kTP = kBase < N / 2 ? kBase : N / 2;
-  static constexpr int kGroup = kTP * kT, kThreads = 6 * kGroup, kWaves = (kThreads + 63) / 64;
+  // whole wavefronts (the residual's sums shuffle over all lanes); threads past the six groups take
+  // pair-points of the update only
+  static constexpr int kGroup = kTP * kT, kWaves = (6 * kGroup + 63) / 64, kThreads = 64 * kWaves;
   static constexpr int kPts = N * kTP, kPPT = (kPts + kThreads - 1) / kThreads;   // pair-points, per thread
   // exchange rows padded by one after every 8, as in k_relax
   static constexpr int kField = (N + N / 8) * kTP;
@@ -691,14 +693,17 @@ k_relax_small(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ u
   __shared__ int redi[G::kWaves];
   const size_t col0 = (size_t)b * H * NN + (size_t)i1 * N + i2;
   // the spectral rows of the thread's transform elements (row N - e conjugated), one column pair each
-  const cx<T>* src = spec6 + f * fstride + col0 + 2 * c;
+  const bool grouped = NT == 6 * G::kGroup || f < 6;
   cx<T> xa[R], xb[R];
+  if (grouped) {
+    const cx<T>* src = spec6 + f * fstride + col0 + 2 * c;
 #pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const int e = t + q * TT;
-    const cx<T>* p = src + (size_t)(e <= N / 2 ? e : N - e) * NN;
-    xa[q] = mk(p[0].x, p[0].y);
-    xb[q] = mk(p[1].x, p[1].y);
+    for (int q = 0; q < R; ++q) {
+      const int e = t + q * TT;
+      const cx<T>* p = src + (size_t)(e <= N / 2 ? e : N - e) * NN;
+      xa[q] = mk(p[0].x, p[0].y);
+      xb[q] = mk(p[1].x, p[1].y);
+    }
   }
   const size_t pt0 = (size_t)i1 * N + i2;
   const T* uin = ubuf + ((size_t)ctl[b].cur * cfg.batch + b) * N3 + pt0;
@@ -714,23 +719,25 @@ k_relax_small(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ u
   for (int i = threadIdx.x; i < N; i += NT) twl[i] = tw[i];
   lds_barrier();
   cx<T> v[R];
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const int e = t + q * TT;
-    if (e > N / 2) {
-      xa[q] = conjg(xa[q]);
-      xb[q] = conjg(xb[q]);
-    }
-    if (e == 0 || e == N / 2) { xa[q].y = T(0); xb[q].y = T(0); }
-    v[q] = mk(xa[q].x - xb[q].y, xa[q].y + xb[q].x);   // x_a + i x_b
-  }
   LdsColWave<T, TP> L;
   L.base = lds + f * G::kField;
   L.c = c;
-  fft<T, N, P, +1>(v, twl, L, t);
-  wave_sync();
+  if (grouped) {
 #pragma unroll
-  for (int q = 0; q < R; ++q) L.store(t + q * TT, v[q]);
+    for (int q = 0; q < R; ++q) {
+      const int e = t + q * TT;
+      if (e > N / 2) {
+        xa[q] = conjg(xa[q]);
+        xb[q] = conjg(xb[q]);
+      }
+      if (e == 0 || e == N / 2) { xa[q].y = T(0); xb[q].y = T(0); }
+      v[q] = mk(xa[q].x - xb[q].y, xa[q].y + xb[q].x);   // x_a + i x_b
+    }
+    fft<T, N, P, +1>(v, twl, L, t);
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < R; ++q) L.store(t + q * TT, v[q]);
+  }
   lds_barrier();
   // pointwise residual and update; a pair-point's slots are read, and its first one rewritten, by
   // its own thread only
@@ -768,8 +775,8 @@ k_relax_small(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ u
     A.base = lds;
     A.store(e, o);
   }
-  abs_r = wave_sum<64>(abs_r);
-  nbad = wave_sum<64>(nbad);
+  abs_r = wave_sum<64, NT>(abs_r);
+  nbad = wave_sum<64, NT>(nbad);
   if ((threadIdx.x & 63) == 0) {
     red[threadIdx.x >> 6] = abs_r;
     redi[threadIdx.x >> 6] = nbad;
@@ -851,8 +858,8 @@ k_absmean_partial(const T* __restrict__ x, size_t n3, double* __restrict__ part)
     sa += fabs(double(xb[i]));
     sm += double(xb[i]);
   }
-  sa = wave_sum<64>(sa);
-  sm = wave_sum<64>(sm);
+  sa = wave_sum<64, 256>(sa);
+  sm = wave_sum<64, 256>(sm);
   __shared__ double ra[4], rm[4];
   if ((threadIdx.x & 63) == 0) {
     ra[threadIdx.x >> 6] = sa;
@@ -1013,7 +1020,7 @@ __device__ __forceinline__ double eps_of(const double* __restrict__ part, int gr
   __shared__ double w[NT / 64];
   double s = 0.0;
   for (int g = threadIdx.x; g < groups; g += NT) s += part[g];
-  s = wave_sum<64>(s);
+  s = wave_sum<64, NT>(s);
   if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = s;
   __syncthreads();
   s = w[0];
@@ -1090,8 +1097,8 @@ k_take_buffer(const SolveCtl* __restrict__ ctl, const T* __restrict__ U, int bat
     sm += v;
   }
   if (!part) return;
-  sa = wave_sum<64>(sa);
-  sm = wave_sum<64>(sm);
+  sa = wave_sum<64, 256>(sa);
+  sm = wave_sum<64, 256>(sm);
   __shared__ double ra[4], rm[4];
   if ((threadIdx.x & 63) == 0) {
     ra[threadIdx.x >> 6] = sa;
@@ -1163,7 +1170,7 @@ k_spherical(size_t n3, const double* __restrict__ S, double* __restrict__ u, dou
       ub[i] = 2.0 * bp / (alpha + sqrt(disc));
     }
   }
-  nbad = wave_sum<64>(nbad);
+  nbad = wave_sum<64, 256>(nbad);
   __shared__ int rb[4];
   if ((threadIdx.x & 63) == 0) rb[threadIdx.x >> 6] = nbad;
   __syncthreads();
@@ -1179,7 +1186,7 @@ k_ctl_spherical(SolveCtl* __restrict__ ctl, const double* __restrict__ eps_part,
   if (threadIdx.x < 64) ctl_reset_history(ctl[b]);
   double nb = 0.0;
   for (int g = threadIdx.x; g < groups; g += 256) nb += partial[(size_t)b * groups + g];
-  nb = wave_sum<64>(nb);
+  nb = wave_sum<64, 256>(nb);
   __shared__ double rb[4];
   if ((threadIdx.x & 63) == 0) rb[threadIdx.x >> 6] = nb;
   __syncthreads();

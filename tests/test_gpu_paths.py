@@ -1,0 +1,121 @@
+"""Calls whose kernels depend on mesh size, particle order or precision, against the oracle or torch (GPU).
+
+Tolerances: float64 results of at most a few thousand operations of one rounding each, relative L2 1e-12;
+float64 transforms at 512^3 1e-12; the mixed form within its switch from float32 (1e-6) for a solve stopped
+there, at the float64 tolerance otherwise."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_0906_4548_amd import inputs  # noqa: E402
+from tests.gpu_common import gpu_params, rel_l2, to_dev  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def dgp():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_0906_4548_amd import dgp as mod
+    mod._lib.load()
+    return mod
+
+
+def _positions(n, np_, order, fp32):
+    box, rng = 2.0 * n, np.random.default_rng(np_ + n)
+    if order == "random":
+        x = rng.uniform(0.0, box, (3, np_))
+    elif order == "clustered":
+        x = (rng.normal(0.0, 0.04 * box, (3, np_)) + 0.1) % box
+    else:
+        side = 8 * int(np.ceil(np_ ** (1 / 3) / 8))
+        x = inputs.zeldovich_load(side, box, 12, rms_disp=0.8, block=8 if order == "blocks" else 0)[0][:, :np_]
+    x = np.ascontiguousarray(x).astype(np.float32 if fp32 else np.float64)
+    return np.where(x >= box, 0.0, x).astype(x.dtype)
+
+
+# gathers with one and three components and their adjoints: chunks that fit the staged box and chunks that
+# do not, loads too thin to fit it, one particle, a ragged last chunk
+@pytest.mark.parametrize("n,np_,order", [(32, 1, "random"), (32, 255, "blocks"), (32, 2 ** 15 - 3, "blocks"),
+                                         (32, 2 ** 15 - 3, "lattice"), (32, 20011, "random"), (32, 20011, "clustered"),
+                                         (64, 8190, "blocks"), (64, 70001, "lattice"), (64, 270001, "blocks")])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_gathers_and_deposit_adjoint(dgp, n, np_, order, fp32):
+    from oracle import adjoint, pm
+    box = 2.0 * n
+    pos = _positions(n, np_, order, fp32)
+    ref_pos = pos.astype(np.float64)
+    rng = np.random.default_rng(np_)
+    with dgp.Plan(n, box) as plan:
+        tp = torch.from_numpy(pos).cuda()
+        gd = rng.standard_normal((n, n, n))
+        gp = torch.zeros((3, np_), dtype=torch.float64, device="cuda")
+        plan.deposit_backward(tp, to_dev(gd), gp)
+        assert rel_l2(gp.cpu().numpy(), adjoint.deposit_backward(ref_pos, gd, box)) <= 1e-12
+        for nc in (1, 2, 3):
+            mesh, g = rng.standard_normal((nc, n, n, n)), rng.standard_normal((nc, np_))
+            out = torch.zeros((nc, np_), dtype=torch.float64, device="cuda")
+            plan.interp(to_dev(mesh), tp, out)
+            assert rel_l2(out.cpu().numpy(), pm.cic_interpolate(mesh, ref_pos, box)) <= 1e-12
+            gm = torch.zeros((nc, n, n, n), dtype=torch.float64, device="cuda")
+            plan.interp_backward(to_dev(mesh), tp, to_dev(g), gp, gm)
+            refp, refm = adjoint.interp_backward(mesh, ref_pos, g, box)
+            assert rel_l2(gp.cpu().numpy(), refp) <= 1e-12
+            assert rel_l2(gm.cpu().numpy(), refm) <= 1e-12
+            # the same bits in another order, whatever path its chunks take
+            perm = torch.randperm(np_, generator=torch.Generator().manual_seed(1)).cuda()
+            gm2 = torch.zeros_like(gm)
+            plan.interp_backward(None, tp[:, perm].contiguous(), to_dev(g)[:, perm].contiguous(), None, gm2)
+            assert torch.equal(gm, gm2)
+
+
+# 512^3, whose spectra and fields the plan keeps in groups of rows: the gradient of the power spectrum and
+# the C field against torch, the adjoint by its defining identity (S is symmetric: <grad_delta, d> does not
+# change when the problem is shifted by whole cells), a warm start in the mixed form
+@pytest.mark.timeout(600)
+def test_row_groups_512_other_calls(dgp):
+    n, box = 512, 1024.0
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    f = torch.randn((n, n, n), dtype=torch.float64, device="cuda", generator=gen) * 0.1
+    roll = ((1, 6, 3), (0, 1, 2))
+
+    def rel(x, y):
+        return float((x - y).norm() / y.norm())
+    p = gpu_params(dgp)
+    with dgp.Plan(n, box) as plan:
+        w = np.random.default_rng(4).standard_normal((1, 9))
+        g = torch.zeros_like(f)
+        plan.power_spectrum_backward(p, f, w, g)
+        pk, cnt = plan.power_spectrum(p, f, nbins=9)
+        # P is a quadratic form of f: <grad, f> = 2 sum_b w_b P_b
+        assert abs(float((g * f).sum()) - 2.0 * float((w * pk).sum())) <= 1e-10 * float((np.abs(w) * pk).sum())
+        u, c = torch.zeros_like(f), torch.zeros_like(f)
+        plan.solve_field(gpu_params(dgp, tol=0.0, max_iter=1), f, u, c)
+        kf = 2.0 * np.pi / box * p.kappa
+        m = torch.fft.fftfreq(n, 1.0 / n, dtype=torch.float64, device="cuda")
+        h = torch.arange(n // 2 + 1, dtype=torch.float64, device="cuda")
+        k2 = (m[:, None, None] ** 2 + m[None, :, None] ** 2 + h[None, None, :] ** 2) * kf ** 2
+        k2[0, 0, 0] = 1.0
+        cs = -torch.fft.rfftn(u) / k2
+        cs[0, 0, 0] = 0.0
+        assert rel(c, torch.fft.irfftn(cs, s=(n, n, n))) <= 1e-12
+        del cs, k2, c
+        # adjoint of a rolled problem is the rolled adjoint
+        gu = torch.randn((n, n, n), dtype=torch.float64, device="cuda", generator=gen)
+        plan.solve_field(gpu_params(dgp, tol=1e-10, lam=0.05), f, u)
+        q = gpu_params(dgp, tol=1e-6, lam=0.05, max_iter=60)
+        st, info = plan.solve_field_backward(q, f, u, gu, g)
+        assert st == 0
+        g2 = torch.zeros_like(f)
+        roll_ = lambda x: x.roll(*roll).contiguous()  # noqa: E731
+        st, info2 = plan.solve_field_backward(q, roll_(f), roll_(u), roll_(gu), g2)
+        assert st == 0 and info2[0]["iters"] == info[0]["iters"]
+        assert rel(g2, roll_(g)) <= 1e-11
+        u64 = u.clone()
+    with dgp.Plan(n, box, precision=dgp.FP32) as plan:
+        plan.solve_field(gpu_params(dgp, tol=1e-9, lam=0.05), f, u)
+        assert rel(u, u64) <= 1e-8
+        # a warm start from the solution is decided by its first float64 evaluations
+        st, info = plan.solve_field(gpu_params(dgp, tol=1e-8, lam=0.05, init=dgp.INIT_WARM), f, u)
+        assert st == 0 and rel(u, u64) <= 1e-8
