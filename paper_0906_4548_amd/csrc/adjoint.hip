@@ -279,7 +279,6 @@ k_adj_finalize(const double* __restrict__ part, int groups, SolveCtl* __restrict
   if (EVAL) {
     const double r = red[1][0] > 0.0 ? red[0][0] / red[1][0] : 0.0;
     const int n = C.iters;
-    if (n < kMaxHist) C.hist[n] = r;
     C.passes += 1;
     bool done = false;
     if (r <= tol) {

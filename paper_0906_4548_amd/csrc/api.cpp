@@ -196,9 +196,14 @@ struct dgp_plan {
   double* partial32 = nullptr;
   int groups32 = 0;
   // control
-  SolveCtl* ctl = nullptr;           // device [2][B]: the current set and the one a deciding launch writes
+  // the two sets of control blocks (the current one and the one a deciding launch writes) with the
+  // histories between them, so that either set is copied to the host with the histories in one piece
+  SolveCtl* ctl[2] = {nullptr, nullptr};   // device [B] each
+  SolveHist* hist = nullptr;         // device [B]
   int ctl_set = 0;                   // the current set
-  SolveCtl* ctl_host = nullptr;      // pinned [B]
+  char* ctl_pinned = nullptr;        // that set and the histories as last copied (ctl_fetch) ...
+  const SolveCtl* ctl_host = nullptr;    // ... [B]
+  const SolveHist* hist_host = nullptr;  // ... [B]
   double* mean_u = nullptr;          // [B]
   double* means_host = nullptr;      // pinned [B]: <u> of the returned iterates
   int hint32 = 0, hint64 = 0;        // passes of the last solve (float32 phase, float64 solve or phase)
@@ -392,8 +397,19 @@ static int plan_alloc(dgp_plan* pl) {
     pl->groups32 = relax_groups(pl->n, 4);
     TRY(dalloc(pl, &pl->partial32, B * pl->groups32 * 2));
   }
-  TRY(dalloc(pl, &pl->ctl, 2 * B));
-  TRY(halloc(pl, &pl->ctl_host, B));
+  char* ctl = nullptr;
+  TRY(dalloc(pl, &ctl, B * (2 * sizeof(SolveCtl) + sizeof(SolveHist))));
+  if (!pl->dry) {
+    pl->ctl[0] = reinterpret_cast<SolveCtl*>(ctl);
+    pl->hist = reinterpret_cast<SolveHist*>(ctl + B * sizeof(SolveCtl));
+    pl->ctl[1] = reinterpret_cast<SolveCtl*>(ctl + B * (sizeof(SolveCtl) + sizeof(SolveHist)));
+  }
+  TRY(halloc(pl, &pl->ctl_pinned, B * (sizeof(SolveCtl) + sizeof(SolveHist))));
+  if (!pl->dry) {   // nothing solved yet
+    std::memset(pl->ctl_pinned, 0, B * (sizeof(SolveCtl) + sizeof(SolveHist)));
+    pl->ctl_host = reinterpret_cast<SolveCtl*>(pl->ctl_pinned);
+    pl->hist_host = reinterpret_cast<SolveHist*>(pl->ctl_pinned + B * sizeof(SolveCtl));
+  }
   TRY(dalloc(pl, &pl->mean_u, B));
   TRY(halloc(pl, &pl->means_host, B));
   TRY(dalloc(pl, &pl->vec, 4 * B));
@@ -409,7 +425,7 @@ static int plan_alloc(dgp_plan* pl) {
   TRY(halloc(pl, &pl->flag_host, 2));
   TRY(dalloc(pl, &pl->fx_state, 4));
   TRY(dalloc(pl, &pl->bin_tab, 129 + 128 * B));
-  TRY(dalloc(pl, &pl->bin_partial, (size_t)p3_row_groups(pl->n) * B * 2 * 128));
+  TRY(dalloc(pl, &pl->bin_partial, (size_t)power_groups(pl->n) * B * 128));
   TRY(halloc(pl, &pl->bin_host, 129 + 128 * B));
   return DGP_OK;
 }
@@ -600,8 +616,17 @@ static int setup_source(dgp_plan* pl, const dgp_params* p, const Contrast& delta
   return DGP_OK;
 }
 
-static SolveCtl* ctl_now(dgp_plan* pl) { return pl->ctl + (size_t)pl->ctl_set * pl->batch; }
-static SolveCtl* ctl_other(dgp_plan* pl) { return pl->ctl + (size_t)(1 - pl->ctl_set) * pl->batch; }
+static SolveCtl* ctl_now(dgp_plan* pl) { return pl->ctl[pl->ctl_set]; }
+static SolveCtl* ctl_other(dgp_plan* pl) { return pl->ctl[1 - pl->ctl_set]; }
+// enqueue the copy of the current control blocks and the histories to pinned memory
+static int ctl_fetch(dgp_plan* pl, hipStream_t s) {
+  const size_t cb = sizeof(SolveCtl) * pl->batch, hb = sizeof(SolveHist) * pl->batch;
+  const void* src = pl->ctl_set == 0 ? static_cast<const void*>(pl->ctl[0]) : pl->hist;
+  pl->ctl_host = reinterpret_cast<SolveCtl*>(pl->ctl_pinned + (pl->ctl_set == 0 ? 0 : hb));
+  pl->hist_host = reinterpret_cast<SolveHist*>(pl->ctl_pinned + (pl->ctl_set == 0 ? cb : 0));
+  HIPCHK(hipMemcpyAsync(pl->ctl_pinned, src, cb + hb, hipMemcpyDeviceToHost, s));
+  return DGP_OK;
+}
 
 // enqueue one relaxation pass on the iterate whose axis-0 spectrum is in spec_u.  decided: the previous
 // pass (if any) has been decided; otherwise this pass's plane launch decides it (meshes of plane_ok
@@ -617,7 +642,7 @@ static int enqueue_pass(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const Solve
     if (decided) {
       launch_plane<T>(n, SPEC_HSPLIT, w.spec_u, fs, w.spec6, fs, 6, B, cf, pl->mean_u, ctl_now(pl), s);
     } else {
-      const PassDecision d{w.partial, w.groups, ctl_now(pl), ctl_other(pl), cfg};
+      const PassDecision d{w.partial, w.groups, ctl_now(pl), ctl_other(pl), pl->hist, cfg};
       launch_plane<T>(n, SPEC_HSPLIT, w.spec_u, fs, w.spec6, fs, 6, B, cf, pl->mean_u, ctl_now(pl), s, &d);
       pl->ctl_set = 1 - pl->ctl_set;
     }
@@ -641,7 +666,7 @@ static int enqueue_pass(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const Solve
   }
   if (decide) {
     Timed t(pl, s, tcls<T>(DGP_T_FINALIZE));
-    launch_finalize(w.partial, w.groups, ctl_now(pl), ctl_other(pl), cfg, s);
+    launch_finalize(w.partial, w.groups, ctl_now(pl), pl->hist, cfg, s);
   }
   LAUNCHCHK();
   return DGP_OK;
@@ -668,7 +693,7 @@ static int run_loop(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const SolveCfg&
     for (int i = 0; i < m; ++i) TRY(enqueue_pass<T>(pl, p, w, cfg, !merge || i == 0, !merge || i == m - 1, s));
     k += m;
     if (!check) return DGP_OK;
-    HIPCHK(hipMemcpyAsync(pl->ctl_host, ctl_now(pl), sizeof(SolveCtl) * B, hipMemcpyDeviceToHost, s));
+    TRY(ctl_fetch(pl, s));
     HIPCHK(hipStreamSynchronize(s));
     timing_flush(pl);
     int active = 0, next = cap;
@@ -679,7 +704,7 @@ static int run_loop(dgp_plan* pl, const dgp_params* p, Ws<T>& w, const SolveCfg&
       int m = 1;
       const int n = C.iters;   // the next pass evaluates iterate n; hist[n-1], hist[n-2] are known
       if (n >= 2 && n - 1 < kMaxHist) {
-        const double r1 = C.hist[n - 1], r0 = C.hist[n - 2];
+        const double r1 = pl->hist_host[b].resid[n - 1], r0 = pl->hist_host[b].resid[n - 2];
         if (r1 > 0.0 && r0 > r1 && cfg.tol > 0.0) {
           const double need = std::log(cfg.tol / r1) / std::log(r1 / r0);
           m = need <= 1.0 ? 1 : int(std::ceil(need));
@@ -771,7 +796,7 @@ static int solve64(dgp_plan* pl, const dgp_params* p, const Contrast& delta, dou
   } else if (p->init == DGP_INIT_ZERO) {
     launch_fill_zero(w.U, (size_t)B * pl->n3, s);
   }
-  launch_ctl_init(ctl_now(pl), ctl_other(pl), pl->red, p1_groups(pl->n), pl->n3, B, s);
+  launch_ctl_init(ctl_now(pl), pl->hist, pl->red, p1_groups(pl->n), pl->n3, B, s);
   // a pass starts from the axis-0 spectrum of its iterate (what the fused pass writes); the linear
   // guess's is there already
   if (p->init != DGP_INIT_LINEAR) launch_p1_fwd<double>(pl->n, w.U, w.spec_u, B, nullptr, s, true);
@@ -798,8 +823,9 @@ static int solve_spherical(dgp_plan* pl, const dgp_params* p, const Contrast& de
   Ws<double> w = ws64(pl);
   const int B = pl->batch;
   TRY(setup_source(pl, p, delta, w, false, s));
-  launch_spherical(pl->n3, B, w.S, w.U, p->alpha, p->lambda, pl->partial, ctl_now(pl), pl->red, p1_groups(pl->n), s);
-  HIPCHK(hipMemcpyAsync(pl->ctl_host, ctl_now(pl), sizeof(SolveCtl) * B, hipMemcpyDeviceToHost, s));
+  launch_spherical(pl->n3, B, w.S, w.U, p->alpha, p->lambda, pl->partial, ctl_now(pl), pl->hist, pl->red,
+                   p1_groups(pl->n), s);
+  TRY(ctl_fetch(pl, s));
   return collect_enqueue<double>(pl, w, u_state, s);
 }
 
@@ -849,7 +875,7 @@ int solve32_polish(dgp_plan* pl, const dgp_params* p, const Contrast& delta, dou
     launch_fill_zero(w32.U, (size_t)B * n3 / 2, s);   // n3 is even
   }
   // eps = <|S|> of the float64 source; it stays in the control blocks for both phases
-  launch_ctl_init(ctl_now(pl), ctl_other(pl), pl->red, p1_groups(pl->n), n3, B, s);
+  launch_ctl_init(ctl_now(pl), pl->hist, pl->red, p1_groups(pl->n), n3, B, s);
   launch_p1_fwd<float>(pl->n, w32.U, w32.spec_u, B, nullptr, s);
   const double switch_tol = std::max(p->tol, double(DGP_SWITCH_TOL));
   const SolveCfg cfg32 = solve_cfg(pl, p, switch_tol, p->max_iter);
@@ -860,7 +886,7 @@ int solve32_polish(dgp_plan* pl, const dgp_params* p, const Contrast& delta, dou
     TRY(run_loop<float>(pl, p, w32, cfg32, s, pl->hint32 + 1, false));
   else
     TRY(run_loop<float>(pl, p, w32, cfg32, s, 0, true));
-  launch_handoff(ctl_now(pl), ctl_other(pl), w32.U, B, pl->n, w.U, s);
+  launch_handoff(ctl_now(pl), pl->hist, w32.U, B, pl->n, w.U, s);
   launch_p1_fwd<double>(pl->n, w.U, w.spec_u, B, nullptr, s, true);
   const SolveCfg cfg = solve_cfg(pl, p, p->tol, p->max_iter);
   TRY(run_loop<double>(pl, p, w, cfg, s, pl->hint64, true));
@@ -1447,8 +1473,8 @@ extern "C" int dgp_solve_history(dgp_plan* pl, int b, double* resid, double* bad
   const SolveCtl& C = pl->ctl_host[b];   // as left by the last solve's final synchronisation
   int m = std::min(std::min(C.passes, kMaxHist), cap);
   for (int i = 0; i < m; ++i) {
-    if (resid) resid[i] = C.hist[i];
-    if (bad) bad[i] = C.hist_bad[i];
+    if (resid) resid[i] = pl->hist_host[b].resid[i];
+    if (bad) bad[i] = pl->hist_host[b].bad[i];
   }
   return m;
 }

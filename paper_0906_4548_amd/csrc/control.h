@@ -72,14 +72,15 @@ __device__ __forceinline__ bool ctl_decides(const SolveCtl& C, double r, const S
 
 // The decision itself, by one thread: C is the element's block of the pass just run (sum_r, sum_bad: its
 // sums of |R| and of the bad points).
-__device__ __forceinline__ void ctl_decide(SolveCtl& C, double sum_r, double sum_bad, const SolveCfg& cfg) {
+__device__ __forceinline__ void ctl_decide(SolveCtl& C, SolveHist& H, double sum_r, double sum_bad,
+                                           const SolveCfg& cfg) {
   const double n3 = double(cfg.n) * cfg.n * cfg.n;
   const double r = ctl_residual(C, sum_r, cfg);
   const int nbad = int(sum_bad);
   const int n = C.iters;
   if (n < kMaxHist) {
-    C.hist[n] = r;
-    C.hist_bad[n] = double(nbad) / n3;
+    H.resid[n] = r;
+    H.bad[n] = double(nbad) / n3;
   }
   C.passes += 1;
   bool done = false;

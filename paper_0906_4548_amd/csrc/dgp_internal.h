@@ -45,9 +45,9 @@ struct SpecCoef {
   int nbins;        // power spectrum: number of bins
 };
 
-// Per-batch-element control block of the relaxation (device memory).  A solve's blocks come in two sets,
-// [2][batch]: a launch that decides the previous pass while it starts the next one (launch_plane) reads
-// one set and writes the other; both sets hold the whole history.
+// Per-batch-element control block of the relaxation (device memory).  A solve's blocks come in two sets of
+// [batch]: a launch that decides the previous pass while it starts the next one (launch_plane) reads one
+// set and writes the other.  The histories are apart, one per element.
 constexpr int kMaxHist = 256;
 constexpr int kStatusInvalid = 3;
 struct SolveCtl {
@@ -71,11 +71,11 @@ struct SolveCtl {
   double resid_min;
   double bad_frac;
   double mean_u;    // <u> of the current iterate (from its k = 0 mode)
-  double hist[kMaxHist];       // r of the iterate evaluated by pass n
-  double hist_bad[kMaxHist];   // bad-point fraction of the update computed by pass n
 };
-
-constexpr size_t kCtlHeadBytes = offsetof(SolveCtl, hist);   // what changes from pass to pass, the histories apart
+struct SolveHist {
+  double resid[kMaxHist];   // r of the iterate evaluated by pass n
+  double bad[kMaxHist];     // bad-point fraction of the update computed by pass n
+};
 
 struct SolveCfg {
   double lam, w, alpha, gamma, omega, tol;
@@ -219,12 +219,14 @@ template <typename T>
 bool plane_ok(int n);
 constexpr int kPlaneMax = 64;   // the largest such mesh, in either precision
 // convergence decision of the previous pass, made by a launch_plane that starts the next one: the pass's
-// partial sums, the control blocks it ran with (prev) and those that the decision goes to (next)
+// partial sums, the control blocks it ran with (prev) and those that the decision goes to (next), and the
+// histories
 struct PassDecision {
   const double* partial;
   int groups;
   SolveCtl* prev;
   SolveCtl* next;
+  SolveHist* hist;
   SolveCfg cfg;
 };
 // ctl: control blocks (null: no element is skipped); with a decision, its prev blocks
@@ -232,10 +234,10 @@ template <typename T>
 void launch_plane(int n, SpecMode mode, const cx<T>* in, size_t in_stride, cx<T>* out, size_t out_stride, int nout,
                   int batch, const SpecCoef& cf, double* mean_out, const SolveCtl* ctl, hipStream_t s,
                   const PassDecision* decision = nullptr);
-int p3_row_groups(int n);   // workgroups per batch element of the float64 axis-2 pass
 // binned power spectrum of [batch] axis-0/1 spectra: sums[b][nbins] of |f|^2 (times 1/kbar^4 with
-// coef.power_c) over the modes with thr[bin] <= |n|^2 < thr[bin + 1]; partial: p3_row_groups(n) x batch x
+// coef.power_c) over the modes with thr[bin] <= |n|^2 < thr[bin + 1]; partial: power_groups(n) x batch x
 // nbins doubles of scratch
+int power_groups(int n);
 void launch_power(int n, const cx<double>* in, int batch, const SpecCoef& coef, const double* thr, double* partial,
                   double* sums, hipStream_t s);
 
@@ -247,7 +249,7 @@ void launch_relax(int n, const cx<T>* spec6, T* ubuf, const T* s_field, cx<T>* s
                   hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 int relax_groups(int n, int elem_bytes);   // workgroups per batch element of the fused pass
 
-void launch_finalize(const double* partial, int groups, SolveCtl* ctl, SolveCtl* other, const SolveCfg& cfg,
+void launch_finalize(const double* partial, int groups, SolveCtl* ctl, SolveHist* hist, const SolveCfg& cfg,
                      hipStream_t s);
 
 // reductions: per-batch mean of |x| and mean of x (double results)
@@ -256,22 +258,22 @@ void launch_absmean(size_t n3, const T* x, int batch, double* scratch, double* a
                     hipStream_t s);
 size_t absmean_scratch_doubles(size_t n3, int batch);
 // control blocks: eps[b] = the sum of part[b][0 .. groups) / n3 (the partial sums of |S|), buffer roles reset
-// (and the histories of both sets)
-void launch_ctl_init(SolveCtl* ctl, SolveCtl* other, const double* part, int groups, size_t n3, int batch,
+// (and the histories)
+void launch_ctl_init(SolveCtl* ctl, SolveHist* hist, const double* part, int groups, size_t n3, int batch,
                      hipStream_t s);
 // spherical approximation (Eqs. FullDGP2sph, SphPoi): u = the first w = 1/3 update from u = 0,
 // u = 2 S / (alpha + sqrt(alpha^2 + (8/3) lam S)) (vertex where the discriminant is negative),
 // for [batch][n3] S into u; then the control blocks record a decided one-update solve
 // (per-workgroup bad counts go through `partial`, which must hold batch x 4096 x 2 doubles)
 void launch_spherical(size_t n3, int batch, const double* S, double* u, double alpha, double lam, double* partial,
-                      SolveCtl* ctl, const double* eps_part, int eps_groups, hipStream_t s);
+                      SolveCtl* ctl, SolveHist* hist, const double* eps_part, int eps_groups, hipStream_t s);
+// a caller's float64 fields into the solve's own row order
+void launch_take_field(int n, const double* in, double* out, int batch, hipStream_t s);
 // end of the float32 phase: per element, the warm start for float64 (the update of the
 // pass that met the switch tolerance unless it met bad points, else the checked iterate;
 // the latest iterate if the phase was still running) converted into dst[B][n3], then the
 // control re-initialised for the float64 phase with the float32 counts kept
-// a caller's float64 fields into the solve's own row order
-void launch_take_field(int n, const double* in, double* out, int batch, hipStream_t s);
-void launch_handoff(SolveCtl* ctl, SolveCtl* other, const float* U32, int batch, int n, double* dst, hipStream_t s);
+void launch_handoff(SolveCtl* ctl, SolveHist* hist, const float* U32, int batch, int n, double* dst, hipStream_t s);
 // the returned iterate of every element, as float64, into dst[B][n3], and its mean into
 // mean[B] (scratch: absmean_scratch_doubles(n3, batch) doubles)
 template <typename T>

@@ -982,12 +982,8 @@ void launch_p3(int n, SpecMode mode, const cx<T>* in, size_t in_stride, int nin,
 void launch_power(int n, const cx<double>* in, int batch, const SpecCoef& coef, const double* thr, double* partial,
                   double* sums, hipStream_t s) {
   const cx<double>* tw = twiddles<double>(n);
-  int g = 0;
-#define C(NN)                                                                                               \
-  {                                                                                                         \
-    g = PowerGeo<NN>::kGroups;                                                                              \
-    hipLaunchKernelGGL((k_power<NN>), dim3(g, batch), dim3(256), 0, s, in, tw, coef, thr, partial);         \
-  }
+  const int g = power_groups(n);
+#define C(NN) hipLaunchKernelGGL((k_power<NN>), dim3(g, batch), dim3(256), 0, s, in, tw, coef, thr, partial)
   DGP_DISPATCH_N(n, C)
 #undef C
   hipLaunchKernelGGL(k_power_final, dim3(batch, (coef.nbins + 63) / 64), dim3(1024), 0, s, partial, g, coef.nbins, sums);
@@ -1001,13 +997,9 @@ int p1_groups(int n) {   // workgroups per batch element of the float64 axis-0 p
   return r;
 }
 
-int p3_row_groups(int n) {   // row groups of the float64 axis-2 pass (bounds the P(k) partials)
+int power_groups(int n) {   // workgroups per batch element of k_power
   int r = 0;
-#define C(NN)                                                          \
-  {                                                                    \
-    using G = RowTile<NN, Geo<double, NN>::P3::R>;                     \
-    r = ((NN / 2 + 1) * NN + G::kRW - 1) / G::kRW;                     \
-  }
+#define C(NN) r = PowerGeo<NN>::kGroups
   DGP_DISPATCH_N(n, C)
 #undef C
   return r;

@@ -57,29 +57,17 @@ struct PlaneRow {   // exchanges of row r (inside one wavefront)
 // own for this takes 3.5 us and a gap, of a 26-31 us pass.  Returns whether the element is done.
 template <int NT>
 __device__ __forceinline__ bool decide_pass(const PassDecision& d, int b, bool write) {
-  SolveCtl& C = d.prev[b];
+  const SolveCtl& C = d.prev[b];
   if (C.done) {
-    if (write) {
-      const auto* src = reinterpret_cast<const long long*>(&C);
-      auto* dst = reinterpret_cast<long long*>(&d.next[b]);
-      for (int i = threadIdx.x; i < int(kCtlHeadBytes / 8); i += NT) dst[i] = src[i];
-    }
+    if (write && threadIdx.x == 0) d.next[b] = C;
     return true;
   }
   double sr, sb;
   pass_sums<NT>(d.partial + (size_t)b * d.groups * 2, d.groups, sr, sb);
   if (write && threadIdx.x == 0) {
-    SolveCtl& D = d.next[b];
-    const int n = C.iters;
-    const auto* src = reinterpret_cast<const long long*>(&C);
-    auto* dst = reinterpret_cast<long long*>(&D);
-#pragma unroll
-    for (int i = 0; i < int(kCtlHeadBytes / 8); ++i) dst[i] = src[i];
-    ctl_decide(D, sr, sb, d.cfg);
-    if (n < kMaxHist) {   // (no other workgroup reads the histories)
-      C.hist[n] = D.hist[n];
-      C.hist_bad[n] = D.hist_bad[n];
-    }
+    SolveCtl D = C;
+    ctl_decide(D, d.hist[b], sr, sb, d.cfg);   // (no other workgroup touches the histories)
+    d.next[b] = D;
   }
   return ctl_decides(C, ctl_residual(C, sr, d.cfg), d.cfg);
 }

@@ -818,19 +818,13 @@ k_relax_small(const cx<T>* __restrict__ spec6, size_t fstride, T* __restrict__ u
 // passes, one workgroup walking the batch: 10.6 us, now 4.3 us; one 32^3 element 4.3 -> 3.7 us).
 template <int NT>
 __global__ void __launch_bounds__(NT)
-k_finalize(const double* __restrict__ partial, int groups, SolveCtl* __restrict__ ctl, SolveCtl* __restrict__ other,
+k_finalize(const double* __restrict__ partial, int groups, SolveCtl* __restrict__ ctl, SolveHist* __restrict__ hist,
            SolveCfg cfg) {
   const int b = blockIdx.x;
   if (ctl[b].done) return;
   double sr, sb;
   pass_sums<NT>(partial + (size_t)b * groups * 2, groups, sr, sb);
-  if (threadIdx.x != 0) return;
-  const int n = ctl[b].iters;
-  ctl_decide(ctl[b], sr, sb, cfg);
-  if (n < kMaxHist) {
-    other[b].hist[n] = ctl[b].hist[n];
-    other[b].hist_bad[n] = ctl[b].hist_bad[n];
-  }
+  if (threadIdx.x == 0) ctl_decide(ctl[b], hist[b], sr, sb, cfg);
 }
 
 // Per-batch sums of |x| and of x per workgroup, the first level of a deterministic two-level reduction.
@@ -972,18 +966,18 @@ int relax_groups(int n, int elem_bytes) {
   return (n / (2 * tp)) * n;
 }
 
-void launch_finalize(const double* partial, int groups, SolveCtl* ctl, SolveCtl* other, const SolveCfg& cfg,
+void launch_finalize(const double* partial, int groups, SolveCtl* ctl, SolveHist* hist, const SolveCfg& cfg,
                      hipStream_t s) {
-  if (groups <= 256) hipLaunchKernelGGL(k_finalize<256>, dim3(cfg.batch), dim3(256), 0, s, partial, groups, ctl, other, cfg);
-  else if (groups <= 512) hipLaunchKernelGGL(k_finalize<512>, dim3(cfg.batch), dim3(512), 0, s, partial, groups, ctl, other, cfg);
-  else hipLaunchKernelGGL(k_finalize<1024>, dim3(cfg.batch), dim3(1024), 0, s, partial, groups, ctl, other, cfg);
+  if (groups <= 256) hipLaunchKernelGGL(k_finalize<256>, dim3(cfg.batch), dim3(256), 0, s, partial, groups, ctl, hist, cfg);
+  else if (groups <= 512) hipLaunchKernelGGL(k_finalize<512>, dim3(cfg.batch), dim3(512), 0, s, partial, groups, ctl, hist, cfg);
+  else hipLaunchKernelGGL(k_finalize<1024>, dim3(cfg.batch), dim3(1024), 0, s, partial, groups, ctl, hist, cfg);
 }
 
-// (one wavefront per control block: the lanes clear the histories, lane 0 continues)
-__device__ __forceinline__ void ctl_reset_history(SolveCtl& C) {
+// (by one wavefront)
+__device__ __forceinline__ void reset_history(SolveHist& H) {
   for (int i = threadIdx.x; i < kMaxHist; i += 64) {
-    C.hist[i] = -1.0;
-    C.hist_bad[i] = -1.0;
+    H.resid[i] = -1.0;
+    H.bad[i] = -1.0;
   }
 }
 
@@ -1029,15 +1023,12 @@ __device__ __forceinline__ double eps_of(const double* __restrict__ part, int gr
 }
 
 __global__ void __launch_bounds__(1024)
-k_ctl_init(SolveCtl* __restrict__ ctl, SolveCtl* __restrict__ other, const double* __restrict__ part, int groups,
+k_ctl_init(SolveCtl* __restrict__ ctl, SolveHist* __restrict__ hist, const double* __restrict__ part, int groups,
            size_t n3) {
   const int b = blockIdx.x;
   const double eps = eps_of<1024>(part + (size_t)b * groups, groups, n3);
   SolveCtl& C = ctl[b];
-  if (threadIdx.x < 64) {
-    ctl_reset_history(C);
-    ctl_reset_history(other[b]);
-  }
+  if (threadIdx.x < 64) reset_history(hist[b]);
   if (threadIdx.x != 0) return;
   ctl_reset(C);
   C.eps = eps;
@@ -1112,10 +1103,9 @@ k_take_buffer(const SolveCtl* __restrict__ ctl, const T* __restrict__ U, int bat
 }
 
 // keeps eps (the float64 source's) and records the float32 phase's counts
-__global__ void __launch_bounds__(64) k_ctl_phase2(SolveCtl* __restrict__ ctl, SolveCtl* __restrict__ other) {
+__global__ void __launch_bounds__(64) k_ctl_phase2(SolveCtl* __restrict__ ctl, SolveHist* __restrict__ hist) {
   SolveCtl& C = ctl[blockIdx.x];
-  ctl_reset_history(C);
-  ctl_reset_history(other[blockIdx.x]);
+  reset_history(hist[blockIdx.x]);
   if (threadIdx.x != 0) return;
   const int src = handoff_buffer(C);
   const bool invalid = C.status == kStatusInvalid;
@@ -1139,10 +1129,10 @@ static unsigned copy_groups(size_t n3) {
   return unsigned(g > 4096 ? 4096 : g);
 }
 
-void launch_handoff(SolveCtl* ctl, SolveCtl* other, const float* U32, int batch, int n, double* dst, hipStream_t s) {
+void launch_handoff(SolveCtl* ctl, SolveHist* hist, const float* U32, int batch, int n, double* dst, hipStream_t s) {
   hipLaunchKernelGGL((k_take_buffer<float>), dim3(copy_groups((size_t)n * n * n), batch), dim3(256), 0, s, ctl, U32,
                      batch, __builtin_ctz(n), dst, 1, nullptr);
-  hipLaunchKernelGGL(k_ctl_phase2, dim3(batch), dim3(64), 0, s, ctl, other);
+  hipLaunchKernelGGL(k_ctl_phase2, dim3(batch), dim3(64), 0, s, ctl, hist);
 }
 
 void launch_take_field(int n, const double* in, double* out, int batch, hipStream_t s) {
@@ -1179,11 +1169,11 @@ k_spherical(size_t n3, const double* __restrict__ S, double* __restrict__ u, dou
 }
 
 __global__ void __launch_bounds__(256)
-k_ctl_spherical(SolveCtl* __restrict__ ctl, const double* __restrict__ eps_part, int eps_groups,
-                const double* __restrict__ partial, int groups, size_t n3) {
+k_ctl_spherical(SolveCtl* __restrict__ ctl, SolveHist* __restrict__ hist, const double* __restrict__ eps_part,
+                int eps_groups, const double* __restrict__ partial, int groups, size_t n3) {
   const int b = blockIdx.x;
   const double eps = eps_of<256>(eps_part + (size_t)b * eps_groups, eps_groups, n3);
-  if (threadIdx.x < 64) ctl_reset_history(ctl[b]);
+  if (threadIdx.x < 64) reset_history(hist[b]);
   double nb = 0.0;
   for (int g = threadIdx.x; g < groups; g += 256) nb += partial[(size_t)b * groups + g];
   nb = wave_sum<64, 256>(nb);
@@ -1204,15 +1194,15 @@ k_ctl_spherical(SolveCtl* __restrict__ ctl, const double* __restrict__ eps_part,
   C.resid = -1.0;       // not evaluated: the approximation is not a root of Eq. FullDGP2
   C.resid_min = -1.0;
   C.bad_frac = (((rb[0] + rb[1]) + rb[2]) + rb[3]) / double(n3);
-  C.hist_bad[0] = C.bad_frac;
+  hist[b].bad[0] = C.bad_frac;
   mark_invalid_input(C);
 }
 
 void launch_spherical(size_t n3, int batch, const double* S, double* u, double alpha, double lam, double* partial,
-                      SolveCtl* ctl, const double* eps_part, int eps_groups, hipStream_t s) {
+                      SolveCtl* ctl, SolveHist* hist, const double* eps_part, int eps_groups, hipStream_t s) {
   const int g = int(std::min<size_t>(4096, (n3 + 255) / 256));
   hipLaunchKernelGGL(k_spherical, dim3(g, batch), dim3(256), 0, s, n3, S, u, alpha, lam, partial);
-  hipLaunchKernelGGL(k_ctl_spherical, dim3(batch), dim3(256), 0, s, ctl, eps_part, eps_groups, partial, g, n3);
+  hipLaunchKernelGGL(k_ctl_spherical, dim3(batch), dim3(256), 0, s, ctl, hist, eps_part, eps_groups, partial, g, n3);
 }
 
 template <typename T>
@@ -1230,9 +1220,9 @@ template void launch_take_result<double>(const SolveCtl*, const double*, int, in
 template void launch_take_result<float>(const SolveCtl*, const float*, int, int, double*, double*, double*,
                                         hipStream_t);
 
-void launch_ctl_init(SolveCtl* ctl, SolveCtl* other, const double* part, int groups, size_t n3, int batch,
+void launch_ctl_init(SolveCtl* ctl, SolveHist* hist, const double* part, int groups, size_t n3, int batch,
                      hipStream_t s) {
-  hipLaunchKernelGGL(k_ctl_init, dim3(batch), dim3(1024), 0, s, ctl, other, part, groups, n3);
+  hipLaunchKernelGGL(k_ctl_init, dim3(batch), dim3(1024), 0, s, ctl, hist, part, groups, n3);
 }
 
 
