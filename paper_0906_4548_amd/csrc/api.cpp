@@ -186,7 +186,7 @@ struct dgp_plan {
   double* S = nullptr;               // [B][n3]
   cx<double>* spec_u = nullptr;      // [B][hs]
   cx<double>* spec6 = nullptr;       // [9][B][hs]; fields 6, 7: axis-0/1 spectra of delta (kept) and u; 8: spec_u
-  double* partial = nullptr;         // [B][groups][2]
+  double* partial = nullptr;         // [B][groups][2], or a spherical solve's [B][spherical_groups]
   int groups64 = 0;
   // float32 solve workspace (precision form)
   float* U32 = nullptr;
@@ -388,7 +388,7 @@ static int plan_alloc(dgp_plan* pl) {
   TRY(dalloc(pl, &pl->spec6, 9 * B * hs));
   pl->spec_u = pl->dry ? nullptr : pl->spec6 + 8 * B * hs;
   pl->groups64 = relax_groups(pl->n, 8);
-  TRY(dalloc(pl, &pl->partial, B * pl->groups64 * 2));
+  TRY(dalloc(pl, &pl->partial, B * std::max(pl->groups64 * 2, spherical_groups(n3))));
   if (pl->precision == DGP_FP32) {
     TRY(dalloc(pl, &pl->U32, 3 * B * n3));
     TRY(dalloc(pl, &pl->S32, B * n3));

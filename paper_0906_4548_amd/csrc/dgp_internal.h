@@ -264,7 +264,8 @@ void launch_ctl_init(SolveCtl* ctl, SolveHist* hist, const double* part, int gro
 // spherical approximation (Eqs. FullDGP2sph, SphPoi): u = the first w = 1/3 update from u = 0,
 // u = 2 S / (alpha + sqrt(alpha^2 + (8/3) lam S)) (vertex where the discriminant is negative),
 // for [batch][n3] S into u; then the control blocks record a decided one-update solve
-// (per-workgroup bad counts go through `partial`, which must hold batch x 4096 x 2 doubles)
+// (per-workgroup bad counts go through `partial`, which must hold batch x spherical_groups(n3) doubles)
+int spherical_groups(size_t n3);
 void launch_spherical(size_t n3, int batch, const double* S, double* u, double alpha, double lam, double* partial,
                       SolveCtl* ctl, SolveHist* hist, const double* eps_part, int eps_groups, hipStream_t s);
 // a caller's float64 fields into the solve's own row order

@@ -1198,9 +1198,11 @@ k_ctl_spherical(SolveCtl* __restrict__ ctl, SolveHist* __restrict__ hist, const 
   mark_invalid_input(C);
 }
 
+int spherical_groups(size_t n3) { return int(std::min<size_t>(4096, (n3 + 255) / 256)); }
+
 void launch_spherical(size_t n3, int batch, const double* S, double* u, double alpha, double lam, double* partial,
                       SolveCtl* ctl, SolveHist* hist, const double* eps_part, int eps_groups, hipStream_t s) {
-  const int g = int(std::min<size_t>(4096, (n3 + 255) / 256));
+  const int g = spherical_groups(n3);
   hipLaunchKernelGGL(k_spherical, dim3(g, batch), dim3(256), 0, s, n3, S, u, alpha, lam, partial);
   hipLaunchKernelGGL(k_ctl_spherical, dim3(batch), dim3(256), 0, s, ctl, hist, eps_part, eps_groups, partial, g, n3);
 }
