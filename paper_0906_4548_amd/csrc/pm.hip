@@ -243,13 +243,15 @@ __device__ __forceinline__ void tile_coords(int t, int n, int& x, int& y, int& z
 }
 static __host__ __device__ int tile_count(int n) { return (n >> kTL[0]) * (n >> kTL[1]) * (n >> kTL[2]); }
 
-// the tiles of a chunk's bounding box: first tile (unwrapped) and extent per axis
-__device__ __forceinline__ bool tile_box(const Cic& cr, const int (&bx)[6], int (&t0)[3], int (&te)[3]) {
+// the tiles of a chunk's bounding box: first tile (unwrapped) and extent per axis, at most the mesh's own
+// (a chunk over the whole mesh that starts inside a tile meets that tile again at the other end: counted
+// twice, the 4096 tiles of 256^3 came to 33 x 33 x 5 = 5445 and its chunks were not sorted)
+__device__ __forceinline__ bool tile_box(const Cic& cr, const int (&bx)[6], int n, int (&t0)[3], int (&te)[3]) {
   int vol = 1;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     t0[d] = (cr.i0[d] + bx[d]) >> kTL[d];
-    te[d] = ((cr.i0[d] + bx[d] + bx[3 + d] - 2) >> kTL[d]) - t0[d] + 1;   // base cells only
+    te[d] = min(((cr.i0[d] + bx[d] + bx[3 + d] - 2) >> kTL[d]) - t0[d] + 1, n >> kTL[d]);   // base cells only
     vol *= te[d];
   }
   return vol <= kTileBoxCap;
@@ -257,7 +259,10 @@ __device__ __forceinline__ bool tile_box(const Cic& cr, const int (&bx)[6], int 
 __device__ __forceinline__ int local_tile(const Cic& cr, const int (&off)[3], const int (&t0)[3], const int (&te)[3]) {
   int l = 0;
 #pragma unroll
-  for (int d = 0; d < 3; ++d) l = l * te[d] + (((cr.i0[d] + off[d]) >> kTL[d]) - t0[d]);
+  for (int d = 0; d < 3; ++d) {
+    const int x = ((cr.i0[d] + off[d]) >> kTL[d]) - t0[d];
+    l = l * te[d] + (x < te[d] ? x : x - te[d]);   // past the extent only where that is the whole axis
+  }
   return l;
 }
 __device__ __forceinline__ int global_tile(int l, const int (&t0)[3], const int (&te)[3], int n) {
@@ -283,7 +288,7 @@ k_deposit_bin(const P* __restrict__ pos, long long np, int n, double scale, unsi
   if constexpr (SORT) {
     static_assert(kTileBoxCap * sizeof(unsigned) <= sizeof(hist), "tile counters alias the histogram");
     int t0[3], te[3];
-    const bool sorted = !binned && tile_box(cr, bx, t0, te);
+    const bool sorted = !binned && tile_box(cr, bx, n, t0, te);
     if (threadIdx.x == 0) {
       ts.sorted[p0 / CH] = sorted ? 1 : 0;
       ts.state[sorted ? 2 : 1] = 1u;
@@ -405,7 +410,7 @@ k_tile_scatter(const P* __restrict__ pos, long long np, int n, double scale, Til
   Cic cr;
   int off[PPT][3], bx[6], t0[3], te[3];
   (void)chunk_box<PPT>(pos, xs, np, n, scale, p0, 0, cr, off, bx);
-  (void)tile_box(cr, bx, t0, te);   // fits: the counting pass sorted this chunk
+  (void)tile_box(cr, bx, n, t0, te);   // fits: the counting pass sorted this chunk
   const int tv = te[0] * te[1] * te[2];
   for (int i = threadIdx.x; i < tv; i += 256) cnt[i] = 0u;
   lds_barrier();
@@ -918,8 +923,11 @@ static unsigned grid_strided(size_t count) {
 // positions; compact chunks keep the direct path inside it.  Lattice-order loads, whole deposit without
 // and with it: 128^3 mesh, 64^3 / 96^3 / 128^3 particles 50 / 111 / 272 and 48 / 59 / 92 us; 256^3 mesh,
 // 128^3 / 256^3 particles 326 / 1786 and 137 / 493 us; on 64^3 (64 tiles) 64^3 particles take 42 and
-// 50 us.  A load in 8^3 blocks pays its four idle launches: 128^3 particles on 128^3 47 and 51 us,
-// 256^3 on 256^3 252 and 260 us.
+// 50 us.  In random order, 128^3 particles on 128^3 750 and 196 us, 4.2M / 16.8M on 256^3 1533 / 5805 and
+// 500 / 1380 us; on 512^3 a random chunk spans more tiles than a workgroup counts (32768) and stays
+// with direct atomics (33.6M: 13.3 and 13.2 ms).  A load in 8^3 blocks pays its four idle launches and
+// the sort's marks: 128^3 particles on 128^3 46 and 49 us, 256^3 on 256^3 244 and 263 us, 512^3 float32
+// on 512^3 1.66 and 1.77 ms.
 static bool tile_sort(int n, size_t psize, long long np, int ch, void* scratch, size_t bytes, TileSort& ts) {
   if (!scratch || n < 128 || np < (1ll << 18) || np >= (1ll << 31)) return false;
   const size_t tiles = tile_count(n), chunks = (np + ch - 1) / ch;
