@@ -291,7 +291,9 @@ k_deposit_bin(const P* __restrict__ pos, long long np, int n, double scale, unsi
     const bool sorted = !binned && tile_box(cr, bx, n, t0, te);
     if (threadIdx.x == 0) {
       ts.sorted[p0 / CH] = sorted ? 1 : 0;
-      ts.state[sorted ? 2 : 1] = 1u;
+      // (all compact chunks of a blocked load set one word: read before it is written)
+      if (sorted) ts.state[2] = 1u;
+      else if (ts.state[1] == 0u) ts.state[1] = 1u;
     }
     if (sorted) {
       unsigned* const cnt = reinterpret_cast<unsigned*>(hist);
@@ -925,9 +927,10 @@ static unsigned grid_strided(size_t count) {
 // 128^3 / 256^3 particles 326 / 1786 and 137 / 493 us; on 64^3 (64 tiles) 64^3 particles take 42 and
 // 50 us.  In random order, 128^3 particles on 128^3 750 and 196 us, 4.2M / 16.8M on 256^3 1533 / 5805 and
 // 500 / 1380 us; on 512^3 a random chunk spans more tiles than a workgroup counts (32768) and stays
-// with direct atomics (33.6M: 13.3 and 13.2 ms).  A load in 8^3 blocks pays its four idle launches and
-// the sort's marks: 128^3 particles on 128^3 46 and 49 us, 256^3 on 256^3 244 and 263 us, 512^3 float32
-// on 512^3 1.66 and 1.77 ms.
+// with direct atomics (33.6M: 13.3 and 13.2 ms).  A load in 8^3 blocks pays its four idle launches (and
+// its chunks' marks): 128^3 particles on 128^3 46 and 49 us, 256^3 on 256^3 244 and 257 us, 512^3 float32
+// on 512^3 1.66 and 1.71 ms.  (Fewer workgroups that walk their chunks, items or tiles make the idle
+// launches cheaper, 512^3 1.67 ms, and the sorting ones slower: lattice order 2.95 -> 3.0-3.2 ms.)
 static bool tile_sort(int n, size_t psize, long long np, int ch, void* scratch, size_t bytes, TileSort& ts) {
   if (!scratch || n < 128 || np < (1ll << 18) || np >= (1ll << 31)) return false;
   const size_t tiles = tile_count(n), chunks = (np + ch - 1) / ch;
