@@ -819,13 +819,15 @@ k_interp_scale(const ulonglong2* __restrict__ part, int blocks, unsigned long lo
 // the LDS atomics together.  A chunk of 1024 particles with one component after another in a 24 KB
 // histogram takes fewer of the first than one of 512 with all components at once (2.1M particles in
 // 8^3 blocks, three components, 128^3: 113 -> 98 us; 2048 particles 104 us); 512 below 2^18 particles,
-// where 1024 would leave the device idle.
+// where 1024 would leave the device idle, with a histogram of 2048 cells: boxes of small clustered loads
+// fit it and not 1536 (32768 particles on 32^3, the whole adjoint: one component 73 and 29 us, three 132
+// and 40 us).
 template <typename P, int CH, int NC>
 __global__ void __launch_bounds__(256)
 k_interp_grad_mesh_bin(const P* __restrict__ pos, long long np, int n, double scale, const double* __restrict__ g,
                        const unsigned long long* __restrict__ st, unsigned long long* __restrict__ acc) {
 #pragma clang fp contract(off)
-  constexpr int PPT = CH / 256, CAP = 3 * CH;
+  constexpr int PPT = CH / 256, CAP = (CH >= 1024 ? 3 : 4) * CH;
   __shared__ unsigned long long hist[CAP];
   const size_t n3 = (size_t)n * n * n;
   const int e = (int)(long long)st[2];

@@ -119,3 +119,19 @@ def test_row_groups_512_other_calls(dgp):
         # a warm start from the solution is decided by its first float64 evaluations
         st, info = plan.solve_field(gpu_params(dgp, tol=1e-8, lam=0.05, init=dgp.INIT_WARM), f, u)
         assert st == 0 and rel(u, u64) <= 1e-8
+
+
+# clustered loads whose chunks' boxes lie between one and four cells a particle: the scatter's histogram
+# takes those of four, and the sums are the oracle's either way
+@pytest.mark.parametrize("np_", [2 ** 15, 2 ** 18 + 300])
+def test_clustered_mesh_gradient(dgp, np_):
+    from oracle import adjoint
+    n, box = 32, 64.0
+    rng = np.random.default_rng(np_)
+    pos = (rng.normal(0.0, box / 20.0, (3, np_)) + 0.5 * box) % box
+    g, mesh = rng.standard_normal((3, np_)), rng.standard_normal((3, n, n, n))
+    _, ref = adjoint.interp_backward(mesh, pos, g, box)
+    with dgp.Plan(n, box) as plan:
+        gm = torch.zeros((3, n, n, n), dtype=torch.float64, device="cuda")
+        plan.interp_backward(None, to_dev(pos), to_dev(g), None, gm)
+    assert rel_l2(gm.cpu().numpy(), ref) <= 1e-12
