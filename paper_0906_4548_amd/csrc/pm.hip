@@ -159,14 +159,18 @@ __device__ __forceinline__ bool chunk_box(const P* __restrict__ pos, const P (&x
 }
 
 // the positions of the thread's particles in a chunk (unused slots past np left at 0); streaming
-// loads: a kernel reads each particle once
-template <int PPT, typename P>
+// loads unless STREAM is false: a kernel reads each particle once
+template <int PPT, bool STREAM = true, typename P>
 __device__ __forceinline__ void load_chunk(const P* __restrict__ a, long long np, long long p0, P (&xs)[PPT][3]) {
 #pragma unroll
   for (int k = 0; k < PPT; ++k) {
     const long long p = p0 + threadIdx.x + k * 256;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) xs[k][d] = p < np ? __builtin_nontemporal_load(&a[(size_t)d * np + p]) : P(0);
+    for (int d = 0; d < 3; ++d) {
+      const P* const x = &a[(size_t)d * np + p];
+      if constexpr (STREAM) xs[k][d] = p < np ? __builtin_nontemporal_load(x) : P(0);
+      else xs[k][d] = p < np ? *x : P(0);
+    }
   }
 }
 
@@ -566,9 +570,11 @@ __device__ __forceinline__ size_t corner_index(const Cic& c, int a, int b, int c
 // LDS staging of the particle gathers.  A workgroup takes a chunk of consecutive particles; when
 // the periodic box of their cells fits, the box's mesh values are staged in LDS (coalesced rows,
 // each cell read once) and the corners gathered from there, otherwise each corner is read from the
-// mesh.  What bounds the direct gather is the L2-to-L1 traffic of its rows (a wavefront of an 8^3
-// block touches ~24 lines of 128 bytes per component), which staging replaces by ~3.3 cells per
-// particle.
+// mesh.  What bounds the direct gather of several components is the L2-to-L1 traffic of its rows (a
+// wavefront of an 8^3 block touches ~24 lines of 128 bytes per component), which staging replaces by
+// ~3.3 cells per particle (2.1M particles in 8^3 blocks on 128^3, three components: 70 -> 35 us).  The
+// box search and its barriers cost what one component has to gain (19-20 us direct, 26-30 us staged),
+// so single components are gathered directly.
 #ifndef DGP_GATHER_CHUNK
 #define DGP_GATHER_CHUNK 256
 #endif
@@ -578,17 +584,40 @@ __device__ __forceinline__ size_t corner_index(const Cic& c, int a, int b, int c
 constexpr int kGatherChunk = DGP_GATHER_CHUNK;
 constexpr int kGatherPPT = kGatherChunk / 256;
 constexpr int kGatherCap = DGP_GATHER_BIN_CAP;
+// how a gather is run (gather_how); template argument of the gather kernels
+enum GatherHow : int {
+  kGatherStage = 1,    // several components: compact chunks through LDS
+  kGatherStream = 2,   // positions by streaming loads
+  kGatherXcd = 4,      // chunks in XCD order
+};
+template <int HOW>
+__device__ __forceinline__ long long gather_first() {   // the workgroup's first particle
+  return ((HOW & kGatherXcd) ? xcd_chunk() : (long long)blockIdx.x) * kGatherChunk;
+}
 static_assert(kGatherChunk % 256 == 0, "chunk must be a multiple of the workgroup size");
 
-// A chunk's box staged from the NC-component mesh [NC][N^3] into fl[NC][kGatherCap]; every thread of
-// the workgroup calls it, and `apply(p, k, cell, at)` then runs for each of the thread's particles
+// With kGatherStage, a chunk's box staged from the NC-component mesh [NC][N^3] into fl[NC][kGatherCap]; every
+// thread of the workgroup calls it, and `apply(p, k, cell, at)` then runs for each of the thread's particles
 // with at(a, b, c, component), the mesh value of a corner.
-template <int NC, typename P, typename M, class Apply>
+template <int NC, int HOW, typename P, typename M, class Apply>
 __device__ __forceinline__ void gather_chunk(const M* __restrict__ mesh, const P* __restrict__ pos,
                                              const P (&xs)[kGatherPPT][3], long long np, long long p0, int n,
                                              double scale, M* fl, const Apply& apply) {
 #pragma clang fp contract(off)
   const size_t n3 = (size_t)n * n * n;
+  if constexpr (!(HOW & kGatherStage)) {
+#pragma unroll
+    for (int k = 0; k < kGatherPPT; ++k) {
+      const long long p = p0 + threadIdx.x + k * 256;
+      if (p >= np) continue;
+      const double s3[3] = {double(xs[k][0]) * scale, double(xs[k][1]) * scale, double(xs[k][2]) * scale};
+      const Cic c = cic_at(s3, n);
+      apply(p, k, c, [&](int a, int b, int cc, int q) {
+        return double(mesh[(size_t)q * n3 + corner_index(c, a, b, cc, n)]);
+      });
+    }
+    return;
+  }
   Cic cr;
   int off[kGatherPPT][3], bx[6];
   const bool binned = chunk_box<kGatherPPT>(pos, xs, np, n, scale, p0, kGatherCap, cr, off, bx);
@@ -624,15 +653,15 @@ __device__ __forceinline__ void gather_chunk(const M* __restrict__ mesh, const P
 }
 
 // out[k][p] = sum_c W_c(x_p) mesh[k][c]
-template <typename P, typename M, int NC>
+template <typename P, typename M, int NC, int HOW>
 __global__ void __launch_bounds__(256)
 k_interp(const M* __restrict__ mesh, const P* __restrict__ pos, long long np, int n, double scale,
          double* __restrict__ out) {
-  __shared__ M fl[NC * kGatherCap];
-  const long long p0 = xcd_chunk() * kGatherChunk;
+  __shared__ M fl[(HOW & kGatherStage) ? NC * kGatherCap : 1];
+  const long long p0 = gather_first<HOW>();
   P xs[kGatherPPT][3];
-  load_chunk<kGatherPPT>(pos, np, p0, xs);
-  gather_chunk<NC>(mesh, pos, xs, np, p0, n, scale, fl, [&](long long p, int, const Cic& c, const auto& at) {
+  load_chunk<kGatherPPT, (HOW & kGatherStream) != 0>(pos, np, p0, xs);
+  gather_chunk<NC, HOW>(mesh, pos, xs, np, p0, n, scale, fl, [&](long long p, int, const Cic& c, const auto& at) {
     double f[NC];
     gather_corners<NC>(c, at, f);
 #pragma unroll
@@ -653,7 +682,7 @@ k_interp_kick_drift_bin(const M* __restrict__ mesh3, P* __restrict__ pos, P* __r
   P xs[kGatherPPT][3], vs[kGatherPPT][3];
   load_chunk<kGatherPPT>(pos, np, p0, xs);
   load_chunk<kGatherPPT>(vel, np, p0, vs);
-  gather_chunk<3>(mesh3, pos, xs, np, p0, n, scale, fl, [&](long long p, int k, const Cic& c, const auto& at) {
+  gather_chunk<3, kGatherStage>(mesh3, pos, xs, np, p0, n, scale, fl, [&](long long p, int k, const Cic& c, const auto& at) {
     double f[3];
     gather_corners<3>(c, at, f);
 #pragma unroll
@@ -697,15 +726,14 @@ __device__ __forceinline__ void gather_weight_grad(const Cic& c, double scale, c
 }
 
 // dL/dx_p = (N^3/Np) sum_c g_c dW_c/dx_p  (derivative of the unquantised weights)
-template <typename P>
+template <typename P, int HOW>
 __global__ void __launch_bounds__(256)
 k_deposit_backward(const P* __restrict__ pos, long long np, int n, double scale, const double* __restrict__ g,
                    double mass, double* __restrict__ grad) {
-  __shared__ double fl[kGatherCap];
-  const long long p0 = xcd_chunk() * kGatherChunk;
+  const long long p0 = gather_first<HOW>();
   P xs[kGatherPPT][3];
-  load_chunk<kGatherPPT>(pos, np, p0, xs);
-  gather_chunk<1>(g, pos, xs, np, p0, n, scale, fl, [&](long long p, int, const Cic& c, const auto& at) {
+  load_chunk<kGatherPPT, (HOW & kGatherStream) != 0>(pos, np, p0, xs);
+  gather_chunk<1, HOW>(g, pos, xs, np, p0, n, scale, (double*)nullptr, [&](long long p, int, const Cic& c, const auto& at) {
     double gx[3];
     gather_weight_grad(c, scale, [&](int a, int b, int cc) { return at(a, b, cc, 0); }, gx);
 #pragma unroll
@@ -725,15 +753,15 @@ k_deposit_backward(const P* __restrict__ pos, long long np, int n, double scale,
 // same positions bounds).
 
 // dL/dx_p: per particle, the 8 corners of its cell
-template <typename P, int NC>
+template <typename P, int NC, int HOW>
 __global__ void __launch_bounds__(256)
 k_interp_grad_pos(const double* __restrict__ mesh, const P* __restrict__ pos, long long np, int n, double scale,
                   const double* __restrict__ g, double* __restrict__ grad) {
-  __shared__ double fl[NC * kGatherCap];
-  const long long p0 = xcd_chunk() * kGatherChunk;
+  __shared__ double fl[(HOW & kGatherStage) ? NC * kGatherCap : 1];
+  const long long p0 = gather_first<HOW>();
   P xs[kGatherPPT][3];
-  load_chunk<kGatherPPT>(pos, np, p0, xs);
-  gather_chunk<NC>(mesh, pos, xs, np, p0, n, scale, fl, [&](long long p, int, const Cic& c, const auto& at) {
+  load_chunk<kGatherPPT, (HOW & kGatherStream) != 0>(pos, np, p0, xs);
+  gather_chunk<NC, HOW>(mesh, pos, xs, np, p0, n, scale, fl, [&](long long p, int, const Cic& c, const auto& at) {
     double gm[NC], gx[3];
 #pragma unroll
     for (int m = 0; m < NC; ++m) gm[m] = g[(size_t)m * np + p];
@@ -1003,16 +1031,38 @@ void launch_fill_zero(void* p, size_t words, hipStream_t s) {
 }
 
 
+// How a gather is run.  A load of less than a particle per four cells (thin) cannot fill boxes of kGatherCap
+// cells, and its chunks in dispatch order are as near to each other as in XCD order (2^18 particles on
+// 256^3 in 8^3 blocks: one component 10.9 us against 12.1 in XCD order, three components 30.0 us direct
+// against 33.8 staged).  Positions are streamed where what the kernel reads exceeds the 256 MB last-level
+// cache, and read with plain loads below (one component: 2.1M float64 particles in blocks on 128^3 16.2 us
+// plain, 19.1 us streamed; 4.2M on 256^3, 235 MB, 38 and 44 us; 16.8M float32, 335 MB, 129 and 104 us).
+// LAUNCH(HOW) for the chosen HOW:
+#define DGP_GATHER_LAUNCH(NC, thin, stream, LAUNCH)                                  \
+  {                                                                                  \
+    constexpr int dense = kGatherXcd | (NC > 1 ? kGatherStage : 0);                  \
+    if (thin && stream) LAUNCH(kGatherStream);                                       \
+    else if (thin) LAUNCH(0);                                                        \
+    else if (stream) LAUNCH(dense | kGatherStream);                                  \
+    else LAUNCH(dense);                                                              \
+  }
+static bool gather_thin(int n, long long np) { return 4 * np < (long long)n * n * n; }
+static bool gather_streams(size_t bytes) { return bytes > (size_t(256) << 20); }
+
+template <typename P, typename M, int NC>
+static void interp_t(int n, double box, const M* mesh, const P* pos, long long np, double* out, hipStream_t s) {
+  const double scale = double(n) / box;
+  const bool thin = gather_thin(n, np), stream = gather_streams(NC * sizeof(M) * n * n * n + 3 * sizeof(P) * np);
+#define L(HOW) \
+  hipLaunchKernelGGL((k_interp<P, M, NC, (HOW)>), dim3(gather_chunks(np)), dim3(256), 0, s, mesh, pos, np, n, scale, out)
+  DGP_GATHER_LAUNCH(NC, thin, stream, L)
+#undef L
+}
 template <typename M, int NC>
 static void interp_m(int n, double box, const M* mesh, const void* pos, int pos_fp32, long long np, double* out,
                      hipStream_t s) {
-  const double scale = double(n) / box;
-  if (pos_fp32)
-    hipLaunchKernelGGL((k_interp<float, M, NC>), dim3(gather_chunks(np)), dim3(256), 0, s, mesh,
-                       static_cast<const float*>(pos), np, n, scale, out);
-  else
-    hipLaunchKernelGGL((k_interp<double, M, NC>), dim3(gather_chunks(np)), dim3(256), 0, s, mesh,
-                       static_cast<const double*>(pos), np, n, scale, out);
+  if (pos_fp32) interp_t<float, M, NC>(n, box, mesh, static_cast<const float*>(pos), np, out, s);
+  else interp_t<double, M, NC>(n, box, mesh, static_cast<const double*>(pos), np, out, s);
 }
 
 void launch_interp(int n, double box, const void* mesh, int mesh_fp32, int nc, const void* pos, int pos_fp32,
@@ -1049,16 +1099,22 @@ void launch_interp_kick_drift(int n, double box, const void* mesh3, int mesh_fp3
     kick_m(n, box, static_cast<const double*>(mesh3), pos, vel, fp32, np, kick, drift, s);
 }
 
-void launch_deposit_backward(int n, double box, const void* pos, int pos_fp32, long long np, const double* grad_delta,
-                             double* grad_pos, hipStream_t s) {
+template <typename P>
+static void deposit_backward_t(int n, double box, const P* pos, long long np, const double* grad_delta, double* grad_pos,
+                               hipStream_t s) {
   const double scale = double(n) / box;
   const double mass = double(n) * n * n / double(np);
-  if (pos_fp32)
-    hipLaunchKernelGGL((k_deposit_backward<float>), dim3(gather_chunks(np)), dim3(256), 0, s,
-                       static_cast<const float*>(pos), np, n, scale, grad_delta, mass, grad_pos);
-  else
-    hipLaunchKernelGGL((k_deposit_backward<double>), dim3(gather_chunks(np)), dim3(256), 0, s,
-                       static_cast<const double*>(pos), np, n, scale, grad_delta, mass, grad_pos);
+  const bool thin = gather_thin(n, np), stream = gather_streams(sizeof(double) * n * n * n + 3 * sizeof(P) * np);
+#define L(HOW)                                                                                                          \
+  hipLaunchKernelGGL((k_deposit_backward<P, (HOW)>), dim3(gather_chunks(np)), dim3(256), 0, s, pos, np, n, scale, grad_delta, \
+                     mass, grad_pos)
+  DGP_GATHER_LAUNCH(1, thin, stream, L)
+#undef L
+}
+void launch_deposit_backward(int n, double box, const void* pos, int pos_fp32, long long np, const double* grad_delta,
+                             double* grad_pos, hipStream_t s) {
+  if (pos_fp32) deposit_backward_t(n, box, static_cast<const float*>(pos), np, grad_delta, grad_pos, s);
+  else deposit_backward_t(n, box, static_cast<const double*>(pos), np, grad_delta, grad_pos, s);
 }
 
 template <typename P, int NC>
@@ -1067,9 +1123,14 @@ static void interp_bwd_t(int n, double box, const double* mesh, const P* pos, lo
                          int* bad, void* scratch, size_t scratch_bytes, hipStream_t s) {
   const double scale = double(n) / box;
   const size_t n3 = (size_t)n * n * n;
-  if (grad_pos)
-    hipLaunchKernelGGL((k_interp_grad_pos<P, NC>), dim3(gather_chunks(np)), dim3(256), 0, s, mesh, pos, np, n, scale, g,
-                       grad_pos);
+  if (grad_pos) {
+    const bool thin = gather_thin(n, np), stream = gather_streams(8 * NC * n3 + (3 * sizeof(P) + 8 * NC) * np);
+#define L(HOW)                                                                                                           \
+  hipLaunchKernelGGL((k_interp_grad_pos<P, NC, (HOW)>), dim3(gather_chunks(np)), dim3(256), 0, s, mesh, pos, np, n, scale, \
+                     g, grad_pos)
+    DGP_GATHER_LAUNCH(NC, thin, stream, L)
+#undef L
+  }
   if (!grad_mesh) return;
   auto* acc = reinterpret_cast<unsigned long long*>(grad_mesh);
   launch_fill_zero(acc, NC * n3, s);

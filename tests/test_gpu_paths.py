@@ -135,3 +135,30 @@ def test_clustered_mesh_gradient(dgp, np_):
         gm = torch.zeros((3, n, n, n), dtype=torch.float64, device="cuda")
         plan.interp_backward(None, to_dev(pos), to_dev(g), None, gm)
     assert rel_l2(gm.cpu().numpy(), ref) <= 1e-12
+
+
+# gathers that read more than the last-level cache stream the positions: thin and dense loads at 256^3, compared
+# with the oracle on every 37th particle (particles do not depend on each other)
+@pytest.mark.parametrize("np_,fp32", [(4003, False), (2 ** 22 + 5, False), (2 ** 22 + 5, True)])
+def test_streamed_gathers_256(dgp, np_, fp32):
+    from oracle import adjoint, pm
+    n, box, nc = 256, 512.0, 2
+    pos = _positions(n, np_, "random", fp32)
+    pos[:, :np_ // 2] = np.sort(pos[:, :np_ // 2], axis=1)   # compact chunks beside spread ones
+    rng = np.random.default_rng(np_)
+    mesh, g = rng.standard_normal((nc, n, n, n)), rng.standard_normal((nc, np_))
+    with dgp.Plan(n, box) as plan:
+        tp, tm = torch.from_numpy(pos).cuda(), to_dev(mesh)
+        out = torch.zeros((nc, np_), dtype=torch.float64, device="cuda")
+        plan.interp(tm, tp, out)
+        gp = torch.zeros((3, np_), dtype=torch.float64, device="cuda")
+        plan.interp_backward(tm, tp, to_dev(g), gp, None)
+        gd = torch.zeros((3, np_), dtype=torch.float64, device="cuda")
+        plan.deposit_backward(tp, tm[0].contiguous(), gd)
+    some = np.arange(0, np_, 37)
+    sub = pos[:, some].astype(np.float64)
+    refp, _ = adjoint.interp_backward(mesh, sub, g[:, some], box)
+    refd = adjoint.deposit_backward(sub, mesh[0], box) * (some.size / np_)   # its factor is N^3 / np
+    assert rel_l2(out.cpu().numpy()[:, some], pm.cic_interpolate(mesh, sub, box)) <= 1e-12
+    assert rel_l2(gp.cpu().numpy()[:, some], refp) <= 1e-12
+    assert rel_l2(gd.cpu().numpy()[:, some], refd) <= 1e-12
