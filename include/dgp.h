@@ -260,11 +260,13 @@ int dgp_fft_inverse(dgp_plan* plan, const double* spectrum, double* field, void*
  * returning).  Enabling resets the counters.  Classes with the DGP_T_FP32_OFFSET
  * added are the float32 launches of the precision form. */
 enum {
-  DGP_T_AXIS1_FWD = 0,   /* forward axis-1 pass of the iterate's spectrum, per relaxation pass */
-  DGP_T_FANOUT = 1,      /* axis-2 pass: forward FFT, 3 spectral multipliers, 3 inverse FFTs */
-  DGP_T_AXIS1_INV = 2,   /* inverse axis-1 pass: 3 spectra in, 6 out (axis-1 factors) */
+  DGP_T_AXIS1_FWD = 0,   /* forward axis-1 pass of the iterate's spectrum, per relaxation pass (N >= 128) */
+  DGP_T_FANOUT = 1,      /* axis-2 pass: forward FFT, 3 spectral multipliers, 3 inverse FFTs; up to N = 64 one
+                            launch for it and both axis-1 passes, which also decides the previous pass */
+  DGP_T_AXIS1_INV = 2,   /* inverse axis-1 pass: 3 spectra in, 6 out (axis-1 factors) (N >= 128) */
   DGP_T_RELAX = 3,       /* fused axis-0 inverse of 6 spectra + pointwise update + axis-0 forward */
-  DGP_T_FINALIZE = 4,    /* residual reduction and stopping rules */
+  DGP_T_FINALIZE = 4,    /* residual reduction and stopping rules; up to N = 64 only of the last pass before the
+                            host reads the control blocks (DGP_T_FANOUT holds the others) */
   DGP_T_SETUP = 5,       /* source S, eps and linear guess from delta */
   DGP_T_DEPOSIT = 6,     /* CIC deposit and density contrast */
   DGP_T_FORCES = 7,      /* modified Poisson + gradient: force mesh */

@@ -16,7 +16,6 @@ enum SpecMode : int {
   SPEC_FORCES = 3,    // delta(k)[, u(k)] -> phi(k) (slot 0) and g_2 = -(c/H0)^2 i k_2 phi(k) (slot 2)
   SPEC_POWER_GRAD = 5,// f(k) -> per-bin coefficient * f(k) [* 1/kbar^4]
   SPEC_ADJ_COMBINE3 = 6,// the three group sums of launch_p2_adj_split -> one combined spectrum
-  SPEC_COPY = 7,      // identity (plain forward+inverse round trip, for tests)
   SPEC_FWD_ONLY = 8,  // forward axis-2 transform only (spectrum export)
   SPEC_INV_ONLY = 9,  // inverse axis-2 transform only, times 1/N^3 (spectrum import)
   SPEC_HSPLIT = 10,   // u(k) -> C' = u/|n|^2, i n2 C' and -u/kbar into slots 0, 3 and 5 of the six
@@ -208,7 +207,8 @@ void launch_p2_adj_split(int n, cx<double>* data, size_t fstride, int batch, dou
 // g0, g1, g2 in slots 0..2 and phi in slot 3 when with_phi; fk = (c/H0)^2 kf
 template <typename T>
 void launch_p2_force_split(int n, cx<T>* data, size_t fstride, int batch, int with_phi, double fk, hipStream_t s);
-// axis-2 pass: nin input arrays (each [batch][H][N][N]) -> nout output arrays
+// axis-2 pass: nin input arrays (each [batch][H][N][N]) -> nout output arrays.  SPEC_HSPLIT, SPEC_FORCES and
+// SPEC_CFIELD above kPlaneMax only: launch_plane does all three stages on the smaller meshes
 template <typename T>
 void launch_p3(int n, SpecMode mode, const cx<T>* in, size_t in_stride, int nin, cx<T>* out,
                size_t out_stride, int nout, int batch, const SpecCoef& coef, const double* bin_coef,

@@ -667,8 +667,6 @@ k_p3(const cx<T>* __restrict__ in, size_t in_stride, cx<T>* __restrict__ out, si
           const double ikb = 1.0 / kb;
           if constexpr (MODE == SPEC_CFIELD) {
             res = scale(v[q], T(-ikb * ikb * cf.inv_n3));
-          } else if constexpr (MODE == SPEC_COPY) {
-            res = scale(v[q], T(cf.inv_n3));
           } else if constexpr (MODE == SPEC_POWER_GRAD) {
             double coef = 0.0;
             const double* thr = bin_coef;
@@ -880,7 +878,6 @@ static void p3_n(SpecMode mode, const cx<T>* in, size_t is, cx<T>* out, size_t o
     case SPEC_SOURCE: DGP_P3(SPEC_SOURCE); break;
     case SPEC_POWER_GRAD: DGP_P3(SPEC_POWER_GRAD); break;
     case SPEC_ADJ_COMBINE3: DGP_P3(SPEC_ADJ_COMBINE3); break;
-    case SPEC_COPY: DGP_P3(SPEC_COPY); break;
     case SPEC_FWD_ONLY: DGP_P3(SPEC_FWD_ONLY); break;
     case SPEC_INV_ONLY: DGP_P3(SPEC_INV_ONLY); break;
     case SPEC_CFIELD:

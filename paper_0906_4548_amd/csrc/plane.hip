@@ -51,10 +51,10 @@ struct PlaneRow {   // exchanges of row r (inside one wavefront)
   __device__ __forceinline__ void sync() const { wave_sync(); }
 };
 
-// Decision of the previous pass at the start of a relaxation plane launch: every workgroup adds the
-// partial sums of its element (while its plane is being loaded) and so knows whether the element is
-// done; the workgroup with `write` records the decision in the next control blocks.  A launch of its
-// own for this takes 3.5 us and a gap, of a 26-31 us pass.  Returns whether the element is done.
+// Decision of the previous pass at the start of a relaxation plane launch, before the plane is loaded:
+// every workgroup adds the partial sums of its element and so knows whether the element is done; the
+// workgroup with `write` records the decision in the next control blocks.  A launch of its own for
+// this takes 3.5 us and a gap, of a 26-31 us pass.  Returns whether the element is done.
 template <int NT>
 __device__ __forceinline__ bool decide_pass(const PassDecision& d, int b, bool write) {
   const SolveCtl& C = d.prev[b];

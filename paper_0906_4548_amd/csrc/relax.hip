@@ -15,9 +15,9 @@
 //   3. writes u^(n+1) and immediately forward-transforms it along axis 0, so
 //      the next pass starts from its axis-0 spectrum;
 //   4. reduces sum |R| (FP64) and the bad-point count per workgroup.
-// A single-workgroup kernel then forms r = <|R|>/eps (Eq. normres) per batch
-// element and runs the stopping rules; kernels of later passes read the
-// per-element `done` flag and exit at once.
+// k_finalize (one workgroup per batch element) or, up to 64^3, the next pass's plane
+// launch then forms r = <|R|>/eps (Eq. normres) and runs the stopping rules; kernels of
+// later passes read the per-element `done` flag and exit at once.
 #include <algorithm>
 #include <type_traits>
 
